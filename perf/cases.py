@@ -213,7 +213,7 @@ def tolerance(case):
     # rows lie far below its root mean square: 0.6 at the largest entry)
     if case["dtype"] == "f32":
         return {"rel": 4e-6, "max": 4e-4}
-    return {"rel": 1e-2, "max": 1.0, "differ": 0.01}
+    return {"rel": 1e-2, "max": 0.9, "differ": 0.01}
 
 
 def exact(case, seed):
