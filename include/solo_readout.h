@@ -96,8 +96,9 @@ size_t solo_readout_workspace_size(int K, int T, int d, int V, int dtype, int fi
  * 64 rows up to d = 1024 and 32 above, twice that in the forward-only
  * passes), "mfma_wide" (bf16 matrix-core kernels, d = 2560; 16-row tiles, 48
  * in the forward-only passes) or
- * "valu" (fp32 vector-ALU kernels, used for SOLO_F32 and for every other bf16
- * width).  Returns "invalid" for arguments solo_readout_fwd_bwd would reject.
+ * "valu" (the fp32 family, for SOLO_F32 and for every other bf16 width: fp32
+ * products and sums, on the fp32 matrix instructions; the name is that of the
+ * vector-ALU kernels that served these calls first).  Returns "invalid" for arguments solo_readout_fwd_bwd would reject.
  */
 const char* solo_readout_kernel_family(int K, int T, int d, int V, int dtype);
 

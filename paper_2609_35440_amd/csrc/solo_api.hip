@@ -42,14 +42,14 @@ struct Plan {
     size_t wtile = 0, whtile = 0, total = 0;
     // ROT pieces: a vector of ones (the rotated rows' gain), the rotated rows
     // u, the heads' e = sum_v delta_v Wbar_v (4 bytes per element: two bf16
-    // planes, or fp32 on the vector-ALU family), D = e R_k (fp32), R_k^T
+    // planes, or fp32 on the fp32 family), D = e R_k (fp32), R_k^T
     size_t ones = 0, ubuf = 0, ebuf = 0, dbuf = 0, rtr = 0;
 };
 
 // Which passes stream tiled copies: every pass of the wide tiling; in the
 // 16-row tiling the passes without a second product (exit evaluation, bias
 // gradient), which read their operand straight into registers.  The others
-// (and the vector-ALU family) read the row-major matrices.
+// (and the fp32 family) read the row-major matrices.
 bool tiled_readout(const Plan& P) { return P.wide || (P.mfma && P.eval); }
 bool tiled_rgrad(const Plan& P) { return P.wide; }
 
@@ -83,7 +83,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
         P->whtile = off;
         off = align_up(off + tv * P->nhead_tiles);
     }
-    const int rows = P->wide ? solo::kMfmaWideRows : (P->mfma ? solo::mfma_rows(d) : solo::kValuRows);
+    const int rows = P->wide ? solo::kMfmaWideRows : (P->mfma ? solo::mfma_rows(d) : solo::f32_rows(d));
     P->rows = rows;
     P->ntiles = (T + rows - 1) / rows;
     P->rot = a.rot != nullptr && K > 1;
@@ -145,9 +145,38 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     P->rowdtau = off;
     off = align_up(off + (a.dtau ? kt * 4 : 0));
     P->dgp = off;
-    off = align_up(off + (size_t)P->slots * P->ntiles * d * 4);
+    // (the fp32 family's partials leave part of their piece unused: it holds one per 8 rows)
+    const size_t dg_tiles = P->mfma ? (size_t)P->ntiles : ((size_t)T + solo::kF32GainRows - 1) / solo::kF32GainRows;
+    off = align_up(off + (size_t)P->slots * dg_tiles * d * 4);
     P->total = off;
     return true;
+}
+
+// Over how many workgroups a row tile of the local-loss pass over n modules is
+// split along the vocabulary: one while the tiles fill the chip's 256 CUs
+// (these kernels run one workgroup per CU); with fewer tiles, the number with
+// the least time by the matrix work of a workgroup's chunks (4 R d clocks per
+// chunk of 256 readout rows at the fp32 matrix rate, 70% of it reached) plus
+// the merge (its launch, and the partial sums written and read once).  The
+// partial sums live in an output that the readout-gradient pass overwrites
+// later, so only calls that compute one are split, as far as it holds them:
+// `room` floats.
+int f32_splits(const Plan& P, int n, int K, int T, int d, int V, size_t room) {
+    const long long tiles = (long long)P.ntiles * n;
+    const long long nch = ((long long)V + 255) / 256;
+    int best = 1;
+    double best_us = 0.0;
+    for (int s = 1; s <= solo::kMaxSplit && s <= nch; ++s) {
+        if (s > 1 && ((double)s * K * T * (d + 4) > (double)room || tiles * (s - 1) >= 512)) break;
+        const double rounds = (double)((tiles * s + 255) / 256), per = (double)((nch + s - 1) / s);
+        double us = rounds * per * 4.0 * P.rows * d / 1.6e3;
+        if (s > 1) us += 6.0 + (double)s * n * T * d * 8.0 / 3e6;
+        if (s == 1 || us < best_us) {
+            best = s;
+            best_us = us;
+        }
+    }
+    return best;
 }
 
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
@@ -204,6 +233,7 @@ int run(const solo_readout_args& x, bool eval) {
     a.V = V;
     a.m0 = 0;
     a.inv_T = (float)(1.0 / (double)T);
+    a.nsplit = 1;
     a.h = x.h;
     a.Wt = x.W;
     // heads: W itself, one shared matrix, or one per head
@@ -262,28 +292,40 @@ int run(const solo_readout_args& x, bool eval) {
         ah.ebuf = eval ? nullptr : (void*)(ws + P.ebuf);
     }
     if (!mark(0)) return SOLO_ERR_HIP;
+    // scratch of split local-loss passes: a readout gradient, written by a later pass
+    float* const room = eval ? nullptr : (x.final_module_dW ? x.dW : (P.rg_hi > P.rg_lo ? x.dWbar : nullptr));
+    const size_t room_floats = room ? (size_t)V * d : 0;
     // one launch over modules [m0, m0 + n) of a pass, with the arguments g
     auto pass = [&](int which, const solo::FusedArgs& g, int m0, int n) -> hipError_t {
         if (n <= 0) return hipSuccess;
         solo::FusedArgs b = g;
         b.m0 = m0;
+        if (which == 1 && !P.mfma) {
+            b.nsplit = f32_splits(P, n, K, T, d, V, room_floats);
+            if (b.nsplit > 1) {
+                b.split_acc = room;
+                b.split_stat = room + (size_t)b.nsplit * K * T * d;
+                const hipError_t e = solo::launch_local_loss_f32(dt, b, n, s);
+                return e != hipSuccess ? e : solo::launch_merge(dt, true, b, n, P.rows, s);
+            }
+        }
         switch (which) {
             case 0:
                 return P.wide   ? solo::launch_exit_eval_mfma_wide(b, n, s)
                        : P.mfma ? solo::launch_exit_eval_mfma(b, n, s)
-                                : solo::launch_exit_eval_valu(dt, b, n, s);
+                                : solo::launch_exit_eval_f32(dt, b, n, s);
             case 1:
                 return P.wide   ? solo::launch_local_loss_mfma_wide(b, P.ext, n, s)
                        : P.mfma ? solo::launch_local_loss_mfma(b, P.ext, n, s)
-                                : solo::launch_local_loss_valu(dt, b, n, s);
+                                : solo::launch_local_loss_f32(dt, b, n, s);
             case 2:
                 return P.wide   ? solo::launch_readout_grad_mfma_wide(b, n, s)
                        : P.mfma ? solo::launch_readout_grad_mfma(b, n, s)
-                                : solo::launch_readout_grad_valu(dt, b, n, s);
+                                : solo::launch_readout_grad_f32(dt, b, n, s);
             default:
                 return P.wide   ? solo::launch_bias_grad_mfma_wide(b, n, s)
                        : P.mfma ? solo::launch_bias_grad_mfma(b, n, s)
-                                : solo::launch_bias_grad_valu(dt, b, n, s);
+                                : solo::launch_bias_grad_f32(dt, b, n, s);
         }
     };
     // modules [lo, hi) of a pass: under ROT the heads and the terminal are two launches

@@ -52,7 +52,7 @@ struct FusedArgs {
     const float* rstd;    // [K][T] 1/sqrt(mean h^2 + eps)
     float* lse;           // [K][T] log-sum-exp of the logits (written by the local-loss pass)
     float* rowrec;        // [K][T][4] or null: {lse log2 e, r tau log2 e, target bits, p_y - 1} per token
-                          // (the vector-ALU family reads only p_y - 1)
+                          // (the fp32 family reads only p_y - 1)
     float* rowloss;       // [K][T] per-token cross-entropy
     float* rowdtau;       // [K][T] or null: per-token share of d loss / d tau
     int32_t* top1;        // [K][T] or null: exit evaluation, argmax of the logits (lowest index on ties)
@@ -67,13 +67,17 @@ struct FusedArgs {
                           // gradient is rotated back afterwards).  Row m = k T + t holds 4 d bytes: the
                           // matrix-core families write two bf16 planes, hi = bf16(e) at [0, d) and
                           // lo = bf16(e - hi) at [d, 2d) (the rotate-back product's operand as a 2d-deep
-                          // bf16 row); the vector-ALU family writes e in fp32
+                          // bf16 row); the fp32 family writes e in fp32
+    int nsplit;           // local-loss pass: workgroups the vocabulary of a row tile is split over (grid z)
+    float* split_acc;     // nsplit > 1: [nsplit][K T][d] unnormalised sums of exp(z - m) R_v of each split
+    float* split_stat;    // nsplit > 1: [nsplit][K T][4] {m (base 2), sum without the target, target logit, -}
 };
 
 // Tile sizes of the two kernel families (the workspace depends on them).
 constexpr int kMfmaRows = 32;      // stationary rows per workgroup of the matrix-core kernels at d > 1024
 constexpr int kMfmaWideRows = 16;  // stationary rows per workgroup (wide matrix-core kernels, d = 2560)
-constexpr int kValuRows = 8;       // stationary rows per workgroup (vector-ALU kernels)
+constexpr int kF32GainRows = 8;    // token rows per gain-gradient partial that the fp32 family's workspace is sized for
+int f32_rows(int d);               // stationary rows per workgroup of the fp32 kernels at width d (32 or 16)
 
 // small kernels (k_small.hip)
 hipError_t launch_row_rstd(int dtype, const void* h, float* rstd, long long rows, int d, float eps, hipStream_t s);
@@ -105,8 +109,12 @@ hipError_t launch_local_loss_mfma_wide(const FusedArgs& a, bool ext, int nmod, h
 hipError_t launch_exit_eval_mfma_wide(const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_readout_grad_mfma_wide(const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_bias_grad_mfma_wide(const FusedArgs& a, int nmod, hipStream_t s);
-hipError_t launch_local_loss_valu(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
-hipError_t launch_exit_eval_valu(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
+hipError_t launch_local_loss_f32(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
+hipError_t launch_exit_eval_f32(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
+// the tokens' ends of a local-loss pass split over the vocabulary, modules m0 .. m0 + nmod - 1, gain partials
+// per tile of rows tokens (k_merge.hip)
+hipError_t launch_merge(int dtype, bool f32fam, const FusedArgs& a, int nmod, int rows, hipStream_t s);
+constexpr int kMaxSplit = 64;  // splits of one row tile (a lane of the merge each)
 // ROT (k_rot.hip): C = A B^T per matrix; transposes; a vector of ones; the
 // heads' RMSNorm backward from the rotated-back gradient D = e R_k
 // u[m] = bf16(R_m bf16(g_m * h_m)) per row, heads m < nmat (gain g_m at gain + m g_stride)
@@ -122,7 +130,7 @@ hipError_t launch_fill_one(int dtype, void* p, int n, hipStream_t s);
 hipError_t launch_rot_post(int dtype, const float* D, const void* h, const void* gain, int g_stride,
                            const float* rstd, const float* tau, void* dh, float* dgain_part, int nmod, int T, int d,
                            int rows, hipStream_t s);
-hipError_t launch_readout_grad_valu(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
-hipError_t launch_bias_grad_valu(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
+hipError_t launch_readout_grad_f32(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
+hipError_t launch_bias_grad_f32(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
 
 }  // namespace solo
