@@ -133,7 +133,9 @@ const char* solo_readout_kernel_family(int K, int T, int d, int V, int dtype);
  *                   contents on entry do not matter and are clobbered.
  *   hip_stream      hipStream_t to enqueue on (NULL = default stream).
  *
- * Semantics: outputs are overwritten (never accumulated).  Inputs, outputs
+ * Semantics: outputs are overwritten (never accumulated); until the stream
+ * has passed the call an output may hold intermediate sums (a call of few
+ * tokens uses dW as scratch before it writes it).  Inputs, outputs
  * and workspace must not overlap.  The call only enqueues work and returns;
  * outputs are valid once the stream has reached this point, and inputs must
  * stay unchanged until then.  The library allocates no memory, keeps no

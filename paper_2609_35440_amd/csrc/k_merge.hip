@@ -8,8 +8,16 @@
 //   e = (sum a_s P_s / s + (p_y - 1) R_y) / T, dhhat = tau e, and the RMSNorm
 //   backward, or e to the rotate-back buffer for ROT heads.
 //
-// One row per wave (its mean is a wave reduction), e kept in registers between
-// the two sweeps; fixed order throughout.  Bound by reading P once.
+// One workgroup per row (its mean is a workgroup reduction), e kept in registers
+// between the two sweeps; fixed order throughout.  For a module that trains its
+// gain e goes back to the first split's part of the row, and k_merge_dgain forms
+// the token tiles' partials of sum_t dhhat_t n_t from it.  Bound by reading P
+// once; a row per wave with the gain partials in the same kernel left 64 rows
+// of 64 splits to 16 waves (565 us at d = 2048).
+//
+// Measured (fp32, K=2, T=1001, d=768, V=8003: 64 tiles): 2.22 ms per training
+// call with one workgroup per tile, 0.99 split.  bf16 exit evaluation of 4 x 16
+// rows, d=2048, V=32000: 2.10 ms on 4 workgroups, 0.09 split.
 #include "mfma_common.h"
 
 namespace solo {
@@ -28,132 +36,186 @@ template <typename E> __device__ __forceinline__ void st4(E* p, f32x4 v) {
     *(EV*)p = EV{(E)v[0], (E)v[1], (E)v[2], (E)v[3]};
 }
 
-constexpr int kQ = 16;  // 256-column groups of the widest row (4096)
+constexpr int kQ = 4;  // 1024-column groups of the widest row (4096)
 
 // FAM: the records the family's gradient passes read (see FusedArgs::rowrec)
 template <typename E, bool F32FAM>
-__global__ __launch_bounds__(256) void k_merge(FusedArgs a, int rows) {
-    extern __shared__ __attribute__((aligned(16))) float pbuf[];  // [4][d] when the module trains its gain
+__global__ __launch_bounds__(256) void k_merge(FusedArgs a) {
+    __shared__ float red[4];
     const int k = a.m0 + (int)blockIdx.y;
-    const int tile = blockIdx.x;
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
     const int d = a.d;
     const long long KT = (long long)a.K * a.T;
+    const long long row = (long long)k * a.T + blockIdx.x;
     const float tau = a.tau ? a.tau[k] : 1.f;
     const E* g = (const E*)a.gain + (long long)k * a.g_stride;
     const E* Rk = k == a.K - 1 ? (const E*)a.Wt : (const E*)a.Wh + (long long)k * a.wh_stride;
     const bool want_dg = !a.ebuf && (a.dg_mode == 2 || (a.dg_mode == 1 && k == a.K - 1));
-    float* pw = pbuf + w * d;
-    if (want_dg)
-        for (int j = lane; j < d; j += 64) pw[j] = 0.f;
-    for (int tr = w; tr < rows; tr += 4) {
-        const int t = tile * rows + tr;
-        if (t >= a.T) break;
-        const long long row = (long long)k * a.T + t;
-        // lane s holds split s
-        f32x4 st = {-INFINITY, 0.f, 0.f, 0.f};
-        if (lane < a.nsplit) st = *(const f32x4*)(a.split_stat + 4 * (lane * KT + row));
-        float m = st[0], sx, zy = st[2];
-        for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-        const float al = st[0] == m ? 1.f : __builtin_amdgcn_exp2f(st[0] - m);
-        sx = lane < a.nsplit ? al * st[1] : 0.f;
-        for (int off = 32; off > 0; off >>= 1) {
-            sx += __shfl_xor(sx, off, 64);
-            zy += __shfl_xor(zy, off, 64);
+    // lane s of every wave holds split s
+    f32x4 st = {-INFINITY, 0.f, 0.f, 0.f};
+    if (lane < a.nsplit) st = *(const f32x4*)(a.split_stat + 4 * (lane * KT + row));
+    float m = st[0], zy = st[2];
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    const float al = st[0] == m ? 1.f : __builtin_amdgcn_exp2f(st[0] - m);
+    float sx = lane < a.nsplit ? al * st[1] : 0.f;
+    for (int off = 32; off > 0; off >>= 1) {
+        sx += __shfl_xor(sx, off, 64);
+        zy += __shfl_xor(zy, off, 64);
+    }
+    const int tgt = a.targets[row];
+    const bool tok = tgt >= 0 && tgt < a.V;
+    const RowEnd re = finish_row(m, sx, zy, tok);
+    const float r = a.rstd[row];
+    if (threadIdx.x == 0) {
+        a.rowloss[row] = re.loss;
+        if (a.rowrec) {
+            const f32x4 r4 = {F32FAM ? m : re.lse2, r * tau * kLog2e, __int_as_float(tgt), re.py1};
+            *(f32x4*)(a.rowrec + 4 * row) = r4;
         }
-        const int tgt = a.targets[row];
-        const bool tok = tgt >= 0 && tgt < a.V;
-        const RowEnd re = finish_row(m, sx, zy, tok);
-        const float r = a.rstd[row];
-        if (lane == 0) {
-            a.rowloss[row] = re.loss;
-            if (a.rowrec) {
-                const f32x4 r4 = {F32FAM ? m : re.lse2, r * tau * kLog2e, __int_as_float(tgt), re.py1};
-                *(f32x4*)(a.rowrec + 4 * row) = r4;
-            }
-            a.lse[row] = F32FAM ? re.inv_s : re.lse2 * kLn2;
+        a.lse[row] = F32FAM ? re.inv_s : re.lse2 * kLn2;
+    }
+    const E* hr = (const E*)a.h + row * d;
+    const E* wr = Rk + (long long)(tok ? tgt : 0) * d;
+    const int j0 = 4 * threadIdx.x;
+    f32x4 ev[kQ];
+    float c = 0.f;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+        const int j = 1024 * q + j0;
+        if (j >= d) break;
+        f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
+        const float* p = a.split_acc + row * d + j;
+#pragma unroll 8
+        for (int s = 0; s < a.nsplit; ++s) {
+            // (a lane read: lane s itself may be past the width here)
+            const float as = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), s));
+            const f32x4 pv = *(const f32x4*)(p + s * KT * d);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s4[e] = __builtin_fmaf(as, pv[e], s4[e]);
         }
-        const E* hr = (const E*)a.h + row * d;
-        const E* wr = Rk + (long long)(tok ? tgt : 0) * d;
-        f32x4 ev[kQ];
-        float c = 0.f;
+        const f32x4 wv = ld4(wr + j), gv = ld4(g + j), hv = ld4(hr + j);
 #pragma unroll
-        for (int q = 0; q < kQ; ++q) {
-            const int j = 256 * q + 4 * lane;
-            if (256 * q >= d) break;
-            f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
-            if (j < d) {
-                const float* p = a.split_acc + row * d + j;
-                for (int s = 0; s < a.nsplit; ++s) {
-                    // (a lane read: lane s itself may be past the width here)
-                    const float as = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(al), s));
-                    const f32x4 pv = *(const f32x4*)(p + s * KT * d);
+        for (int e = 0; e < 4; ++e) {
+            s4[e] = __builtin_fmaf(s4[e], re.inv_s, re.py1 * (tok ? wv[e] : 0.f)) * a.inv_T;
+            c = __builtin_fmaf(gv[e] * s4[e], r * hv[e], c);
+        }
+        ev[q] = s4;
+    }
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    if (lane == 0) red[w] = c;
+    __syncthreads();
+    c = (red[0] + red[1]) + (red[2] + red[3]);
+    if (a.rowdtau && threadIdx.x == 0) a.rowdtau[row] = tok ? c : 0.f;
+    const float cm = tau * c / (float)d;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) s4[e] = __builtin_fmaf(as, pv[e], s4[e]);
-                }
-                const f32x4 wv = ld4(wr + j), gv = ld4(g + j), hv = ld4(hr + j);
+    for (int q = 0; q < kQ; ++q) {
+        const int j = 1024 * q + j0;
+        if (j >= d) break;
+        if (a.ebuf) {
+            if (F32FAM) {
+                *(f32x4*)((float*)a.ebuf + row * d + j) = ev[q];
+            } else {
+                bf16x4 hi, lo;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    s4[e] = __builtin_fmaf(s4[e], re.inv_s, re.py1 * (tok ? wv[e] : 0.f)) * a.inv_T;
-                    c = __builtin_fmaf(gv[e] * s4[e], r * hv[e], c);
+                    hi[e] = (bf16)ev[q][e];
+                    lo[e] = (bf16)(ev[q][e] - (float)hi[e]);
                 }
+                bf16* er = (bf16*)a.ebuf + row * (2LL * d);
+                *(bf16x4*)(er + j) = hi;
+                *(bf16x4*)(er + d + j) = lo;
             }
-            ev[q] = s4;
+            continue;
         }
-        for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-        if (a.rowdtau && lane == 0) a.rowdtau[row] = tok ? c : 0.f;
-        const float cm = tau * c / (float)d;
+        const f32x4 gv = ld4(g + j), hv = ld4(hr + j);
+        f32x4 o;
 #pragma unroll
-        for (int q = 0; q < kQ; ++q) {
-            const int j = 256 * q + 4 * lane;
-            if (256 * q >= d) break;
-            if (j >= d) continue;
-            if (a.ebuf) {
-                if (F32FAM) {
-                    *(f32x4*)((float*)a.ebuf + row * d + j) = ev[q];
-                } else {
-                    bf16x4 hi, lo;
+        for (int e = 0; e < 4; ++e) o[e] = r * (gv[e] * (tau * ev[q][e]) - cm * (r * hv[e]));
+        st4((E*)a.dh + row * d + j, o);
+        if (want_dg) *(f32x4*)(a.split_acc + row * d + j) = ev[q];
+    }
+}
+
+// The token tiles' partials of dgain = sum_t tau e_t n_t: one thread per four
+// columns of a tile of `rows` tokens.
+template <typename E>
+__global__ __launch_bounds__(256) void k_merge_dgain(FusedArgs a, int rows) {
+    const int k = a.m0 + (int)blockIdx.y;
+    if (a.dg_mode == 1 && k != a.K - 1) return;
+    const int j = 4 * (blockIdx.z * 256 + threadIdx.x);
+    if (j >= a.d) return;
+    const int t0 = blockIdx.x * rows;
+    const int t1 = t0 + rows < a.T ? t0 + rows : a.T;
+    const float tau = a.tau ? a.tau[k] : 1.f;
+    f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int t = t0; t < t1; ++t) {
+        const long long row = (long long)k * a.T + t;
+        const float r = a.rstd[row];
+        const f32x4 ev = *(const f32x4*)(a.split_acc + row * a.d + j);
+        const f32x4 hv = ld4((const E*)a.h + row * a.d + j);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        hi[e] = (bf16)ev[q][e];
-                        lo[e] = (bf16)(ev[q][e] - (float)hi[e]);
-                    }
-                    bf16* er = (bf16*)a.ebuf + row * (2LL * d);
-                    *(bf16x4*)(er + j) = hi;
-                    *(bf16x4*)(er + d + j) = lo;
-                }
-                continue;
-            }
-            const f32x4 gv = ld4(g + j), hv = ld4(hr + j);
-            f32x4 o, pv;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float dhat = tau * ev[q][e];
-                const float n = r * hv[e];
-                o[e] = r * (gv[e] * dhat - cm * n);
-                pv[e] = dhat * n;
-            }
-            st4((E*)a.dh + row * d + j, o);
-            if (want_dg) *(f32x4*)(pw + j) += pv;
+        for (int e = 0; e < 4; ++e) s4[e] = __builtin_fmaf(tau * ev[e], r * hv[e], s4[e]);
+    }
+    *(f32x4*)(a.dgain_part + ((long long)(a.dg_mode == 2 ? k : 0) * gridDim.x + blockIdx.x) * a.d + j) = s4;
+}
+
+// Exit evaluation split over the vocabulary: the row's loss and top-1 (the
+// larger logit, then the lower column) from the splits' parts; one row per wave.
+__global__ __launch_bounds__(256) void k_merge_eval(FusedArgs a, long long rows) {
+    const int lane = threadIdx.x & 63;
+    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= rows) return;
+    float m = -INFINITY, s_own = 0.f, zy = 0.f, best = -INFINITY;
+    int best_v = -1;
+    if (lane < a.nsplit) {
+        const float* sp = a.split_stat + 8 * ((long long)lane * a.K * a.T + row);
+        const f32x4 st = *(const f32x4*)sp;
+        m = st[0];
+        s_own = st[1];
+        zy = st[2];
+        best = st[3];
+        best_v = __float_as_int(sp[4]);
+    }
+    const float m_own = m;
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    float sx = m_own == m ? s_own : s_own * __builtin_amdgcn_exp2f(m_own - m);
+    if (lane >= a.nsplit) sx = 0.f;
+    for (int off = 32; off > 0; off >>= 1) {
+        sx += __shfl_xor(sx, off, 64);
+        zy += __shfl_xor(zy, off, 64);
+        const float ob = __shfl_xor(best, off, 64);
+        const int ov = __shfl_xor(best_v, off, 64);
+        if (ob > best || (ob == best && (unsigned)ov < (unsigned)best_v)) {
+            best = ob;
+            best_v = ov;
         }
     }
-    if (want_dg) {
-        __syncthreads();
-        float* p = a.dgain_part + ((long long)(a.dg_mode == 2 ? k : 0) * gridDim.x + tile) * d;
-        for (int j = threadIdx.x; j < d; j += 256) p[j] = ((pbuf[j] + pbuf[d + j]) + pbuf[2 * d + j]) + pbuf[3 * d + j];
+    if (lane == 0) {
+        const int tgt = a.targets[row];
+        a.rowloss[row] = finish_row(m, sx, zy, tgt >= 0 && tgt < a.V).loss;
+        if (a.top1) a.top1[row] = best_v;
     }
 }
 
 template <typename E, bool F32FAM>
 hipError_t launch_t(const FusedArgs& a, int nmod, int rows, hipStream_t s) {
-    const size_t lds = a.dg_mode ? (size_t)16 * a.d : 0;  // at most 64 KiB
-    hipLaunchKernelGGL((k_merge<E, F32FAM>), dim3((unsigned)((a.T + rows - 1) / rows), (unsigned)nmod), dim3(256), lds,
-                       s, a, rows);
+    hipLaunchKernelGGL((k_merge<E, F32FAM>), dim3((unsigned)a.T, (unsigned)nmod), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    // (the terminal's gain alone: only a launch that holds the terminal has partials)
+    if (e != hipSuccess || a.ebuf || !a.dg_mode || (a.dg_mode == 1 && a.m0 + nmod != a.K)) return e;
+    const dim3 grid((unsigned)((a.T + rows - 1) / rows), (unsigned)nmod, (unsigned)((a.d + 1023) / 1024));
+    hipLaunchKernelGGL((k_merge_dgain<E>), grid, dim3(256), 0, s, a, rows);
     return hipGetLastError();
 }
 
 }  // namespace
+
+hipError_t launch_merge_eval(const FusedArgs& a, long long rows, hipStream_t s) {
+    hipLaunchKernelGGL(k_merge_eval, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, a, rows);
+    return hipGetLastError();
+}
 
 hipError_t launch_merge(int dtype, bool f32fam, const FusedArgs& a, int nmod, int rows, hipStream_t s) {
     if (dtype != 0) return launch_t<float, true>(a, nmod, rows, s);

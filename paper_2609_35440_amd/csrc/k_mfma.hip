@@ -111,7 +111,13 @@ __device__ __forceinline__ const bf16* tiled_readout_of(const FusedArgs& a, int 
 // MODE LOCAL / EVAL: grid (ceil(T/XR), nmod); MODE RGRAD / BGRAD: grid
 // (ceil(V/XR), nmod); module k = m0 + blockIdx.y.
 // EXT (LOCAL and EVAL): the variant with per-chunk biases, launched when the call has biases.
-template <int MODE, int DS, bool EXT>
+// SPL (LOCAL and EVAL): the vocabulary of a row tile is split over the grid's z
+// dimension, and the workgroup leaves its part of every row for the merge
+// (k_merge.hip).  Exit evaluation then reads the readout row-major, 64 bytes of
+// 16 rows per load: few rows read it, so it comes from memory once and a tiled
+// copy would triple the traffic; and it can take the rows of all modules as one
+// list (a.flat) where they share one readout and no biases.
+template <int MODE, int DS, bool EXT, bool SPL>
 __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     constexpr bool PC = MODE == LOCAL || MODE == RGRAD;     // second product
     using G = Geo<DS, PC>;
@@ -121,6 +127,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     constexpr bool LL = MODE == LOCAL || MODE == EVAL;      // X = h, Y = readout
     constexpr bool RF = !PC;                                // operand registers fed from the tiled copy
     constexpr bool BZ = (MODE == LOCAL || MODE == EVAL) && EXT;  // per-chunk biases through LDS
+    constexpr bool RM = RF && SPL;                               // operand registers fed row-major
+    static_assert(!SPL || MODE == LOCAL || MODE == EVAL, "split over the vocabulary");
+    const bool flat = RM && a.flat;
     // the stream of the next chunk: instructions [0, kDmaA) one per k-step of
     // the logit products, [kDmaA, NI) after the elementwise step.  Measured:
     // with a second product, at d = 2048 5 of 8 inside the products (3 and 8
@@ -148,8 +157,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     const int d = a.d;
     const int js = w * DS;
     const int x0 = blockIdx.x * XR;
-    const int k = a.m0 + (int)blockIdx.y;
-    const long long modoff = (long long)k * a.T;
+    const int k = flat ? a.K - 1 : a.m0 + (int)blockIdx.y;
+    const long long modoff = flat ? 0 : (long long)k * a.T;
     const float tau_k = a.tau ? a.tau[k] : 1.f;
 
     const bf16* __restrict__ hk = (const bf16*)a.h + modoff * d;
@@ -159,11 +168,13 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     // the streamed rows: the readout, or the copy of g_k * h_k (row-major for
     // the direct-to-LDS stream, tiled for the register-fed passes); module
     // copies sit tiled_elems(T, d) apart either way
-    const bf16* __restrict__ Y = LL ? (RF ? tiled_readout_of(a, k) : Rk)
+    const bf16* __restrict__ Y = LL ? (RF && !RM ? tiled_readout_of(a, k) : Rk)
                                     : (const bf16*)a.hg + (long long)(k - a.hg_m0) * tiled_elems(a.T, d);
-    const int nX = LL ? a.T : a.V;
+    const int nX = LL ? (flat ? a.K * a.T : a.T) : a.V;
     const int nY = LL ? a.V : a.T;
     const int nchunks = (nY + YC - 1) / YC;
+    const int ck_lo = SPL ? (int)((long long)nchunks * blockIdx.z / a.nsplit) : 0;
+    const int ck_hi = SPL ? (int)((long long)nchunks * (blockIdx.z + 1) / a.nsplit) : nchunks;
 
     LDS_AS char* sliceA = (LDS_AS char*)(LDS_AS void*)ybufA + w * G::SLICE;
     LDS_AS char* sliceB = (LDS_AS char*)(LDS_AS void*)ybufB + w * G::SLICE;
@@ -188,7 +199,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         tgt_rel[r] = -1 - yy;
         bx2[r] = 0.f;
         if (LL && x0 + xo[r] < nX) {
-            own_r2[r] = a.rstd[modoff + x0 + xo[r]] * tau_k * kLog2e;
+            const float tau_r = flat && a.tau ? a.tau[(x0 + xo[r]) / a.T] : tau_k;
+            own_r2[r] = a.rstd[modoff + x0 + xo[r]] * tau_r * kLog2e;
             tgt_rel[r] = a.targets[modoff + x0 + xo[r]] - yy;
         }
         if (!LL && a.bias && x0 + xo[r] < nX) bx2[r] = a.bias[(long long)k * a.V + x0 + xo[r]] * kLog2e;
@@ -199,24 +211,28 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     if (PC) stream.init(d, js, lane);
     // first chunk in flight before the stationary operand is read
     const unsigned sliceA_u = lds_addr(sliceA), sliceB_u = lds_addr(sliceB);
-    if (PC) stream.issue(Y, nY, d, 0, sliceA_u);
+    if (PC) stream.issue(Y, nY, d, ck_lo * YC, sliceA_u);
     // register-fed passes: k-step kk of chunk c of this wave's slice is NK KiB
     // into chunk c of the tiled copy plus 1 KiB kk; buffer loads over those NK
     // KiB, one lane offset shared by every load and the k-step as a scalar offset
-    const bf16* __restrict__ Yw = Y + w * (G::NK * 512);
+    // (row-major: over the chunk's rows, rows past the end read as zeros)
+    const bf16* __restrict__ Yw = Y + (RM ? 0 : w * (G::NK * 512));
+    const int rm_off = ((lane & 15) * d + js + 8 * (lane >> 4)) * 2;
     auto rsrc_of = [&](int c) __attribute__((always_inline)) {
-        return __builtin_amdgcn_make_buffer_rsrc((void*)(Yw + (long long)c * 16 * d), (short)0, G::NK * 1024,
-                                                 0x00020000);
+        const int rows = nY - c * YC < YC ? nY - c * YC : YC;
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(Yw + (long long)c * 16 * d), (short)0,
+                                                 RM ? rows * d * 2 : G::NK * 1024, 0x00020000);
     };
     auto ld_op = [&](__amdgpu_buffer_rsrc_t rs, int kk) __attribute__((always_inline)) {
-        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, kk * 1024, 0));
+        return __builtin_bit_cast(bf16x8, RM ? __builtin_amdgcn_raw_buffer_load_b128(rs, rm_off + kk * 64, 0, 0)
+                                             : __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, kk * 1024, 0));
     };
     // operand registers of the register-fed passes: k-step kk of the current
     // chunk (lane: streamed row lane % 16, columns js + 32 kk + 8 (lane / 16) .. + 7)
     bf16x8 ay_rf[RF ? G::NK : 1];
     if (RF) {
 #pragma unroll
-        for (int kk = 0; kk < G::NK; ++kk) ay_rf[kk] = ld_op(rsrc_of(0), kk);
+        for (int kk = 0; kk < G::NK; ++kk) ay_rf[kk] = ld_op(rsrc_of(ck_lo), kk);
     }
     const unsigned recA_u = lds_addr((LDS_AS char*)(LDS_AS void*)recA);
     const unsigned recB_u = lds_addr((LDS_AS char*)(LDS_AS void*)recB);
@@ -234,7 +250,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             buffer_load_lds4(make_rsrc(a.bias + (long long)k * a.V + y0, rem), dst, lane16 * 4);
         }
     };
-    issue_side(0, recA_u);
+    issue_side(ck_lo * YC, recA_u);
 
     // stationary operand (local loss and exit evaluation: times the gain,
     // rounded once): B of the 16x16x32 logit product, lane holds
@@ -243,13 +259,14 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
 #pragma unroll
     for (int kk = 0; kk < G::NK; ++kk) {
         const int j0 = js + 32 * kk + 8 * (lane >> 4);
-        const bf16x8 gv = *(const bf16x8*)(gk + j0);
+        bf16x8 gv = *(const bf16x8*)(gk + j0);
 #pragma unroll
         for (int xb = 0; xb < G::NXB; ++xb) {
             const int xrow = x0 + 16 * xb + (lane & 15);
             bf16x8 xv;
             if (xrow < nX) {
                 xv = *(const bf16x8*)(X + (long long)xrow * d + j0);
+                if (flat) gv = *(const bf16x8*)((const bf16*)a.gain + (long long)(xrow / a.T) * a.g_stride + j0);
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) xv[e] = (bf16)0.f;
@@ -293,7 +310,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     auto step = [&](LDS_AS char* cur, unsigned nxt, LDS_AS float* side, unsigned side_nxt, int c)
                     __attribute__((always_inline)) {
         const int y0 = c * YC;
-        const bool more = c + 1 < nchunks;
+        const bool more = c + 1 < ck_hi;
         const i32x4 nrs = ChunkStream<DS>::rsrc(Y, nY, d, y0 + YC);
         // register-fed passes reload the operand registers with the next chunk
         // (the last chunk reloads itself: no branch around the loads)
@@ -479,9 +496,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     };
 
     wait_vm();
-    for (int c = 0; c < nchunks; c += 2) {
+    for (int c = ck_lo; c < ck_hi; c += 2) {
         step(sliceA, sliceB_u, (LDS_AS float*)(LDS_AS void*)recA, recB_u, c);
-        if (c + 1 < nchunks) step(sliceB, sliceA_u, (LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
+        if (c + 1 < ck_hi) step(sliceB, sliceA_u, (LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
     }
 
     // ---- epilogues.  acc[b][h] lane layout: x = 32 h + lane%32,
@@ -509,6 +526,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                     }
                 }
             }
+            if (SPL) {
+                if (lane % LPR == 0 && x0 + xo[r] < nX) {
+                    constexpr int SW = MODE == EVAL ? 8 : 4;  // floats per row and split
+                    float* sp = a.split_stat + SW * ((long long)blockIdx.z * a.K * a.T + modoff + x0 + xo[r]);
+                    *(f32x4*)sp = (f32x4){m_run[r], sx, zy, bst};
+                    if (MODE == EVAL) *(f32x4*)(sp + 4) = (f32x4){__int_as_float(bv), 0.f, 0.f, 0.f};
+                }
+                continue;
+            }
             if (lane % LPR == 0) {
                 const int xr_ = x0 + xo[r];
                 const bool tok = own_tgt >= 0 && own_tgt < nY;
@@ -529,7 +555,25 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             }
         }
     }
-    if (MODE == LOCAL) {
+    if (MODE == LOCAL && SPL) {
+        // the unnormalised partial sums of this split, for the merge
+#pragma unroll
+        for (int h = 0; h < NR; ++h) {
+            const int xg = x0 + 32 * h + ex;
+            if (xg >= nX) continue;
+            float* P = a.split_acc + ((long long)blockIdx.z * a.K * a.T + modoff + xg) * d;
+#pragma unroll
+            for (int b = 0; b < (PC ? G::NB : 1); ++b)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    f32x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = acc[b][h][4 * i4 + e];
+                    *(f32x4*)(P + js + 32 * b + 8 * i4 + 4 * ehh) = o;
+                }
+        }
+    }
+    if (MODE == LOCAL && !SPL) {
         __syncthreads();
         const bool want_dg = a.dg_mode == 2 || (a.dg_mode == 1 && k == a.K - 1);
         float* dgp = want_dg ? a.dgain_part + ((long long)(a.dg_mode == 2 ? k : 0) * gridDim.x + blockIdx.x) * d
@@ -706,9 +750,17 @@ template <int MODE, int DS, bool EXT>
 hipError_t launch_ds(const FusedArgs& a, int nmod, hipStream_t s) {
     const bool ll = MODE == LOCAL || MODE == EVAL;
     constexpr int XR = Geo<DS, MODE == LOCAL || MODE == RGRAD>::XR;
+    if constexpr (MODE == LOCAL || MODE == EVAL) {
+        if (a.nsplit > 1 || a.flat) {
+            const int rows = a.flat ? a.K * a.T : a.T;
+            const dim3 grid((unsigned)((rows + XR - 1) / XR), a.flat ? 1u : (unsigned)nmod, (unsigned)a.nsplit);
+            hipLaunchKernelGGL((k_fused<MODE, DS, EXT, true>), grid, dim3(NTHR), 0, s, a);
+            return hipGetLastError();
+        }
+    }
     dim3 grid = ll ? dim3((unsigned)((a.T + XR - 1) / XR), (unsigned)nmod)
                    : dim3((unsigned)((a.V + XR - 1) / XR), (unsigned)nmod);
-    hipLaunchKernelGGL((k_fused<MODE, DS, EXT>), grid, dim3(NTHR), 0, s, a);
+    hipLaunchKernelGGL((k_fused<MODE, DS, EXT, false>), grid, dim3(NTHR), 0, s, a);
     return hipGetLastError();
 }
 
@@ -730,6 +782,8 @@ hipError_t launch_mode(const FusedArgs& a, int nmod, hipStream_t s) {
 }  // namespace
 
 bool mfma_supported(int dtype, int d) { return dtype == 0 && d % (NW * 32) == 0 && d >= NW * 32 && d <= NW * 256; }
+
+int mfma_eval_rows(int d) { return d <= NW * 128 ? rows_of<128, false>() : rows_of<256, false>(); }
 
 int mfma_rows(int d) { return d <= NW * 128 ? rows_of<128, true>() : rows_of<256, true>(); }
 

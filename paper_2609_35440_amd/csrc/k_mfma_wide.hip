@@ -48,7 +48,7 @@ constexpr int PP = 16;
 // passes without one (exit evaluation, bias gradient: 120 registers of
 // stationary operand), which cuts the readout streamed per flop to a third.
 template <bool PC>
-constexpr int wide_rows() { return PC ? kMfmaWideRows : 48; }
+constexpr int wide_rows() { return PC ? kMfmaWideRows : kMfmaWideEvalRows; }
 static_assert(kMfmaWideRows == 16, "one 16-row block of stationary rows with a second product");
 
 enum Mode { LOCAL = 0, RGRAD = 1, BGRAD = 2, EVAL = 3 };
@@ -76,7 +76,10 @@ __device__ __forceinline__ const bf16* readout_of(const FusedArgs& a, int k) {
 // (ceil(V/XR), nmod); module k = m0 + blockIdx.y.
 // XR = 16 with a second product (LOCAL, RGRAD), 48 without (EVAL, BGRAD).
 // EXT (LOCAL and EVAL): the variant with per-chunk biases, launched when the call has biases.
-template <int MODE, int DS, bool EXT>
+// SPL (LOCAL and EVAL): the vocabulary split over the grid's z dimension, and
+// exit evaluation then row-major and over the rows of all modules (a.flat), as
+// in k_mfma.hip.
+template <int MODE, int DS, bool EXT, bool SPL>
 __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     constexpr bool LL = MODE == LOCAL || MODE == EVAL;           // X = h, Y = readout
     constexpr bool PC = MODE == LOCAL || MODE == RGRAD;          // second product
@@ -85,6 +88,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     static_assert((PC && XR == 16) || (!PC && (XR == 16 || XR == 32 || XR == 48)), "tile height");
     using G = Geo<DS, XR>;
     constexpr bool BZ = (MODE == LOCAL || MODE == EVAL) && EXT;  // per-chunk biases through LDS
+    constexpr bool RM = MODE == EVAL && SPL;                     // operand registers fed row-major
+    static_assert(!SPL || MODE == LOCAL || MODE == EVAL, "split over the vocabulary");
+    const bool flat = RM && a.flat;
     __shared__ __attribute__((aligned(16))) char ybuf[PC ? G::YBUF : 16];
     __shared__ __attribute__((aligned(16))) float part[NW * XR * PP];
     __shared__ __attribute__((aligned(16))) bf16 gbuf[XR * YC];
@@ -100,37 +106,44 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     const int d = a.d;
     const int js = w * DS;
     const int x0 = blockIdx.x * XR;
-    const int k = a.m0 + (int)blockIdx.y;
-    const long long modoff = (long long)k * a.T;
+    const int k = flat ? a.K - 1 : a.m0 + (int)blockIdx.y;
+    const long long modoff = flat ? 0 : (long long)k * a.T;
     const float tau_k = a.tau ? a.tau[k] : 1.f;
 
     const bf16* __restrict__ hk = (const bf16*)a.h + modoff * d;
     const bf16* __restrict__ Rk = readout_of(a, k);
     const bf16* __restrict__ gk = (const bf16*)a.gain + (long long)k * a.g_stride;
     const bf16* __restrict__ X = LL ? hk : Rk;
-    const int nX = LL ? a.T : a.V;
+    const int nX = LL ? (flat ? a.K * a.T : a.T) : a.V;
     const int nY = LL ? a.V : a.T;
     const int nchunks = (nY + YC - 1) / YC;
+    const int ck_lo = SPL ? (int)((long long)nchunks * blockIdx.z / a.nsplit) : 0;
+    const int ck_hi = SPL ? (int)((long long)nchunks * (blockIdx.z + 1) / a.nsplit) : nchunks;
     // this wave's k-step 0 of chunk 0 in the tiled streamed operand; k-step kk
     // of chunk c is 512 kk + 16 d c elements further, the lane's 16 bytes 8 lane
-    const bf16* __restrict__ Yw =
+    const bf16* __restrict__ Yw = RM ? Rk :
         (LL ? (k == a.K - 1 ? (const bf16*)a.Wtt : (const bf16*)a.Wht + (long long)k * a.wht_stride)
             : (const bf16*)a.hg + (long long)(k - a.hg_m0) * tiled_elems(a.T, d)) +
         w * (G::NK * 512);
     const long long cstride = 16LL * d;
     // buffer loads over this wave's NK KiB of a chunk, one lane offset shared by
     // every load and the k-step as a scalar offset
-    auto rsrc_of = [&](const bf16* __restrict__ base) __attribute__((always_inline)) {
-        return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, G::NK * 1024, 0x00020000);
+    // (row-major: over the chunk's rows, rows past the end read as zeros)
+    const int rm_off = ((lane & 15) * d + js + 8 * (lane >> 4)) * 2;
+    auto rsrc_of = [&](int c) __attribute__((always_inline)) {
+        const int rows = nY - c * YC < YC ? nY - c * YC : YC;
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(Yw + (long long)c * cstride), (short)0,
+                                                 RM ? rows * d * 2 : G::NK * 1024, 0x00020000);
     };
     auto ld_op = [&](__amdgpu_buffer_rsrc_t rs, int kk) __attribute__((always_inline)) {
-        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, kk * 1024, 0));
+        return __builtin_bit_cast(bf16x8, RM ? __builtin_amdgcn_raw_buffer_load_b128(rs, rm_off + kk * 64, 0, 0)
+                                             : __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, kk * 1024, 0));
     };
     // operand registers: k-step kk of the current chunk (lane: streamed row
     // lane % 16, columns js + 32 kk + 8 (lane / 16) .. + 7)
     bf16x8 ay[G::NK];
 #pragma unroll
-    for (int kk = 0; kk < G::NK; ++kk) ay[kk] = ld_op(rsrc_of(Yw), kk);
+    for (int kk = 0; kk < G::NK; ++kk) ay[kk] = ld_op(rsrc_of(ck_lo), kk);
 
     LDS_AS char* slice = (LDS_AS char*)(LDS_AS void*)ybuf + w * G::SLICE;
 
@@ -158,7 +171,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
         own_tgt[r] = -1;
         bx2[r] = 0.f;
         if (LL && x0 + xo[r] < nX) {
-            own_r2[r] = a.rstd[modoff + x0 + xo[r]] * tau_k * kLog2e;
+            const float tau_r = flat && a.tau ? a.tau[(x0 + xo[r]) / a.T] : tau_k;
+            own_r2[r] = a.rstd[modoff + x0 + xo[r]] * tau_r * kLog2e;
             own_tgt[r] = a.targets[modoff + x0 + xo[r]];
         }
         if (!LL && a.bias && x0 + xo[r] < nX) bx2[r] = a.bias[(long long)k * a.V + x0 + xo[r]] * kLog2e;
@@ -182,7 +196,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
         }
     };
 
-    issue_side(0, recA_u);
+    issue_side(ck_lo * YC, recA_u);
 
     // stationary operand (local loss and exit evaluation: times the gain,
     // rounded once): B of the 16x16x32 logit product, lane holds
@@ -191,13 +205,14 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
 #pragma unroll
     for (int kk = 0; kk < G::NK; ++kk) {
         const int j0 = js + 32 * kk + 8 * (lane >> 4);
-        const bf16x8 gv = *(const bf16x8*)(gk + j0);
+        bf16x8 gv = *(const bf16x8*)(gk + j0);
 #pragma unroll
         for (int xb = 0; xb < NXB; ++xb) {
             const int xrow = x0 + 16 * xb + (lane & 15);
             bf16x8 xv;
             if (xrow < nX) {
                 xv = *(const bf16x8*)(X + (long long)xrow * d + j0);
+                if (flat) gv = *(const bf16x8*)((const bf16*)a.gain + (long long)(xrow / a.T) * a.g_stride + j0);
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) xv[e] = (bf16)0.f;
@@ -236,9 +251,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
 
     auto step = [&](LDS_AS float* side, unsigned side_nxt, int c) __attribute__((always_inline)) {
         const int y0 = c * YC;
-        const bool more = c + 1 < nchunks;
+        const bool more = c + 1 < ck_hi;
         // reload with the next chunk (the last chunk reloads itself, unused)
-        const __amdgpu_buffer_rsrc_t yn = rsrc_of(Yw + (more ? (long long)(c + 1) : (long long)c) * cstride);
+        const __amdgpu_buffer_rsrc_t yn = rsrc_of(more ? c + 1 : c);
 
         // ---- (1) split-K partial of the logit tile S[y][x] over this wave's columns
         if (more) issue_side(y0 + YC, side_nxt);
@@ -339,9 +354,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
 
     wait_vm();
 
-    for (int c = 0; c < nchunks; c += 2) {
+    for (int c = ck_lo; c < ck_hi; c += 2) {
         step((LDS_AS float*)(LDS_AS void*)recA, recB_u, c);
-        if (c + 1 < nchunks) step((LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
+        if (c + 1 < ck_hi) step((LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
     }
 
     // ---- epilogues.  acc[b] lane layout: x = lane%16, j = js + 16 b + 4 (lane/16) + i
@@ -367,6 +382,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
                     }
                 }
             }
+            if (SPL) {
+                if (yy == 0 && wr[r] && x0 + xo[r] < nX) {
+                    constexpr int SW = MODE == EVAL ? 8 : 4;  // floats per row and split
+                    float* sp = a.split_stat + SW * ((long long)blockIdx.z * a.K * a.T + modoff + x0 + xo[r]);
+                    *(f32x4*)sp = (f32x4){m_run[r], sx, zy, bst};
+                    if (MODE == EVAL) *(f32x4*)(sp + 4) = (f32x4){__int_as_float(bv), 0.f, 0.f, 0.f};
+                }
+                continue;
+            }
             if (yy == 0 && wr[r]) {
                 const int xr_ = x0 + xo[r];
                 const bool tok = own_tgt[r] >= 0 && own_tgt[r] < nY;
@@ -387,7 +411,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
             }
         }
     }
-    if (MODE == LOCAL) {
+    if (MODE == LOCAL && SPL) {
+        // the unnormalised partial sums of this split, for the merge
+        if (x0 + ex < nX) {
+            float* P = a.split_acc + ((long long)blockIdx.z * a.K * a.T + modoff + x0 + ex) * d;
+#pragma unroll
+            for (int b = 0; b < G::NB; ++b) *(f32x4*)(P + js + 16 * b + 4 * eg) = acc[b];
+        }
+    }
+    if (MODE == LOCAL && !SPL) {
         __syncthreads();
         const int xg = x0 + ex;
         const bool xok = xg < nX;
@@ -502,9 +534,17 @@ template <int MODE, int DS, bool EXT>
 hipError_t launch_ds(const FusedArgs& a, int nmod, hipStream_t s) {
     const bool ll = MODE == LOCAL || MODE == EVAL;
     constexpr int XR = wide_rows<MODE == LOCAL || MODE == RGRAD>();
+    if constexpr (MODE == LOCAL || MODE == EVAL) {
+        if (a.nsplit > 1 || a.flat) {
+            const int rows = a.flat ? a.K * a.T : a.T;
+            const dim3 sgrid((unsigned)((rows + XR - 1) / XR), a.flat ? 1u : (unsigned)nmod, (unsigned)a.nsplit);
+            hipLaunchKernelGGL((k_fused_wide<MODE, DS, EXT, true>), sgrid, dim3(NTHR), 0, s, a);
+            return hipGetLastError();
+        }
+    }
     dim3 grid = ll ? dim3((unsigned)((a.T + XR - 1) / XR), (unsigned)nmod)
                    : dim3((unsigned)((a.V + XR - 1) / XR), (unsigned)nmod);
-    hipLaunchKernelGGL((k_fused_wide<MODE, DS, EXT>), grid, dim3(NTHR), 0, s, a);
+    hipLaunchKernelGGL((k_fused_wide<MODE, DS, EXT, false>), grid, dim3(NTHR), 0, s, a);
     return hipGetLastError();
 }
 

@@ -152,31 +152,63 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     return true;
 }
 
-// Over how many workgroups a row tile of the local-loss pass over n modules is
-// split along the vocabulary: one while the tiles fill the chip's 256 CUs
-// (these kernels run one workgroup per CU); with fewer tiles, the number with
-// the least time by the matrix work of a workgroup's chunks (4 R d clocks per
-// chunk of 256 readout rows at the fp32 matrix rate, 70% of it reached) plus
-// the merge (its launch, and the partial sums written and read once).  The
-// partial sums live in an output that the readout-gradient pass overwrites
-// later, so only calls that compute one are split, as far as it holds them:
-// `room` floats.
-int f32_splits(const Plan& P, int n, int K, int T, int d, int V, size_t room) {
-    const long long tiles = (long long)P.ntiles * n;
-    const long long nch = ((long long)V + 255) / 256;
+// Splits of a row tile's vocabulary over several workgroups.  These kernels run
+// one workgroup per CU, so a launch of `tiles` row tiles, each cut s ways, takes
+// ceil(tiles s / 256) rounds of ceil(chunks / s) chunks; the merge of the parts
+// adds its launch and what it reads and writes.  The rules below take the s
+// with the least of that sum, so a launch whose tiles fill the chip stays whole.
+struct SplitCost {
+    double chunk_us;    // one chunk of streamed rows of one workgroup
+    double merge_us;    // the merge's launch
+    double part_us;     // the parts of one split, written and read once
+};
+
+int best_split(long long tiles, long long nch, const SplitCost& c, double max_s, double* us_out = nullptr) {
     int best = 1;
-    double best_us = 0.0;
-    for (int s = 1; s <= solo::kMaxSplit && s <= nch; ++s) {
-        if (s > 1 && ((double)s * K * T * (d + 4) > (double)room || tiles * (s - 1) >= 512)) break;
-        const double rounds = (double)((tiles * s + 255) / 256), per = (double)((nch + s - 1) / s);
-        double us = rounds * per * 4.0 * P.rows * d / 1.6e3;
-        if (s > 1) us += 6.0 + (double)s * n * T * d * 8.0 / 3e6;
-        if (s == 1 || us < best_us) {
+    double best_us = (double)((tiles + 255) / 256) * (double)nch * c.chunk_us;
+    for (int s = 2; s <= solo::kMaxSplit && s <= nch && s <= max_s && tiles * (s - 1) < 512; ++s) {
+        const double us = (double)((tiles * s + 255) / 256) * (double)((nch + s - 1) / s) * c.chunk_us + c.merge_us +
+                          s * c.part_us;
+        if (us < best_us) {
             best = s;
             best_us = us;
         }
     }
+    if (us_out) *us_out = best_us;
     return best;
+}
+
+// The local-loss pass over n modules.  Its parts (a row of d fp32 sums and 4
+// scalars per token and split) live in an output that the readout-gradient
+// pass overwrites later, so only calls that compute one are split, as far as
+// its `room` floats hold them.  Time per chunk: the fp32 family's 256 readout
+// rows take 4 R d clocks at the fp32 matrix rate, 70% of it reached; a 16-row
+// chunk of the bf16 kernels measured 1.15 us at 65536 elements per tile (32 x
+// 2048 and 64 x 1024), of which about 0.5 us is the exchange and its barriers.
+int local_splits(const Plan& P, int n, int K, int T, int d, int V, size_t room) {
+    const double td = (double)P.rows * d;
+    const SplitCost c = {P.mfma ? 0.5 + 0.65 * td / 65536.0 : 4.0 * td / 1.6e3, 6.0, (double)n * T * d * 8.0 / 3e6};
+    const int yc = P.mfma ? 16 : 256;
+    return best_split((long long)P.ntiles * n, ((long long)V + yc - 1) / yc, c, (double)room / ((double)K * T * (d + 4)));
+}
+
+// Exit evaluation on the matrix-core kernels: split, it reads the readouts
+// row-major and its parts (8 scalars per row and split) take the place of the
+// tiled copies; whole, it streams the copies, whose writing costs a read and a
+// write of every readout.  Returns the splits (1: whole).
+int eval_splits(const Plan& P, int K, int T, int d, int V, bool flat) {
+    const int rows = P.wide ? solo::kMfmaWideEvalRows : solo::mfma_eval_rows(d);
+    const long long tiles = (long long)K * ((T + rows - 1) / rows);
+    const long long stiles = flat ? ((long long)K * T + rows - 1) / rows : tiles;
+    const long long nch = ((long long)V + 15) / 16;
+    const double chunk = 0.3 + 0.8 * (double)rows * d / 131072.0;
+    const double whole = (double)((tiles + 255) / 256) * (double)nch * chunk +
+                         (1 + P.nhead_tiles) * (4.0 + 4.0 * (double)V * d / 4e6);
+    const double room = (double)solo::tiled_elems(V, d) * 2.0;
+    const SplitCost c = {1.3 * chunk, 5.0, (double)K * T * 64.0 / 3e6};
+    double us = 0.0;
+    const int s = best_split(stiles, nch, c, room / ((double)K * T * 32.0), &us);
+    return s > 1 && us < whole ? s : 1;
 }
 
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
@@ -271,7 +303,15 @@ int run(const solo_readout_args& x, bool eval) {
     (void)hipGetLastError();
     if (solo::launch_row_rstd(dt, x.h, (float*)(ws + P.rstd), (long long)K * T, d, x.eps, s) != hipSuccess)
         return SOLO_ERR_HIP;
-    if (tiled_readout(P)) {
+    // exit evaluation of few rows: split over the vocabulary, no tiled copies
+    const bool flat = eval && P.mfma && !P.rot && !x.bias && !P.nhead_tiles;
+    const int esplit = eval && P.mfma ? eval_splits(P, K, T, d, V, flat) : 1;
+    if (esplit > 1) {
+        a.nsplit = esplit;
+        a.split_stat = (float*)(ws + P.wtile);
+        a.flat = flat;
+    }
+    if (tiled_readout(P) && esplit == 1) {
         if (solo::launch_tile((const solo::bf16*)x.W, 0, nullptr, 0, (solo::bf16*)(ws + P.wtile), 1, V, d, s) !=
             hipSuccess)
             return SOLO_ERR_HIP;
@@ -300,24 +340,23 @@ int run(const solo_readout_args& x, bool eval) {
         if (n <= 0) return hipSuccess;
         solo::FusedArgs b = g;
         b.m0 = m0;
-        if (which == 1 && !P.mfma) {
-            b.nsplit = f32_splits(P, n, K, T, d, V, room_floats);
-            if (b.nsplit > 1) {
-                b.split_acc = room;
-                b.split_stat = room + (size_t)b.nsplit * K * T * d;
-                const hipError_t e = solo::launch_local_loss_f32(dt, b, n, s);
-                return e != hipSuccess ? e : solo::launch_merge(dt, true, b, n, P.rows, s);
-            }
+        if (which == 1) {
+            b.nsplit = local_splits(P, n, K, T, d, V, room_floats);
+            b.split_acc = room;
+            b.split_stat = room + (size_t)b.nsplit * K * T * d;
         }
         switch (which) {
             case 0:
                 return P.wide   ? solo::launch_exit_eval_mfma_wide(b, n, s)
                        : P.mfma ? solo::launch_exit_eval_mfma(b, n, s)
                                 : solo::launch_exit_eval_f32(dt, b, n, s);
-            case 1:
-                return P.wide   ? solo::launch_local_loss_mfma_wide(b, P.ext, n, s)
-                       : P.mfma ? solo::launch_local_loss_mfma(b, P.ext, n, s)
-                                : solo::launch_local_loss_f32(dt, b, n, s);
+            case 1: {
+                const hipError_t e = P.wide   ? solo::launch_local_loss_mfma_wide(b, P.ext, n, s)
+                                     : P.mfma ? solo::launch_local_loss_mfma(b, P.ext, n, s)
+                                              : solo::launch_local_loss_f32(dt, b, n, s);
+                if (e != hipSuccess || b.nsplit == 1) return e;
+                return solo::launch_merge(dt, !P.mfma, b, n, P.rows, s);
+            }
             case 2:
                 return P.wide   ? solo::launch_readout_grad_mfma_wide(b, n, s)
                        : P.mfma ? solo::launch_readout_grad_mfma(b, n, s)
@@ -334,6 +373,7 @@ int run(const solo_readout_args& x, bool eval) {
         return pass(which, ah, lo, K - 1 - lo) == hipSuccess && pass(which, a, K - 1, hi - K + 1) == hipSuccess;
     };
     if (!pass_range(eval ? 0 : 1, 0, K)) return SOLO_ERR_HIP;
+    if (esplit > 1 && solo::launch_merge_eval(a, (long long)K * T, s) != hipSuccess) return SOLO_ERR_HIP;
     if (P.rot && !eval) {
         // back to the basis of h: D = e R_k = e (R_k^T)^T, then the heads' RMSNorm
         // backward (and their gain partials when every module trains its gain)

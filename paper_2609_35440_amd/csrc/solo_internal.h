@@ -70,7 +70,9 @@ struct FusedArgs {
                           // bf16 row); the fp32 family writes e in fp32
     int nsplit;           // local-loss pass: workgroups the vocabulary of a row tile is split over (grid z)
     float* split_acc;     // nsplit > 1: [nsplit][K T][d] unnormalised sums of exp(z - m) R_v of each split
-    float* split_stat;    // nsplit > 1: [nsplit][K T][4] {m (base 2), sum without the target, target logit, -}
+    float* split_stat;    // nsplit > 1: [nsplit][K T][4] {m (base 2), sum without the target, target logit, -};
+                          // exit evaluation: [nsplit][K T][8], the largest logit and its column after those three
+    int flat;             // split exit evaluation: 1 takes the rows of all modules as one list (one readout, no bias)
 };
 
 // Tile sizes of the two kernel families (the workspace depends on them).
@@ -97,6 +99,7 @@ hipError_t launch_dgain_reduce(const float* part, float* dgain, int slots, int n
 // fused passes; `ext` selects the local-loss variant with per-chunk biases,
 // `nmod` is the number of modules of a readout-/bias-gradient launch
 bool mfma_supported(int dtype, int d);
+int mfma_eval_rows(int d);  // the same of the forward-only passes
 int mfma_rows(int d);  // stationary rows per workgroup of the matrix-core kernels at width d (64 or 32)
 // local-loss and exit passes: modules m0 .. m0 + nmod - 1
 hipError_t launch_local_loss_mfma(const FusedArgs& a, bool ext, int nmod, hipStream_t s);
@@ -105,6 +108,7 @@ hipError_t launch_readout_grad_mfma(const FusedArgs& a, int nmod, hipStream_t s)
 hipError_t launch_bias_grad_mfma(const FusedArgs& a, int nmod, hipStream_t s);
 // the wide matrix-core kernels (k_mfma_wide.hip): d = 2560
 bool mfma_wide_supported(int dtype, int d);
+constexpr int kMfmaWideEvalRows = 48;  // stationary rows per workgroup of their forward-only passes
 hipError_t launch_local_loss_mfma_wide(const FusedArgs& a, bool ext, int nmod, hipStream_t s);
 hipError_t launch_exit_eval_mfma_wide(const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_readout_grad_mfma_wide(const FusedArgs& a, int nmod, hipStream_t s);
@@ -115,6 +119,7 @@ hipError_t launch_exit_eval_f32(int dtype, const FusedArgs& a, int nmod, hipStre
 // per tile of rows tokens (k_merge.hip)
 hipError_t launch_merge(int dtype, bool f32fam, const FusedArgs& a, int nmod, int rows, hipStream_t s);
 constexpr int kMaxSplit = 64;  // splits of one row tile (a lane of the merge each)
+hipError_t launch_merge_eval(const FusedArgs& a, long long rows, hipStream_t s);
 // ROT (k_rot.hip): C = A B^T per matrix; transposes; a vector of ones; the
 // heads' RMSNorm backward from the rotated-back gradient D = e R_k
 // u[m] = bf16(R_m bf16(g_m * h_m)) per row, heads m < nmat (gain g_m at gain + m g_stride)
