@@ -95,7 +95,9 @@ struct Geo : layout::Geo<DS> {
     // one chunk buffer (all waves); the passes without a second product keep no chunk in LDS
     static constexpr int YBUF = PC ? NW * layout::Geo<DS>::SLICE : 16;
     static constexpr int GB = PC ? XR * YC : 8;        // elements of the probability tile (second product only)
-    static constexpr int TOTAL = 2 * YBUF + NW * PR * PP * 4 + GB * 2 + 3 * XR * 4 + NW * XR * 4 + 4 * YC * 4;
+    // the passes without a second product keep two exchange buffers (see k_fused)
+    static constexpr int NPART = PC ? 1 : 2;
+    static constexpr int TOTAL = 2 * YBUF + NPART * NW * PR * PP * 4 + GB * 2 + 3 * XR * 4 + NW * XR * 4 + 4 * YC * 4;
     static_assert(TOTAL <= 160 * 1024, "LDS budget");
 };
 
@@ -141,7 +143,12 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     // from the chunk being prefetched (no needless waits on the prefetch).
     __shared__ __attribute__((aligned(16))) char ybufA[G::YBUF];
     __shared__ __attribute__((aligned(16))) char ybufB[G::YBUF];
+    // Exchange of the partial logits.  The passes without a second product take
+    // turns on two buffers and need one barrier per chunk: a wave that has finished the
+    // elementwise step of a chunk goes on to the products of the next one, and
+    // by the barrier after those every wave has left the buffer it then reuses.
     __shared__ __attribute__((aligned(16))) float part[NW * PR * PP];
+    __shared__ __attribute__((aligned(16))) float partB[RF ? NW * PR * PP : 4];
     __shared__ __attribute__((aligned(16))) bf16 gbuf[G::GB];
     __shared__ float abuf[XR];
     __shared__ float sbuf[XR];
@@ -307,7 +314,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     const int c_lo = layout::trread_off<DS>(lane, 0);
     const int c_hi = layout::trread_off<DS>(lane, 1);
 
-    auto step = [&](LDS_AS char* cur, unsigned nxt, LDS_AS float* side, unsigned side_nxt, int c)
+    auto step = [&](LDS_AS char* cur, unsigned nxt, LDS_AS float* prt, LDS_AS float* side, unsigned side_nxt, int c)
                     __attribute__((always_inline)) {
         const int y0 = c * YC;
         const bool more = c + 1 < ck_hi;
@@ -329,7 +336,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
 #pragma unroll
             for (int kk = 0; kk < G::NK; ++kk) ay[kk] = *(LDS_AS bf16x8*)(cur + ao + 64 * kk);
         }
-        if (more) issue_side(y0 + YC, side_nxt);
+        if (PC && more) issue_side(y0 + YC, side_nxt);
         f32x4 S[G::NXB];
 #pragma unroll
         for (int xb = 0; xb < G::NXB; ++xb) S[xb] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -354,10 +361,11 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
 #pragma unroll
         for (int xb = 0; xb < G::NXB; ++xb) {
             const int xl = 16 * xb + (lane & 15);
-            *(LDS_AS f32x4*)((LDS_AS float*)(LDS_AS void*)part + (w * PR + xl) * PP + 4 * ((lane >> 4) ^ ((xl >> 1) & 3))) =
+            *(LDS_AS f32x4*)(prt + (w * PR + xl) * PP + 4 * ((lane >> 4) ^ ((xl >> 1) & 3))) =
                 S[xb];
         }
         lds_barrier();
+        if (!PC && more) issue_side(y0 + YC, side_nxt);  // every wave has left the previous chunk's side data
         {
             // ---- elementwise step for rows xo[r] (lane: row xo[r], columns yy .. yy + EWC - 1)
 #pragma unroll
@@ -368,11 +376,11 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
 #pragma unroll
                 for (int ww = 0; ww < NW; ++ww) {
                     if constexpr (EWC == 2) {
-                        const f32x2 v = *(LDS_AS f32x2*)((LDS_AS float*)(LDS_AS void*)part + (ww * PR + xl) * PP + yq);
+                        const f32x2 v = *(LDS_AS f32x2*)(prt + (ww * PR + xl) * PP + yq);
                         q[0][ww] = v[0];
                         q[EWC - 1][ww] = v[1];
                     } else {
-                        q[0][ww] = ((LDS_AS float*)(LDS_AS void*)part)[(ww * PR + xl) * PP + yq];
+                        q[0][ww] = prt[(ww * PR + xl) * PP + yq];
                     }
                 }
                 static_assert(NW == 8, "partial-sum tree");
@@ -447,7 +455,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             }
         }
         if (PC && more) stream.template issue_range<kDmaA, G::NI>(nrs, d, nxt);
-        lds_barrier();
+        if (PC) lds_barrier();
 
         // 64-row tiles: the second product runs at raised wave priority, so that
         // a wave's products for the next chunk do not overtake the other wave's
@@ -492,13 +500,16 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         }
         if (PRIO) __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
-        wait_vm();
+        // the untracked streams: the chunk and the side data (wave 0's)
+        if (PC || ((!LL || BZ) && w == 0)) wait_vm();
     };
 
     wait_vm();
     for (int c = ck_lo; c < ck_hi; c += 2) {
-        step(sliceA, sliceB_u, (LDS_AS float*)(LDS_AS void*)recA, recB_u, c);
-        if (c + 1 < ck_hi) step(sliceB, sliceA_u, (LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
+        step(sliceA, sliceB_u, (LDS_AS float*)(LDS_AS void*)part, (LDS_AS float*)(LDS_AS void*)recA, recB_u, c);
+        if (c + 1 < ck_hi)
+            step(sliceB, sliceA_u, (LDS_AS float*)(LDS_AS void*)(RF ? partB : part),
+                 (LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
     }
 
     // ---- epilogues.  acc[b][h] lane layout: x = 32 h + lane%32,

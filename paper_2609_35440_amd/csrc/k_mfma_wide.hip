@@ -58,7 +58,7 @@ struct Geo : layoutw::Geo<DS> {
     static constexpr int NK = DS / 32;  // 32-deep k-steps of the logit product
     static constexpr int NB = DS / 16;  // 16-column accumulator blocks per wave
     static constexpr int YBUF = NW * layoutw::Geo<DS>::SLICE;
-    static constexpr int TOTAL = YBUF + NW * XR * PP * 4 + XR * YC * 2 + 2 * XR * 4 + NW * XR * 4 + 2 * YC * 16;
+    static constexpr int TOTAL = YBUF + (XR > 16 ? 2 : 1) * NW * XR * PP * 4 + XR * YC * 2 + 2 * XR * 4 + NW * XR * 4 + 2 * YC * 16;
     static_assert(TOTAL <= 160 * 1024, "LDS budget");
 };
 
@@ -92,7 +92,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     static_assert(!SPL || MODE == LOCAL || MODE == EVAL, "split over the vocabulary");
     const bool flat = RM && a.flat;
     __shared__ __attribute__((aligned(16))) char ybuf[PC ? G::YBUF : 16];
+    // exchange of the partial logits; two buffers in turn and one barrier per chunk
+    // without a second product, as in k_mfma.hip
     __shared__ __attribute__((aligned(16))) float part[NW * XR * PP];
+    __shared__ __attribute__((aligned(16))) float partB[PC ? 4 : NW * XR * PP];
     __shared__ __attribute__((aligned(16))) bf16 gbuf[XR * YC];
     __shared__ float abuf[XR];
     __shared__ float sbuf[XR];
@@ -249,14 +252,14 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     const int rd_even = layoutw::rowread_off<DS>(lane, 0);
     const int rd_odd = layoutw::rowread_off<DS>(lane, 1) - 64;
 
-    auto step = [&](LDS_AS float* side, unsigned side_nxt, int c) __attribute__((always_inline)) {
+    auto step = [&](LDS_AS float* prt, LDS_AS float* side, unsigned side_nxt, int c) __attribute__((always_inline)) {
         const int y0 = c * YC;
         const bool more = c + 1 < ck_hi;
         // reload with the next chunk (the last chunk reloads itself, unused)
         const __amdgpu_buffer_rsrc_t yn = rsrc_of(more ? c + 1 : c);
 
         // ---- (1) split-K partial of the logit tile S[y][x] over this wave's columns
-        if (more) issue_side(y0 + YC, side_nxt);
+        if (PC && more) issue_side(y0 + YC, side_nxt);
         f32x4 S[NXB];
 #pragma unroll
         for (int xb = 0; xb < NXB; ++xb) S[xb] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -272,16 +275,17 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
 #pragma unroll
         for (int xb = 0; xb < NXB; ++xb) {
             const int xl = 16 * xb + (lane & 15);
-            *(f32x4*)(part + (w * XR + xl) * PP + 4 * ((lane >> 4) ^ ((xl >> 1) & 3))) = S[xb];
+            *(LDS_AS f32x4*)(prt + (w * XR + xl) * PP + 4 * ((lane >> 4) ^ ((xl >> 1) & 3))) = S[xb];
         }
         lds_barrier();
+        if (!PC && more) issue_side(y0 + YC, side_nxt);  // every wave has left the previous chunk's side data
 
         // ---- (2) elementwise step (lane: rows xo[r], column yy)
 #pragma unroll
         for (int r = 0; r < ER; ++r) {
             float q[NW];
 #pragma unroll
-            for (int ww = 0; ww < NW; ++ww) q[ww] = part[(ww * XR + xo[r]) * PP + (yy ^ (4 * ((xo[r] >> 1) & 3)))];
+            for (int ww = 0; ww < NW; ++ww) q[ww] = prt[(ww * XR + xo[r]) * PP + (yy ^ (4 * ((xo[r] >> 1) & 3)))];
             static_assert(NW == 8, "partial-sum tree");
             const float sxy = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
             const int yg = y0 + yy;
@@ -324,7 +328,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
             }
             if (PC && wr[r]) gbuf[xo[r] * YC + (yy ^ (8 * ((xo[r] >> 3) & 1)))] = (bf16)gval;
         }
-        lds_barrier();
+        if (PC) lds_barrier();
 
         if (PC) {
             // ---- (3) second product: acc[j][x] += sum_y Y[y][j] G[x][y] over this wave's columns
@@ -349,14 +353,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
         // slice is rewritten by the next logit product only after this
         // chunk's transposing reads (LDS operations of a wave run in order)
         __builtin_amdgcn_sched_barrier(0);
-        wait_vm();
+        if (PC || ((!LL || BZ) && w == 0)) wait_vm();  // the side data (wave 0's) and the operand registers
     };
 
     wait_vm();
 
     for (int c = ck_lo; c < ck_hi; c += 2) {
-        step((LDS_AS float*)(LDS_AS void*)recA, recB_u, c);
-        if (c + 1 < ck_hi) step((LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
+        step((LDS_AS float*)(LDS_AS void*)part, (LDS_AS float*)(LDS_AS void*)recA, recB_u, c);
+        if (c + 1 < ck_hi)
+            step((LDS_AS float*)(LDS_AS void*)(PC ? part : partB), (LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
     }
 
     // ---- epilogues.  acc[b] lane layout: x = lane%16, j = js + 16 b + 4 (lane/16) + i
