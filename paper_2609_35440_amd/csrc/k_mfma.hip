@@ -96,7 +96,10 @@ struct Geo : layout::Geo<DS> {
     static constexpr int YBUF = PC ? NW * layout::Geo<DS>::SLICE : 16;
     static constexpr int GB = PC ? XR * YC : 8;        // elements of the probability tile (second product only)
     // the passes without a second product keep two exchange buffers (see k_fused)
-    static constexpr int NPART = PC ? 1 : 2;
+    // from d = 512 on; at 256 their registers allow two workgroups per CU and the second
+    // buffer's LDS would not (2 x 20000 x 256 x 600: 97 us with it, 84 without)
+    static constexpr bool TWO = !PC && DS > 32;
+    static constexpr int NPART = TWO ? 2 : 1;
     static constexpr int TOTAL = 2 * YBUF + NPART * NW * PR * PP * 4 + GB * 2 + 3 * XR * 4 + NW * XR * 4 + 4 * YC * 4;
     static_assert(TOTAL <= 160 * 1024, "LDS budget");
 };
@@ -143,12 +146,12 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     // from the chunk being prefetched (no needless waits on the prefetch).
     __shared__ __attribute__((aligned(16))) char ybufA[G::YBUF];
     __shared__ __attribute__((aligned(16))) char ybufB[G::YBUF];
-    // Exchange of the partial logits.  The passes without a second product take
+    // Exchange of the partial logits.  The wider passes without a second product take
     // turns on two buffers and need one barrier per chunk: a wave that has finished the
     // elementwise step of a chunk goes on to the products of the next one, and
     // by the barrier after those every wave has left the buffer it then reuses.
     __shared__ __attribute__((aligned(16))) float part[NW * PR * PP];
-    __shared__ __attribute__((aligned(16))) float partB[RF ? NW * PR * PP : 4];
+    __shared__ __attribute__((aligned(16))) float partB[G::TWO ? NW * PR * PP : 4];
     __shared__ __attribute__((aligned(16))) bf16 gbuf[G::GB];
     __shared__ float abuf[XR];
     __shared__ float sbuf[XR];
@@ -336,7 +339,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
 #pragma unroll
             for (int kk = 0; kk < G::NK; ++kk) ay[kk] = *(LDS_AS bf16x8*)(cur + ao + 64 * kk);
         }
-        if (PC && more) issue_side(y0 + YC, side_nxt);
+        if (!G::TWO && more) issue_side(y0 + YC, side_nxt);
         f32x4 S[G::NXB];
 #pragma unroll
         for (int xb = 0; xb < G::NXB; ++xb) S[xb] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -365,7 +368,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                 S[xb];
         }
         lds_barrier();
-        if (!PC && more) issue_side(y0 + YC, side_nxt);  // every wave has left the previous chunk's side data
+        if (G::TWO && more) issue_side(y0 + YC, side_nxt);  // every wave has left the previous chunk's side data
         {
             // ---- elementwise step for rows xo[r] (lane: row xo[r], columns yy .. yy + EWC - 1)
 #pragma unroll
@@ -455,7 +458,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             }
         }
         if (PC && more) stream.template issue_range<kDmaA, G::NI>(nrs, d, nxt);
-        if (PC) lds_barrier();
+        if (!G::TWO) lds_barrier();
 
         // 64-row tiles: the second product runs at raised wave priority, so that
         // a wave's products for the next chunk do not overtake the other wave's
@@ -508,7 +511,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     for (int c = ck_lo; c < ck_hi; c += 2) {
         step(sliceA, sliceB_u, (LDS_AS float*)(LDS_AS void*)part, (LDS_AS float*)(LDS_AS void*)recA, recB_u, c);
         if (c + 1 < ck_hi)
-            step(sliceB, sliceA_u, (LDS_AS float*)(LDS_AS void*)(RF ? partB : part),
+            step(sliceB, sliceA_u, (LDS_AS float*)(LDS_AS void*)(G::TWO ? partB : part),
                  (LDS_AS float*)(LDS_AS void*)recB, recA_u, c + 1);
     }
 

@@ -192,23 +192,90 @@ int local_splits(const Plan& P, int n, int K, int T, int d, int V, size_t room) 
     return best_split((long long)P.ntiles * n, ((long long)V + yc - 1) / yc, c, (double)room / ((double)K * T * (d + 4)));
 }
 
-// Exit evaluation on the matrix-core kernels: split, it reads the readouts
-// row-major and its parts (8 scalars per row and split) take the place of the
-// tiled copies; whole, it streams the copies, whose writing costs a read and a
-// write of every readout.  Returns the splits (1: whole).
-int eval_splits(const Plan& P, int K, int T, int d, int V, bool flat) {
+// Exit evaluation on the matrix-core families runs in one of three forms:
+//   FUSED  the fused pass over whole row tiles, streaming tiled readout copies
+//          (their writing costs a read and a write of every readout);
+//   SPLIT  the fused pass split over the vocabulary, reading the readouts
+//          row-major: few rows, memory-bound; the parts (8 scalars per row and
+//          split) take the place of the copies;
+//   PROD   the tiled product (k_logits.hip): 256 x 256 tiles, so many rows; the
+//          copies of bf16(g * h) it multiplies, `pass_rows` rows at a time,
+//          and its parts take the place of the readout copies.
+// The form with the least estimated time is taken.  Measured: 60 us per tile of
+// 256 x 256 of the product at d = 2048, 10 at d = 256; 1.05 and 1.28 us per chunk of 16
+// readout rows of the fused pass at d = 2048 (64 rows per tile) and 1024 (128),
+// 0.9 at d = 256 (128).  4 x 8192 x 32000 rows: product against fused pass 2.01
+// against 2.55 ms at d = 1024, 0.67 against 1.79 at d = 256.
+struct EvalPlan {
+    enum Form { FUSED, SPLIT, PROD } form = FUSED;
+    int nsplit = 1;
+    long long pass_rows = 0;
+};
+
+double prod_tile_us(int d) { return 4.0 + 0.027 * d; }
+double eval_chunk_us(int rows, int d) { return 0.2 + 0.0055 * rows + 0.45 * (double)rows * d / 131072.0; }
+
+EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
+    EvalPlan E;
     const int rows = P.wide ? solo::kMfmaWideEvalRows : solo::mfma_eval_rows(d);
     const long long tiles = (long long)K * ((T + rows - 1) / rows);
     const long long stiles = flat ? ((long long)K * T + rows - 1) / rows : tiles;
     const long long nch = ((long long)V + 15) / 16;
-    const double chunk = 0.3 + 0.8 * (double)rows * d / 131072.0;
-    const double whole = (double)((tiles + 255) / 256) * (double)nch * chunk +
-                         (1 + P.nhead_tiles) * (4.0 + 4.0 * (double)V * d / 4e6);
+    const double chunk = eval_chunk_us(rows, d);
+    double best = (double)((tiles + 255) / 256) * (double)nch * chunk +
+                  (1 + P.nhead_tiles) * (4.0 + 4.0 * (double)V * d / 4e6);
+    const double kt = (double)K * T;
     const double room = (double)solo::tiled_elems(V, d) * 2.0;
-    const SplitCost c = {1.3 * chunk, 5.0, (double)K * T * 64.0 / 3e6};
     double us = 0.0;
-    const int s = best_split(stiles, nch, c, room / ((double)K * T * 32.0), &us);
-    return s > 1 && us < whole ? s : 1;
+    // (row-major, a chunk's operand loads take 16 rows of 64 bytes each: 1.75 us at d = 2048)
+    const SplitCost c = {1.05 * chunk > 0.00085 * d ? 1.05 * chunk : 0.00085 * d, 10.0, kt * 64.0 / 3e6};
+    const int s = best_split(stiles, nch, c, room / (kt * 32.0), &us);
+    if (s > 1 && us < best) {
+        E.form = EvalPlan::SPLIT;
+        E.nsplit = s;
+        best = us;
+    }
+    const long long lists = flat ? 1 : K, n = flat ? (long long)K * T : T;  // rows are one list, or one per module
+    const long long nvt = ((long long)V + 255) / 256;
+    for (int sp = 1; sp <= 32 && sp <= nvt; ++sp) {
+        const double cap = (room - 512.0 - (sp > 1 ? kt * 32.0 * sp : 0.0)) / (2.0 * d);
+        if (cap < 256.0) break;
+        const long long np0 = (long long)((double)n / cap) + 1;
+        for (long long np = np0; np < np0 + 4; ++np) {
+            const long long pr = ((n + np - 1) / np + 255) / 256 * 256;
+            if ((double)(pr < n ? pr : n) > cap) continue;
+            const long long whole = n / pr, rest = n - whole * pr;
+            auto rounds = [&](long long r) { return (double)(((r + 255) / 256 * sp + 255) / 256); };
+            const double t = (double)lists * ((whole * rounds(pr) + (rest ? rounds(rest) : 0.0)) *
+                                                  (double)((nvt + sp - 1) / sp) * prod_tile_us(d) +
+                                              (double)(whole + (rest > 0)) * 8.0) +
+                             10.0 + kt * d * 4.0 / 4e6 + (sp > 1 ? 5.0 + kt * 64.0 * sp / 3e6 : 0.0);
+            if (t < best) {
+                best = t;
+                E.form = EvalPlan::PROD;
+                E.nsplit = sp;
+                E.pass_rows = pr;
+            }
+        }
+    }
+    return E;
+}
+
+// The bias-gradient pass over n modules as a tiled product (the readout rows
+// against all tokens): the splits of its tokens, or 0 where the fused pass is
+// estimated faster (few tokens: a tile is 256 of them; a chunk of the fused pass
+// measured 1.2 times one of exit evaluation).  Its parts but the last, which
+// goes to the output, take the place of the row statistics and losses (3 K T
+// floats), which no later stage reads.
+int prod_bgrad_splits(const Plan& P, int n, int K, int T, int d, int V) {
+    const int rows = P.wide ? solo::kMfmaWideEvalRows : solo::mfma_eval_rows(d);
+    const double chunk = 1.2 * eval_chunk_us(rows, d);
+    const double fused = (double)(((((long long)V + rows - 1) / rows) * n + 255) / 256) * (double)((T + 15) / 16) * chunk;
+    const SplitCost c = {prod_tile_us(d), 4.0, (double)n * V * 8.0 / 3e6};
+    double us = 0.0;
+    const int s = best_split((((long long)V + 255) / 256) * n, ((long long)T + 255) / 256, c,
+                             1.0 + 3.0 * K * T / ((double)n * V), &us);
+    return us < fused ? s : 0;
 }
 
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
@@ -305,13 +372,13 @@ int run(const solo_readout_args& x, bool eval) {
         return SOLO_ERR_HIP;
     // exit evaluation of few rows: split over the vocabulary, no tiled copies
     const bool flat = eval && P.mfma && !P.rot && !x.bias && !P.nhead_tiles;
-    const int esplit = eval && P.mfma ? eval_splits(P, K, T, d, V, flat) : 1;
-    if (esplit > 1) {
-        a.nsplit = esplit;
-        a.split_stat = (float*)(ws + P.wtile);
+    const EvalPlan E = eval && P.mfma ? plan_eval(P, K, T, d, V, flat) : EvalPlan();
+    a.split_stat = (float*)(ws + P.wtile);
+    if (E.form == EvalPlan::SPLIT) {
+        a.nsplit = E.nsplit;
         a.flat = flat;
     }
-    if (tiled_readout(P) && esplit == 1) {
+    if (tiled_readout(P) && E.form == EvalPlan::FUSED) {
         if (solo::launch_tile((const solo::bf16*)x.W, 0, nullptr, 0, (solo::bf16*)(ws + P.wtile), 1, V, d, s) !=
             hipSuccess)
             return SOLO_ERR_HIP;
@@ -372,8 +439,55 @@ int run(const solo_readout_args& x, bool eval) {
         if (!P.rot || hi <= K - 1 || lo >= K - 1) return pass(which, P.rot && lo < K - 1 ? ah : a, lo, hi - lo) == hipSuccess;
         return pass(which, ah, lo, K - 1 - lo) == hipSuccess && pass(which, a, K - 1, hi - K + 1) == hipSuccess;
     };
-    if (!pass_range(eval ? 0 : 1, 0, K)) return SOLO_ERR_HIP;
-    if (esplit > 1 && solo::launch_merge_eval(a, (long long)K * T, s) != hipSuccess) return SOLO_ERR_HIP;
+    // exit evaluation as a tiled product over the rows of all modules, or of one at a time
+    auto prod_eval = [&]() -> bool {
+        const long long n = flat ? (long long)K * T : T;
+        const size_t parts = E.nsplit > 1 ? align_up((size_t)K * T * 32 * E.nsplit) : 0;
+        solo::bf16* const copy = (solo::bf16*)(ws + P.wtile + parts);
+        for (int k = 0; k < (flat ? 1 : K); ++k) {
+            const solo::FusedArgs& g = P.rot && k < K - 1 ? ah : a;
+            solo::LogitsArgs l = {};
+            l.Y = (const solo::bf16*)(flat || k == K - 1 ? a.Wt : (const void*)((const solo::bf16*)a.Wh + k * a.wh_stride));
+            l.nY = V;
+            l.d = d;
+            l.x_last = -1;
+            l.nsplit = E.nsplit;
+            l.parts = a.split_stat;
+            l.part_rows = (long long)K * T;
+            l.bias = x.bias ? x.bias + (long long)k * V : nullptr;
+            l.T = T;
+            l.rstd = a.rstd;
+            l.tau = a.tau;
+            l.targets = a.targets;
+            l.rowloss = a.rowloss;
+            l.top1 = a.top1;
+            for (long long r0 = 0; r0 < n; r0 += E.pass_rows) {
+                const long long nr = n - r0 < E.pass_rows ? n - r0 : E.pass_rows;
+                l.row0 = (flat ? 0 : (long long)k * T) + r0;
+                l.nX = (int)nr;
+                // the rows' products with their modules' gains
+                for (long long r = 0; r < nr;) {
+                    const long long m = (l.row0 + r) / T;
+                    const long long end = g.g_stride ? (m + 1) * T - l.row0 : nr;
+                    const long long cnt = (end < nr ? end : nr) - r;
+                    if (solo::launch_gain_rows((const solo::bf16*)g.h + (l.row0 + r) * d, 0,
+                                               (const solo::bf16*)g.gain + m * g.g_stride, 0, copy + r * d, 0, 1, (int)cnt,
+                                               d, s) != hipSuccess)
+                        return false;
+                    r += cnt;
+                }
+                l.X = copy;
+                if (solo::launch_logits_eval(l, s) != hipSuccess) return false;
+            }
+        }
+        return true;
+    };
+    if (E.form == EvalPlan::PROD ? !prod_eval() : !pass_range(eval ? 0 : 1, 0, K)) return SOLO_ERR_HIP;
+    if (E.nsplit > 1) {
+        a.nsplit = E.nsplit;
+        if (solo::launch_merge_eval(a, (long long)K * T, s) != hipSuccess) return SOLO_ERR_HIP;
+        a.nsplit = 1;
+    }
     if (P.rot && !eval) {
         // back to the basis of h: D = e R_k = e (R_k^T)^T, then the heads' RMSNorm
         // backward (and their gain partials when every module trains its gain)
@@ -406,12 +520,36 @@ int run(const solo_readout_args& x, bool eval) {
         if (!P.rot || hi <= K - 1 || lo >= K - 1) return copies(P.rot && lo < K - 1 ? ah : a, lo, hi, as_tiles);
         return copies(ah, lo, K - 1, as_tiles) && copies(a, K - 1, hi, as_tiles);
     };
+    const int nbg = P.bg_hi - P.bg_lo;
+    const int bsplit = !eval && P.mfma && nbg > 0 ? prod_bgrad_splits(P, nbg, K, T, d, V) : 0;
     if (!eval && P.mfma &&
-        (!gain_copies(P.rg_lo, P.rg_hi, tiled_rgrad(P)) || !gain_copies(P.bg_lo, P.bg_hi, true)))
+        (!gain_copies(P.rg_lo, P.rg_hi, tiled_rgrad(P)) || !gain_copies(P.bg_lo, P.bg_hi, bsplit == 0)))
         return SOLO_ERR_HIP;
     if (!eval && !pass_range(2, P.rg_lo, P.rg_hi)) return SOLO_ERR_HIP;
     if (!mark(3)) return SOLO_ERR_HIP;
-    if (!eval && !pass_range(3, P.bg_lo, P.bg_hi)) return SOLO_ERR_HIP;
+    auto prod_bgrad = [&]() -> bool {
+        const int lo = P.bg_lo;
+        const solo::bf16* const heads = (const solo::bf16*)a.Wh;
+        const solo::bf16* const term = (const solo::bf16*)a.Wt;
+        solo::LogitsArgs l = {};
+        l.X = lo < K - 1 ? heads + lo * a.wh_stride : term;
+        l.x_stride = lo < K - 1 ? a.wh_stride : 0;
+        l.x_last = lo < K - 1 && P.bg_hi == K ? K - 1 - lo : -1;
+        l.x_last_off = ((intptr_t)term - (intptr_t)(heads + (K - 1) * a.wh_stride)) / 2;
+        l.Y = (const solo::bf16*)a.hg + (long long)(lo - P.hg_lo) * solo::tiled_elems(T, d);
+        l.y_stride = solo::tiled_elems(T, d);
+        l.nX = V;
+        l.nY = T;
+        l.d = d;
+        l.nsplit = bsplit;
+        l.parts = (float*)(ws + P.rstd);
+        l.bias = x.bias ? x.bias + (long long)lo * V : nullptr;
+        l.rowrec = a.rowrec + 4LL * lo * T;
+        l.out = x.dbias + (long long)lo * V;
+        l.inv_T = a.inv_T;
+        return solo::launch_logits_bgrad(l, nbg, s) == hipSuccess;
+    };
+    if (!eval && (bsplit > 0 ? !prod_bgrad() : !pass_range(3, P.bg_lo, P.bg_hi))) return SOLO_ERR_HIP;
     if (!mark(4)) return SOLO_ERR_HIP;
     if (!eval && P.slots) {
         if (solo::launch_dgain_reduce(a.dgain_part, x.dgain, P.slots, P.ntiles, d, s) != hipSuccess)

@@ -106,6 +106,34 @@ hipError_t launch_local_loss_mfma(const FusedArgs& a, bool ext, int nmod, hipStr
 hipError_t launch_exit_eval_mfma(const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_readout_grad_mfma(const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_bias_grad_mfma(const FusedArgs& a, int nmod, hipStream_t s);
+// forward-only passes as a tiled product (k_logits.hip): d % 256 == 0
+struct LogitsArgs {
+    const bf16* X;          // [nX][d] stationary rows; module m of a launch x_stride elements further,
+    long long x_stride;     // and module x_last another x_last_off (the terminal's own readout)
+    int x_last;
+    long long x_last_off;
+    const bf16* Y;          // [nY][d] streamed rows, module m y_stride further
+    long long y_stride;
+    int nX, nY, d;
+    int nsplit;             // workgroups the streamed tiles of a row tile are split over
+    float* parts;           // nsplit > 1: exit evaluation [nsplit][part_rows][8] as FusedArgs::split_stat, at the
+                            // global row; bias gradient [nsplit - 1][nmod][nX] sums
+    const float* bias;      // exit evaluation [nY]; bias gradient [nmod][nX]; or null
+    // exit evaluation: X row i is the global row row0 + i (module row / T)
+    long long row0, part_rows;
+    int T;
+    const float* rstd;
+    const float* tau;
+    const int32_t* targets;
+    float* rowloss;
+    int32_t* top1;
+    // bias gradient
+    const float* rowrec;    // [nmod][nY][4]
+    float* out;             // [nmod][nX]
+    float inv_T;
+};
+hipError_t launch_logits_eval(const LogitsArgs& a, hipStream_t s);
+hipError_t launch_logits_bgrad(const LogitsArgs& a, int nmod, hipStream_t s);
 // the wide matrix-core kernels (k_mfma_wide.hip): d = 2560
 bool mfma_wide_supported(int dtype, int d);
 constexpr int kMfmaWideEvalRows = 48;  // stationary rows per workgroup of their forward-only passes

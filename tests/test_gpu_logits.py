@@ -1,0 +1,89 @@
+"""The forward-only passes as a tiled product (exit evaluation over many rows, the
+bias gradient over many tokens) at the edges of their 256 x 256 tiles: a last
+tile of one row of either operand, rows in one list over modules with
+their own gains and temperatures, one list per module (biases, one readout per
+head), more rows than one pass holds, invalid targets, vocabulary entries masked
+by a bias of -inf, the largest negative bias, and ties across tiles.
+
+The calls are sized so that the product form is the one taken (see plan_eval and
+prod_bgrad_splits in solo_api.hip)."""
+import numpy as np
+import pytest
+
+import oracle
+from solo_inputs import make_extras, make_inputs
+from tests.gpu_helpers import rel_max_err
+from tests.test_gpu_general import check_exit_eval, compare, oracle_general, run_exit_eval, run_general
+
+pytestmark = pytest.mark.gpu
+
+
+# a last tile of one row of either operand; the last case takes two passes of rows
+EVAL = [("plain", 2, 1537, 16129, dict()), ("one-list", 2, 1537, 16129, dict(per_module_gain=True, tau=True)),
+        ("bias", 2, 1537, 16129, dict(bias=True)),
+        ("per-head", 2, 1537, 16129, dict(wbar="per_head", bias=True, tau=True)),
+        ("two-passes", 2, 6017, 12289, dict(per_module_gain=True))]
+
+
+@pytest.mark.parametrize("name,K,T,V,extras", EVAL, ids=[c[0] for c in EVAL])
+def test_eval(name, K, T, V, extras):
+    x = make_extras(make_inputs("1b", seed=12, K=K, T=T, d=256, V=V), seed=12, **extras)
+    losses, row_loss, top1 = run_exit_eval(x)
+    check_exit_eval(x, losses, row_loss, top1, f"product eval {name}", min_rows_for_agreement=100)
+
+
+def _device(K, T, d, V, seed=4):
+    import torch
+
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    h = torch.randn(K, T, d, generator=g, device="cuda").to(torch.bfloat16)
+    W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).to(torch.bfloat16)
+    y = torch.randint(0, V, (K, T), generator=g, device="cuda", dtype=torch.int32)
+    return h, torch.ones(d, dtype=torch.bfloat16, device="cuda"), W, y
+
+
+def test_eval_masks_ties_and_invalid_targets():
+    import torch
+
+    from paper_2609_35440_amd import binding
+
+    K, T, d, V = 1, 3073, 256, 12289
+    h, gain, W, y = _device(K, T, d, V)
+    W[12288] = W[70] = W[2500] = (0.1 * h[0, 7].float()).to(torch.bfloat16)
+    y[0, 11] = V + 5
+    y[0, 12] = -1
+    plain = binding.exit_eval(h, gain, W, y)
+    assert int(plain.top1[0, 7]) == 70
+    bad = torch.isnan(plain.row_loss[0])
+    assert bad[11] and bad[12] and int(bad.sum()) == 2
+    # half the vocabulary masked, by -inf and by the type's lowest value, the target kept
+    y = (y.clamp(0, V - 1) // 2 * 2).clamp(max=V - 1)
+    for low in (-float("inf"), torch.finfo(torch.float32).min):
+        bias = torch.zeros(K, V, device="cuda")
+        bias[:, 1::2] = low
+        r = binding.exit_eval(h, gain, W, y, bias=bias)
+        z = (h[0].double() * torch.rsqrt(h[0].double().square().mean(1, keepdim=True) + 1e-6)) @ W.double().t()
+        z[:, 1::2] = -float("inf")
+        ref = torch.logsumexp(z, 1) - z.gather(1, y[0].long()[:, None])[:, 0]
+        assert float((r.row_loss[0].double() - ref).abs().max()) < 2e-2
+        assert int((r.top1 % 2).sum()) == 0
+    # everything but the target masked: no loss
+    bias = torch.full((K, V), -float("inf"), device="cuda")
+    bias[:, 12288] = 0.0
+    r = binding.exit_eval(h, gain, W, torch.full_like(y, 12288), bias=bias)
+    assert torch.equal(r.row_loss, torch.zeros_like(r.row_loss)) and bool((r.top1 == 12288).all())
+
+
+@pytest.mark.parametrize("T,V,extras,final", [(2049, 1025, dict(bias=True, tau=True), True),
+                                              (1800, 513, dict(wbar="per_head", bias=True), False),
+                                              (2304, 769, dict(per_module_gain=True), True),
+                                              (1500, 600, dict(rot=True, tau=True), True)],
+                         ids=["heads", "all-per-head", "no-bias", "rot"])
+def test_bias_gradient(T, V, extras, final):
+    x = make_extras(make_inputs("1b", seed=13, K=3, T=T, d=256, V=V), seed=13, **extras)
+    flags = dict(final_module_dW=final, want_dtau=True, want_dbias=True)
+    g = run_general(x, flags)
+    ref = oracle_general(x, flags)
+    compare(g, ref, "bf16", flags, f"product bias gradient {T} {V}")
+    for k in range(3):
+        assert rel_max_err(g["dbias"][k], ref["dbias"][k]) <= 2e-2
