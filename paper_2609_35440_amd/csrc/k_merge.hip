@@ -38,8 +38,12 @@ template <typename E> __device__ __forceinline__ void st4(E* p, f32x4 v) {
 
 constexpr int kQ = 4;  // 1024-column groups of the widest row (4096)
 
-// FAM: the records the family's gradient passes read (see FusedArgs::rowrec)
-template <typename E, bool F32FAM>
+// What the form's gradient passes read: the record's first entry is the
+// log-sum-exp (base 2), or the maximum with 1 / s in the lse array (fp32
+// kernels; they scale by that array, so the exact form, whose bias gradient they
+// compute, leaves ones there); e goes to the rotate-back buffer as two bf16
+// planes, or in fp32.
+template <typename E, int FORM>
 __global__ __launch_bounds__(256) void k_merge(FusedArgs a) {
     __shared__ float red[4];
     const int k = a.m0 + (int)blockIdx.y;
@@ -70,10 +74,10 @@ __global__ __launch_bounds__(256) void k_merge(FusedArgs a) {
     if (threadIdx.x == 0) {
         a.rowloss[row] = re.loss;
         if (a.rowrec) {
-            const f32x4 r4 = {F32FAM ? m : re.lse2, r * tau * kLog2e, __int_as_float(tgt), re.py1};
+            const f32x4 r4 = {FORM == MERGE_F32 ? m : re.lse2, r * tau * kLog2e, __int_as_float(tgt), re.py1};
             *(f32x4*)(a.rowrec + 4 * row) = r4;
         }
-        a.lse[row] = F32FAM ? re.inv_s : re.lse2 * kLn2;
+        a.lse[row] = FORM == MERGE_F32 ? re.inv_s : (FORM == MERGE_EXACT ? 1.f : re.lse2 * kLn2);
     }
     const E* hr = (const E*)a.h + row * d;
     const E* wr = Rk + (long long)(tok ? tgt : 0) * d;
@@ -113,7 +117,7 @@ __global__ __launch_bounds__(256) void k_merge(FusedArgs a) {
         const int j = 1024 * q + j0;
         if (j >= d) break;
         if (a.ebuf) {
-            if (F32FAM) {
+            if (FORM != MERGE_BF16) {
                 *(f32x4*)((float*)a.ebuf + row * d + j) = ev[q];
             } else {
                 bf16x4 hi, lo;
@@ -199,9 +203,9 @@ __global__ __launch_bounds__(256) void k_merge_eval(FusedArgs a, long long rows)
     }
 }
 
-template <typename E, bool F32FAM>
+template <typename E, int FORM>
 hipError_t launch_t(const FusedArgs& a, int nmod, int rows, hipStream_t s) {
-    hipLaunchKernelGGL((k_merge<E, F32FAM>), dim3((unsigned)a.T, (unsigned)nmod), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_merge<E, FORM>), dim3((unsigned)a.T, (unsigned)nmod), dim3(256), 0, s, a);
     const hipError_t e = hipGetLastError();
     // (the terminal's gain alone: only a launch that holds the terminal has partials)
     if (e != hipSuccess || a.ebuf || !a.dg_mode || (a.dg_mode == 1 && a.m0 + nmod != a.K)) return e;
@@ -217,9 +221,11 @@ hipError_t launch_merge_eval(const FusedArgs& a, long long rows, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t launch_merge(int dtype, bool f32fam, const FusedArgs& a, int nmod, int rows, hipStream_t s) {
-    if (dtype != 0) return launch_t<float, true>(a, nmod, rows, s);
-    return f32fam ? launch_t<bf16, true>(a, nmod, rows, s) : launch_t<bf16, false>(a, nmod, rows, s);
+hipError_t launch_merge(int dtype, MergeForm form, const FusedArgs& a, int nmod, int rows, hipStream_t s) {
+    if (dtype != 0) return launch_t<float, MERGE_F32>(a, nmod, rows, s);
+    return form == MERGE_BF16 ? launch_t<bf16, MERGE_BF16>(a, nmod, rows, s)
+           : form == MERGE_F32 ? launch_t<bf16, MERGE_F32>(a, nmod, rows, s)
+                               : launch_t<bf16, MERGE_EXACT>(a, nmod, rows, s);
 }
 
 }  // namespace solo

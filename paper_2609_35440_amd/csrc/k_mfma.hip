@@ -75,12 +75,17 @@ enum Mode { LOCAL = 0, RGRAD = 1, BGRAD = 2, EVAL = 3 };
 // otherwise.  The passes without a second product (no accumulator) hold as
 // many rows as 128 registers of stationary operand take: 128 up to d = 1024,
 // 64 at d = 2048.  The readout streamed per flop halves with each doubling.
-template <int DS, bool PC>
-constexpr int rows_of() { return (!PC && DS <= 128) ? 128 : ((DS <= 128 || (!PC && DS <= 256)) ? 64 : 32); }
+// The exact form (XA, see k_fused) holds two planes of the stationary operand.
+template <int DS, bool PC, bool XA = false>
+constexpr int rows_of() {
+    if (XA) return DS <= 96 ? 64 : 32;
+    return (!PC && DS <= 128) ? 128 : ((DS <= 128 || (!PC && DS <= 256)) ? 64 : 32); }
 
-template <int DS, bool PC>
+template <int DS, bool PC, bool XA = false>
 struct Geo : layout::Geo<DS> {
-    static constexpr int XR = rows_of<DS, PC>();       // stationary rows per workgroup
+    static constexpr int XR = rows_of<DS, PC, XA>();   // stationary rows per workgroup
+    static constexpr int NXP = XA ? 2 : 1;             // planes of the stationary operand
+    static constexpr int NGP = XA ? 3 : 1;             // planes of the probability tile
     static constexpr int PR = XR;                      // rows of the partial-logit exchange buffer
     static constexpr int NXB = XR / 16;                // 16-row blocks of the logit product
     static constexpr int NR = XR / 32;                 // 32-row halves of the second product
@@ -94,7 +99,7 @@ struct Geo : layout::Geo<DS> {
     static constexpr int NK = DS / 32;                 // 32-deep k-steps of the logit product
     // one chunk buffer (all waves); the passes without a second product keep no chunk in LDS
     static constexpr int YBUF = PC ? NW * layout::Geo<DS>::SLICE : 16;
-    static constexpr int GB = PC ? XR * YC : 8;        // elements of the probability tile (second product only)
+    static constexpr int GB = PC ? NGP * XR * YC : 8;  // elements of the probability tile (second product only)
     // the passes without a second product keep two exchange buffers (see k_fused)
     // from d = 512 on; at 256 their registers allow two workgroups per CU and the second
     // buffer's LDS would not (2 x 20000 x 256 x 600: 97 us with it, 84 without)
@@ -122,10 +127,20 @@ __device__ __forceinline__ const bf16* tiled_readout_of(const FusedArgs& a, int 
 // 16 rows per load: few rows read it, so it comes from memory once and a tiled
 // copy would triple the traffic; and it can take the rows of all modules as one
 // list (a.flat) where they share one readout and no biases.
-template <int MODE, int DS, bool EXT, bool SPL>
+// XA (LOCAL and RGRAD): products exact to fp32, for bf16 storage whose calls are
+// defined in fp32 (the widths outside this family's own): the stationary
+// operand g * h (or g * R) has 16 significant bits and is held as two bf16
+// planes, a probability or delta as three, and every product of planes is exact
+// in the fp32 accumulation, so the streamed bf16 operand meets the full values
+// at 2 and 3 matrix instructions instead of the fp32 instructions' 16 times
+// slower rate.  Y is then the raw operand (R or h; dR_v = g * the sum).  The
+// width d is any multiple of 8 up to 8 DS; columns past it read as zeros and
+// are not written.
+template <int MODE, int DS, bool EXT, bool SPL, bool XA = false>
 __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     constexpr bool PC = MODE == LOCAL || MODE == RGRAD;     // second product
-    using G = Geo<DS, PC>;
+    static_assert(!XA || PC, "the exact form is of the passes with a second product");
+    using G = Geo<DS, PC, XA>;
     constexpr int XR = G::XR;
     constexpr int NR = G::NR;
     constexpr int PR = G::PR;
@@ -179,7 +194,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     // the direct-to-LDS stream, tiled for the register-fed passes); module
     // copies sit tiled_elems(T, d) apart either way
     const bf16* __restrict__ Y = LL ? (RF && !RM ? tiled_readout_of(a, k) : Rk)
-                                    : (const bf16*)a.hg + (long long)(k - a.hg_m0) * tiled_elems(a.T, d);
+                              : (XA ? hk : (const bf16*)a.hg + (long long)(k - a.hg_m0) * tiled_elems(a.T, d));
     const int nX = LL ? (flat ? a.K * a.T : a.T) : a.V;
     const int nY = LL ? a.V : a.T;
     const int nchunks = (nY + YC - 1) / YC;
@@ -218,7 +233,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     const bool has_bias = BZ || a.bias != nullptr;  // the bias variant always has one
 
     ChunkStream<DS> stream;
-    if (PC) stream.init(d, js, lane);
+    if (PC) stream.template init<XA>(d, js, lane);
     // first chunk in flight before the stationary operand is read
     const unsigned sliceA_u = lds_addr(sliceA), sliceB_u = lds_addr(sliceB);
     if (PC) stream.issue(Y, nY, d, ck_lo * YC, sliceA_u);
@@ -266,22 +281,31 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     // rounded once): B of the 16x16x32 logit product, lane holds
     // X[x0 + 16 xb + lane%16][js + 32 kk + 8 (lane/16) .. +7]
     bf16x8 xr[G::NXB][G::NK];
+    bf16x8 xlo[XA ? G::NXB : 1][G::NK];  // XA: the second plane
 #pragma unroll
     for (int kk = 0; kk < G::NK; ++kk) {
         const int j0 = js + 32 * kk + 8 * (lane >> 4);
-        bf16x8 gv = *(const bf16x8*)(gk + j0);
+        const bool jok = !XA || j0 < d;
+        bf16x8 gv = *(const bf16x8*)(gk + (jok ? j0 : 0));
 #pragma unroll
         for (int xb = 0; xb < G::NXB; ++xb) {
             const int xrow = x0 + 16 * xb + (lane & 15);
             bf16x8 xv;
-            if (xrow < nX) {
+            if (xrow < nX && jok) {
                 xv = *(const bf16x8*)(X + (long long)xrow * d + j0);
                 if (flat) gv = *(const bf16x8*)((const bf16*)a.gain + (long long)(xrow / a.T) * a.g_stride + j0);
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) xv[e] = (bf16)0.f;
             }
-            if (LL) {
+            if (XA) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float p = (float)xv[e] * (float)gv[e];  // exact: 16 bits
+                    xr[xb][kk][e] = (bf16)p;
+                    xlo[XA ? xb : 0][kk][e] = (bf16)(p - (float)xr[xb][kk][e]);
+                }
+            } else if (LL) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) xr[xb][kk][e] = (bf16)((float)xv[e] * (float)gv[e]);
             } else {
@@ -353,6 +377,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             } else {
 #pragma unroll
                 for (int xb = 0; xb < G::NXB; ++xb) S[xb] = mfma16(ay[kk], xr[xb][kk], S[xb]);
+                if constexpr (XA) {
+#pragma unroll
+                    for (int xb = 0; xb < G::NXB; ++xb) S[xb] = mfma16(ay[kk], xlo[XA ? xb : 0][kk], S[xb]);
+                }
                 if (kk < kDmaA) {
                     if (more) stream.issue_one(nrs, d, nxt, kk);
                     __builtin_amdgcn_sched_barrier(0);  // keeps the instruction between these products
@@ -445,14 +473,23 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                     }
                 }
                 if (PC) {
-                    bf16* gp = gbuf + xo[r] * YC + (yy ^ (8 * ((xo[r] >> 2) & 1)));
-                    if constexpr (EWC == 2) {
-                        bf16x2 g2;
-                        g2[0] = (bf16)gval[0];
-                        g2[1] = (bf16)gval[EWC - 1];
-                        *(bf16x2*)gp = g2;
-                    } else {
-                        *gp = (bf16)gval[0];
+#pragma unroll
+                    for (int pl = 0; pl < G::NGP; ++pl) {
+                        bf16* gp = gbuf + (pl * XR + xo[r]) * YC + (yy ^ (8 * ((xo[r] >> 2) & 1)));
+                        if constexpr (EWC == 2) {
+                            bf16x2 g2;
+                            g2[0] = (bf16)gval[0];
+                            g2[1] = (bf16)gval[EWC - 1];
+                            *(bf16x2*)gp = g2;
+                            if (XA) {
+                                gval[0] -= (float)g2[0];
+                                gval[EWC - 1] -= (float)g2[1];
+                            }
+                        } else {
+                            const bf16 g1 = (bf16)gval[0];
+                            *gp = g1;
+                            if (XA) gval[0] -= (float)g1;
+                        }
                     }
                 }
             }
@@ -468,12 +505,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         if (PRIO) __builtin_amdgcn_s_setprio(2);
         if (PC) {
             // ---- second product: acc[j][x] += sum_y Y[y][j] G[x][y] over this wave's columns
-            bf16x8 gfrag[NR];
+            bf16x8 gfrag[G::NGP][NR];
 #pragma unroll
-            for (int h = 0; h < NR; ++h) {
-                const int xg = 32 * h + (lane & 31);
-                gfrag[h] = *(bf16x8*)(gbuf + xg * YC + 8 * ((lane >> 5) ^ ((xg >> 2) & 1)));
-            }
+            for (int pl = 0; pl < G::NGP; ++pl)
+#pragma unroll
+                for (int h = 0; h < NR; ++h) {
+                    const int xg = 32 * h + (lane & 31);
+                    gfrag[pl][h] =
+                        *(bf16x8*)(gbuf + (pl * XR + xg) * YC + 8 * ((lane >> 5) ^ ((xg >> 2) & 1)));
+                }
             if (MODE == LOCAL) {
 #pragma unroll
                 for (int h = 0; h < NR; ++h) {
@@ -498,7 +538,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                 at[0] = tlo[b][0]; at[1] = tlo[b][1]; at[2] = tlo[b][2]; at[3] = tlo[b][3];
                 at[4] = thi[b][0]; at[5] = thi[b][1]; at[6] = thi[b][2]; at[7] = thi[b][3];
 #pragma unroll
-                for (int h = 0; h < NR; ++h) acc[PC ? b : 0][h] = mfma32(at, gfrag[h], acc[PC ? b : 0][h]);
+                for (int pl = 0; pl < G::NGP; ++pl)
+#pragma unroll
+                    for (int h = 0; h < NR; ++h) acc[PC ? b : 0][h] = mfma32(at, gfrag[pl][h], acc[PC ? b : 0][h]);
             }
         }
         if (PRIO) __builtin_amdgcn_s_setprio(0);
@@ -555,7 +597,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                 const RowEnd re = finish_row(m_run[r], sx, zy, tok);
                 if (xr_ < nX) {
                     const long long t = modoff + xr_;
-                    a.lse[t] = re.lse2 * kLn2;
+                    a.lse[t] = XA ? 1.f : re.lse2 * kLn2;  // (the fp32 family's gradient passes scale by it)
                     a.rowloss[t] = re.loss;
                     if (MODE == EVAL && a.top1) a.top1[t] = bv;
                     if (MODE == LOCAL && a.rowrec) {
@@ -583,7 +625,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                     f32x4 o;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = acc[b][h][4 * i4 + e];
-                    *(f32x4*)(P + js + 32 * b + 8 * i4 + 4 * ehh) = o;
+                    if (!XA || js + 32 * b + 8 * i4 < d) *(f32x4*)(P + js + 32 * b + 8 * i4 + 4 * ehh) = o;
                 }
         }
     }
@@ -620,9 +662,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                     const int j = js + 32 * b + 8 * i4 + 4 * ehh;
                     // unconditional loads (the row pointers are clamped to row 0), masked
                     // afterwards: no control flow inside the sweep
-                    const u16x4 hv = *(const u16x4*)(hrow[h] + j);
-                    const u16x4 wv = *(const u16x4*)(wrow + j);
-                    const u16x4 gv = *(const u16x4*)(gk + j);
+                    const int jc = XA && j >= d ? 0 : j;
+                    const u16x4 hv = *(const u16x4*)(hrow[h] + jc);
+                    const u16x4 wv = *(const u16x4*)(wrow + jc);
+                    const u16x4 gv = *(const u16x4*)(gk + jc);
+                    if (XA && j >= d) {  // (columns past the width hold the streamed rows' zeros, and add none)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[b][h][4 * i4 + e] = 0.f;
+                        continue;
+                    }
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float wy = tok[h] ? bf16_bits_to_f32(wv[e]) : 0.f;
@@ -655,8 +703,23 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             const float cmean = tau_k * csum / (float)d;
             if (a.rowdtau && w == 0 && ehh == 0 && xok[h]) a.rowdtau[modoff + xg] = tok[h] ? csum : 0.f;
             if (a.ebuf) {
-                // e to the buffer as bf16 planes hi | lo; the RMSNorm backward follows
-                // the rotation back
+                // e to the buffer as bf16 planes hi | lo (XA: in fp32); the RMSNorm backward
+                // follows the rotation back
+                if (XA) {
+                    if (!xok[h]) continue;
+                    float* er = (float*)a.ebuf + (modoff + xg) * (long long)d;
+#pragma unroll
+                    for (int b = 0; b < (PC ? G::NB : 1); ++b)
+#pragma unroll
+                        for (int i4 = 0; i4 < 4; ++i4) {
+                            const int j = js + 32 * b + 8 * i4 + 4 * ehh;
+                            f32x4 o;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) o[e] = acc[b][h][4 * i4 + e];
+                            if (j < d) *(f32x4*)(er + j) = o;
+                        }
+                    continue;
+                }
                 if (xok[h]) {
                     bf16* er = (bf16*)a.ebuf + (modoff + xg) * (long long)(2 * d);
 #pragma unroll
@@ -682,8 +745,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
 #pragma unroll
                 for (int i4 = 0; i4 < 4; ++i4) {
                     const int j = js + 32 * b + 8 * i4 + 4 * ehh;
-                    const u16x4 hv = *(const u16x4*)(hrow[h] + j);  // row 0 for rows past the end
-                    const u16x4 gv = *(const u16x4*)(gk + j);
+                    const int jc = XA && j >= d ? 0 : j;
+                    const u16x4 hv = *(const u16x4*)(hrow[h] + jc);  // row 0 for rows past the end
+                    const u16x4 gv = *(const u16x4*)(gk + jc);
                     bf16x4 o;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
@@ -701,7 +765,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                 const i32x4 v = *(LDS_AS i32x4*)((row < 16 ? sliceA : sliceB) + (row & 15) * (2 * DS) +
                                                  16 * (g ^ (row & SM)));
                 const int xr = x0 + 32 * h + row;
-                if (xr < nX) *(i32x4*)((bf16*)a.dh + (modoff + xr) * (long long)d + js + 8 * g) = v;
+                if (xr < nX && (!XA || js + 8 * g < d)) *(i32x4*)((bf16*)a.dh + (modoff + xr) * (long long)d + js + 8 * g) = v;
             }
         }
         // sweep 3, for a module that trains its gain: the tile's partial sums
@@ -716,14 +780,14 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                     f32x4 pv = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int h = 0; h < NR; ++h) {
-                        const u16x4 hv = *(const u16x4*)(hrow[h] + j);  // rx = 0 masks rows past the end
+                        const u16x4 hv = *(const u16x4*)(hrow[h] + (XA && j >= d ? 0 : j));  // rx = 0 masks rows past the end
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float t = row16_sum(tau_k * acc[b][h][4 * i4 + e] * (rx[h] * bf16_bits_to_f32(hv[e])));
                             pv[e] += t + __shfl_xor(t, 16, 64);
                         }
                     }
-                    if (ex == 0) *(f32x4*)(dgp + j) = pv;
+                    if (ex == 0 && (!XA || j < d)) *(f32x4*)(dgp + j) = pv;
                 }
             }
         }
@@ -753,7 +817,13 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                     f32x4 o;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = acc[b][h][4 * i4 + e];
-                    if (vok) *(f32x4*)(dwrow + j) = o;
+                    if (XA) {
+                        // the streamed rows were the raw h: the gain joins here
+                        const u16x4 gv = *(const u16x4*)(gk + (j < d ? j : 0));
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] *= bf16_bits_to_f32(gv[e]);
+                    }
+                    if (vok && (!XA || j < d)) *(f32x4*)(dwrow + j) = o;
                 }
             }
         }
@@ -778,6 +848,34 @@ hipError_t launch_ds(const FusedArgs& a, int nmod, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int MODE, int DS, bool EXT>
+hipError_t launch_exact_ds(const FusedArgs& a, int nmod, hipStream_t s) {
+    constexpr int XR = rows_of<DS, true, true>();
+    const dim3 grid((unsigned)(((MODE == LOCAL ? a.T : a.V) + XR - 1) / XR), (unsigned)nmod,
+                    MODE == LOCAL ? (unsigned)a.nsplit : 1u);
+    if constexpr (MODE == LOCAL) {
+        if (a.nsplit > 1) {
+            hipLaunchKernelGGL((k_fused<MODE, DS, EXT, true, true>), grid, dim3(NTHR), 0, s, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_fused<MODE, DS, EXT, false, true>), grid, dim3(NTHR), 0, s, a);
+    return hipGetLastError();
+}
+
+template <int MODE, bool EXT>
+hipError_t launch_exact(const FusedArgs& a, int nmod, hipStream_t s) {
+    switch ((a.d + NW * 32 - 1) / (NW * 32)) {
+        case 1: return launch_exact_ds<MODE, 32, EXT>(a, nmod, s);
+        case 2: return launch_exact_ds<MODE, 64, EXT>(a, nmod, s);
+        case 3: return launch_exact_ds<MODE, 96, EXT>(a, nmod, s);
+        case 4: return launch_exact_ds<MODE, 128, EXT>(a, nmod, s);
+        case 5: return launch_exact_ds<MODE, 160, EXT>(a, nmod, s);
+        case 6: return launch_exact_ds<MODE, 192, EXT>(a, nmod, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 template <int MODE, bool EXT>
 hipError_t launch_mode(const FusedArgs& a, int nmod, hipStream_t s) {
     switch (a.d / NW) {
@@ -800,6 +898,20 @@ bool mfma_supported(int dtype, int d) { return dtype == 0 && d % (NW * 32) == 0 
 int mfma_eval_rows(int d) { return d <= NW * 128 ? rows_of<128, false>() : rows_of<256, false>(); }
 
 int mfma_rows(int d) { return d <= NW * 128 ? rows_of<128, true>() : rows_of<256, true>(); }
+
+// From d = 72 to 1536: up to 64 the fp32 kernels' narrow column slices are as fast or
+// faster (2 x 256 x 512 at d = 64: 45 us against 66; 4 x 8192 x 32000: 4.3 ms
+// against 3.9), and past 1536 two planes of 32 rows do not fit the registers
+// next to the accumulator.  At 4 x 8192 x 32000 tokens, against the fp32 kernels: d =
+// 640 7.6 ms against 35.8, d = 104 3.9 against 7.7 (fp32 storage).
+bool exact_supported(int dtype, int d) { return dtype == 0 && d > 64 && d <= NW * 192; }
+int exact_rows(int d) { return d <= NW * 96 ? rows_of<96, true, true>() : rows_of<128, true, true>(); }
+hipError_t launch_local_loss_exact(const FusedArgs& a, bool ext, int nmod, hipStream_t s) {
+    return ext ? launch_exact<LOCAL, true>(a, nmod, s) : launch_exact<LOCAL, false>(a, nmod, s);
+}
+hipError_t launch_readout_grad_exact(const FusedArgs& a, int nmod, hipStream_t s) {
+    return launch_exact<RGRAD, false>(a, nmod, s);
+}
 
 hipError_t launch_local_loss_mfma(const FusedArgs& a, bool ext, int nmod, hipStream_t s) {
     return ext ? launch_mode<LOCAL, true>(a, nmod, s) : launch_mode<LOCAL, false>(a, nmod, s);

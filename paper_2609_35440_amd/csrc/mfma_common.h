@@ -176,9 +176,14 @@ struct ChunkStream {
     using G = layout::Geo<DS>;
     int voff[G::NV];
 
+    // CUT: columns at or past d read as zeros (an offset past any chunk's range)
+    template <bool CUT = false>
     __device__ __forceinline__ void init(int d, int js, int lane) {
 #pragma unroll
-        for (int v = 0; v < G::NV; ++v) voff[v] = layout::stream_voff<DS>(v, d, js, lane);
+        for (int v = 0; v < G::NV; ++v) {
+            voff[v] = layout::stream_voff<DS>(v, d, js, lane);
+            if (CUT && layout::stream_voff<DS>(v, 0, js, lane) >= 2 * d) voff[v] = 0x40000000;
+        }
     }
 
     // buffer resource of the chunk starting at row y0; rows at or beyond nY

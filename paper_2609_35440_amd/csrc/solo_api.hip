@@ -26,6 +26,7 @@ bool flag_ok(int f) { return f == 0 || f == 1; }
 // What one call launches, and where its workspace pieces sit.
 struct Plan {
     bool mfma = false;         // matrix-core family (either tiling)
+    bool exact = false;        // fp32 family, bf16 storage: local loss and readout gradient in the exact form (k_mfma.hip)
     bool wide = false;         // the 16-row wide tiling of the matrix-core family (d = 2560)
     bool eval = false;
     bool ext = false;          // local-loss variant with per-chunk biases
@@ -64,6 +65,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     const int K = a.K, T = a.T, d = a.d;
     P->wide = solo::mfma_wide_supported(a.dtype, d);
     P->mfma = solo::mfma_supported(a.dtype, d) || P->wide;
+    P->exact = !P->mfma && solo::exact_supported(a.dtype, d);
     P->eval = eval;
     const size_t kt = (size_t)K * T;
     size_t off = 0;
@@ -83,7 +85,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
         P->whtile = off;
         off = align_up(off + tv * P->nhead_tiles);
     }
-    const int rows = P->wide ? solo::kMfmaWideRows : (P->mfma ? solo::mfma_rows(d) : solo::f32_rows(d));
+    const int rows = P->wide ? solo::kMfmaWideRows : (P->mfma ? solo::mfma_rows(d) : (P->exact ? solo::exact_rows(d) : solo::f32_rows(d)));
     P->rows = rows;
     P->ntiles = (T + rows - 1) / rows;
     P->rot = a.rot != nullptr && K > 1;
@@ -187,8 +189,9 @@ int best_split(long long tiles, long long nch, const SplitCost& c, double max_s,
 // 2048 and 64 x 1024), of which about 0.5 us is the exchange and its barriers.
 int local_splits(const Plan& P, int n, int K, int T, int d, int V, size_t room) {
     const double td = (double)P.rows * d;
-    const SplitCost c = {P.mfma ? 0.5 + 0.65 * td / 65536.0 : 4.0 * td / 1.6e3, 6.0, (double)n * T * d * 8.0 / 3e6};
-    const int yc = P.mfma ? 16 : 256;
+    const bool fused = P.mfma || P.exact;
+    const SplitCost c = {fused ? 0.5 + 0.65 * td / 65536.0 : 4.0 * td / 1.6e3, 6.0, (double)n * T * d * 8.0 / 3e6};
+    const int yc = fused ? 16 : 256;
     return best_split((long long)P.ntiles * n, ((long long)V + yc - 1) / yc, c, (double)room / ((double)K * T * (d + 4)));
 }
 
@@ -418,16 +421,19 @@ int run(const solo_readout_args& x, bool eval) {
                        : P.mfma ? solo::launch_exit_eval_mfma(b, n, s)
                                 : solo::launch_exit_eval_f32(dt, b, n, s);
             case 1: {
-                const hipError_t e = P.wide   ? solo::launch_local_loss_mfma_wide(b, P.ext, n, s)
-                                     : P.mfma ? solo::launch_local_loss_mfma(b, P.ext, n, s)
-                                              : solo::launch_local_loss_f32(dt, b, n, s);
+                const hipError_t e = P.wide    ? solo::launch_local_loss_mfma_wide(b, P.ext, n, s)
+                                     : P.mfma  ? solo::launch_local_loss_mfma(b, P.ext, n, s)
+                                     : P.exact ? solo::launch_local_loss_exact(b, P.ext, n, s)
+                                               : solo::launch_local_loss_f32(dt, b, n, s);
                 if (e != hipSuccess || b.nsplit == 1) return e;
-                return solo::launch_merge(dt, !P.mfma, b, n, P.rows, s);
+                return solo::launch_merge(dt, P.mfma ? solo::MERGE_BF16 : (P.exact ? solo::MERGE_EXACT : solo::MERGE_F32),
+                                          b, n, P.rows, s);
             }
             case 2:
-                return P.wide   ? solo::launch_readout_grad_mfma_wide(b, n, s)
-                       : P.mfma ? solo::launch_readout_grad_mfma(b, n, s)
-                                : solo::launch_readout_grad_f32(dt, b, n, s);
+                return P.wide    ? solo::launch_readout_grad_mfma_wide(b, n, s)
+                       : P.mfma  ? solo::launch_readout_grad_mfma(b, n, s)
+                       : P.exact ? solo::launch_readout_grad_exact(b, n, s)
+                                 : solo::launch_readout_grad_f32(dt, b, n, s);
             default:
                 return P.wide   ? solo::launch_bias_grad_mfma_wide(b, n, s)
                        : P.mfma ? solo::launch_bias_grad_mfma(b, n, s)

@@ -106,6 +106,11 @@ hipError_t launch_local_loss_mfma(const FusedArgs& a, bool ext, int nmod, hipStr
 hipError_t launch_exit_eval_mfma(const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_readout_grad_mfma(const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_bias_grad_mfma(const FusedArgs& a, int nmod, hipStream_t s);
+// the local-loss and readout-gradient passes of bf16 storage with products exact to fp32 (k_mfma.hip)
+bool exact_supported(int dtype, int d);
+int exact_rows(int d);
+hipError_t launch_local_loss_exact(const FusedArgs& a, bool ext, int nmod, hipStream_t s);
+hipError_t launch_readout_grad_exact(const FusedArgs& a, int nmod, hipStream_t s);
 // forward-only passes as a tiled product (k_logits.hip): d % 256 == 0
 struct LogitsArgs {
     const bf16* X;          // [nX][d] stationary rows; module m of a launch x_stride elements further,
@@ -145,7 +150,9 @@ hipError_t launch_local_loss_f32(int dtype, const FusedArgs& a, int nmod, hipStr
 hipError_t launch_exit_eval_f32(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
 // the tokens' ends of a local-loss pass split over the vocabulary, modules m0 .. m0 + nmod - 1, gain partials
 // per tile of rows tokens (k_merge.hip)
-hipError_t launch_merge(int dtype, bool f32fam, const FusedArgs& a, int nmod, int rows, hipStream_t s);
+// (form: what the form's gradient passes read, see k_merge)
+enum MergeForm { MERGE_BF16 = 0, MERGE_F32 = 1, MERGE_EXACT = 2 };
+hipError_t launch_merge(int dtype, MergeForm form, const FusedArgs& a, int nmod, int rows, hipStream_t s);
 constexpr int kMaxSplit = 64;  // splits of one row tile (a lane of the merge each)
 hipError_t launch_merge_eval(const FusedArgs& a, long long rows, hipStream_t s);
 // ROT (k_rot.hip): C = A B^T per matrix; transposes; a vector of ones; the

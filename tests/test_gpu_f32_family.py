@@ -23,7 +23,8 @@ CASES = [("tiny", 1, 1, 8, 1), ("tiny", 2, 33, 24, 257), ("tiny", 1, 31, 32, 256
          ("tiny", 1, 33, 2048, 300), ("tiny", 1, 17, 2056, 300), ("tiny", 1, 18, 3080, 260), ("tiny", 1, 17, 4096, 260),
          ("tiny", 2, 5, 64, 9000), ("tiny", 3, 70, 208, 5000),
          ("1b", 1, 33, 8, 257), ("1b", 2, 40, 72, 513), ("1b", 1, 31, 128, 256), ("1b", 2, 37, 640, 2000),
-         ("1b", 1, 33, 1160, 300), ("1b", 1, 18, 2304, 300), ("1b", 1, 17, 3072, 600), ("1b", 2, 19, 4088, 520)]
+         ("1b", 2, 65, 200, 1030), ("1b", 1, 33, 904, 300), ("1b", 1, 33, 1160, 300), ("1b", 2, 34, 1528, 500), ("1b", 1, 33, 1800, 300),
+         ("1b", 1, 18, 2304, 300), ("1b", 1, 17, 3072, 600), ("1b", 2, 19, 4088, 520)]
 
 
 @pytest.mark.parametrize("final", [True, False], ids=["dW", "frozen"])
