@@ -316,7 +316,9 @@ int solo_readout_general(const solo_readout_args* args);
 
 /* Workspace bytes of solo_readout_exit_eval: per-token statistics (K T
  * floats each), the tiled readout copies of the matrix-core families (V d
- * terms, as for the general entry point) and, with rot, the rotated rows. */
+ * terms, as for the general entry point) or, for the other bf16 widths, copies
+ * of up to 16384 rows (4 d bytes each) and at most 32 MiB of partial
+ * statistics, and, with rot, the rotated rows. */
 size_t solo_readout_exit_eval_workspace_size(const solo_readout_args* args);
 
 /* Forward-only exit evaluation: losses, row_loss and top1 of every module. */

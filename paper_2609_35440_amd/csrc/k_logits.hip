@@ -28,7 +28,7 @@
 //
 // Measured (4 x 16384 rows, d = 2048, V = 32000): exit evaluation 7.35 ms, 1.2
 // PFLOP/s in the product, against 8.4 ms of the fused pass; at d = 256 (4 x 8192) 0.67
-// against 1.79.
+// against 1.79.  On two planes (4 x 8192 x 32000, d = 640): 2.3 ms, 115 on the vector ALU.
 #include "mfma_common.h"
 
 namespace solo {
@@ -61,7 +61,11 @@ __device__ __forceinline__ void buffer_load_lds16s(i32x4 rsrc, unsigned lds_base
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-template <int MODE, bool EXT>
+// XA: logits exact to fp32, for the bf16 widths whose calls are defined in fp32:
+// one operand is the copy of g * h (16 significant bits) as two bf16 planes side by side,
+// rows of 2 dp elements (dp = d rounded up to 64, zeros past d), and the readout
+// is read once per plane; its columns past d read as zeros.
+template <int MODE, bool EXT, bool XA>
 __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     __shared__ __attribute__((aligned(16))) char sA0[STAGE];
     __shared__ __attribute__((aligned(16))) char sA1[STAGE];
@@ -86,7 +90,12 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     const int x0 = xt * BT;
     const int nt = (a.nY + BT - 1) / BT;
     const int t_lo = (int)((long long)nt * sp / S), t_hi = (int)((long long)nt * (sp + 1) / S);
-    const int nk = d / BK;  // a multiple of 4 (d % 256 == 0)
+    // stages per tile: an even number (d % 256 == 0, or two planes)
+    const int nkd = (d + BK - 1) / BK;
+    const int nk = XA ? 2 * nkd : nkd;
+    // row pitches: the copy of g * h is X in exit evaluation, Y in the bias gradient
+    const int cp = 2 * nkd * BK;
+    const int dX = XA && MODE == EVAL ? cp : d, dY = XA && MODE == BGRAD ? cp : d;
 
     LDS_AS char* const pA0 = (LDS_AS char*)(LDS_AS void*)sA0;
     LDS_AS char* const pA1 = (LDS_AS char*)(LDS_AS void*)sA1;
@@ -94,25 +103,33 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     LDS_AS char* const pB1 = (LDS_AS char*)(LDS_AS void*)sB1;
 
     // ---- stream: instruction i of wave w fills rows 32 w + 8 i .. + 7 of a stage
-    int vo[4];
+    const int gr = (lane & 7) ^ (lane >> 3);  // the lane's granule of a row
+    int voA[4], voB[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        vo[i] = (32 * w + 8 * i + (lane >> 3)) * d * 2 + 16 * ((lane & 7) ^ (lane >> 3));
-    auto rows_rsrc = [&](const bf16* __restrict__ P, int n, int r0) __attribute__((always_inline)) {
+    for (int i = 0; i < 4; ++i) {
+        voA[i] = (32 * w + 8 * i + (lane >> 3)) * dY * 2 + 16 * gr;
+        voB[i] = XA ? (32 * w + 8 * i + (lane >> 3)) * dX * 2 + 16 * gr : voA[i];
+    }
+    auto rows_rsrc = [&](const bf16* __restrict__ P, int n, int r0, int pitch) __attribute__((always_inline)) {
         const int rows = n - r0 < BT ? n - r0 : BT;
-        return make_rsrc(P + (long long)r0 * d, (unsigned)rows * (unsigned)d * 2u);
+        return make_rsrc(P + (long long)r0 * pitch, (unsigned)rows * (unsigned)pitch * 2u);
     };
-    const i32x4 brs = rows_rsrc(X, a.nX, x0);
+    const i32x4 brs = rows_rsrc(X, a.nX, x0, dX);
     const unsigned uA[2] = {lds_addr(pA0) + w * 4096, lds_addr(pA1) + w * 4096};
     const unsigned uB[2] = {lds_addr(pB0) + w * 4096, lds_addr(pB1) + w * 4096};
     int it = t_lo, ik = 0;  // the next stage to stream
-    i32x4 ars = rows_rsrc(Y, a.nY, t_lo * BT);
+    i32x4 ars = rows_rsrc(Y, a.nY, t_lo * BT, dY);
     auto issue = [&](int buf) __attribute__((always_inline)) {
         if (it >= t_hi) return;
+        // XA: the readout's k of this stage, and whether the lane's granule of it is past d
+        const int kr = XA && ik >= nkd ? ik - nkd : ik;
+        const bool past = XA && kr * BK + 8 * gr >= d;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            buffer_load_lds16s(ars, uA[buf] + i * 1024, vo[i], ik * (BK * 2));
-            buffer_load_lds16s(brs, uB[buf] + i * 1024, vo[i], ik * (BK * 2));
+            buffer_load_lds16s(ars, uA[buf] + i * 1024, MODE == EVAL && past ? 0x40000000 : voA[i],
+                               (MODE == EVAL ? kr : ik) * (BK * 2));
+            buffer_load_lds16s(brs, uB[buf] + i * 1024, MODE == BGRAD && past ? 0x40000000 : voB[i],
+                               (MODE == EVAL ? ik : kr) * (BK * 2));
         }
         if (ik == 1) {
             // the tile's side data, long before its end: every wave has left the
@@ -129,7 +146,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
         if (++ik == nk) {
             ik = 0;
             ++it;
-            if (it < t_hi) ars = rows_rsrc(Y, a.nY, it * BT);
+            if (it < t_hi) ars = rows_rsrc(Y, a.nY, it * BT, dY);
         }
     };
 
@@ -398,10 +415,10 @@ __global__ void k_db_sum(const float* __restrict__ parts, float* __restrict__ ou
     out[i] = (s + out[i]) * inv_T;
 }
 
-template <int MODE, bool EXT>
+template <int MODE, bool EXT, bool XA>
 hipError_t launch_t(const LogitsArgs& a, int nmod, hipStream_t s) {
     const int tiles = (a.nX + BT - 1) / BT;
-    hipLaunchKernelGGL((k_logits<MODE, EXT>), dim3((unsigned)(((long long)tiles * a.nsplit + 7) / 8 * 8), (unsigned)nmod),
+    hipLaunchKernelGGL((k_logits<MODE, EXT, XA>), dim3((unsigned)(((long long)tiles * a.nsplit + 7) / 8 * 8), (unsigned)nmod),
                        dim3(NTHR), 0, s, a);
     return hipGetLastError();
 }
@@ -409,11 +426,12 @@ hipError_t launch_t(const LogitsArgs& a, int nmod, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_logits_eval(const LogitsArgs& a, hipStream_t s) {
-    return a.bias ? launch_t<EVAL, true>(a, 1, s) : launch_t<EVAL, false>(a, 1, s);
+    if (a.exact) return a.bias ? launch_t<EVAL, true, true>(a, 1, s) : launch_t<EVAL, false, true>(a, 1, s);
+    return a.bias ? launch_t<EVAL, true, false>(a, 1, s) : launch_t<EVAL, false, false>(a, 1, s);
 }
 
 hipError_t launch_logits_bgrad(const LogitsArgs& a, int nmod, hipStream_t s) {
-    hipError_t e = launch_t<BGRAD, false>(a, nmod, s);
+    hipError_t e = a.exact ? launch_t<BGRAD, false, true>(a, nmod, s) : launch_t<BGRAD, false, false>(a, nmod, s);
     if (e != hipSuccess || a.nsplit == 1) return e;
     const long long n = (long long)nmod * a.nX;
     hipLaunchKernelGGL(k_db_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.parts, a.out, n, a.nsplit,

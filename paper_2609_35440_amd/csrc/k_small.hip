@@ -92,6 +92,33 @@ __global__ void k_gain_rows(const bf16* __restrict__ h, long long src_stride, co
     }
 }
 
+// g * h (16 significant bits) as two bf16 planes side by side, rows of
+// plane_pitch(d) elements; 8 elements of a row per thread (d % 8 == 0)
+__global__ void k_gain_planes(const bf16* __restrict__ h, const bf16* __restrict__ gain, bf16* __restrict__ out,
+                              long long rows, int d) {
+    typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+    const int half = plane_pitch(d) / 2;
+    const int j = 8 * (blockIdx.y * blockDim.x + threadIdx.x);
+    if (j >= half) return;
+    for (long long r = blockIdx.x; r < rows; r += gridDim.x) {
+        bf16x8 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) hi[e] = lo[e] = (bf16)0.f;
+        if (j < d) {
+            const bf16x8 hv = *(const bf16x8*)(h + r * d + j);
+            const bf16x8 gv = *(const bf16x8*)(gain + j);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float p = (float)hv[e] * (float)gv[e];
+                hi[e] = (bf16)p;
+                lo[e] = (bf16)(p - (float)hi[e]);
+            }
+        }
+        *(bf16x8*)(out + r * (2LL * half) + j) = hi;
+        *(bf16x8*)(out + r * (2LL * half) + half + j) = lo;
+    }
+}
+
 // out[k] = scale * sum_t rows[k][t], fixed order, fp64 accumulation
 // (module losses: the per-token losses with scale 1/T; temperature gradients:
 // the per-token shares with scale 1).
@@ -162,6 +189,13 @@ hipError_t launch_gain_rows(const bf16* h, long long src_stride, const bf16* gai
     if (blocks > 4096) blocks = 4096;
     hipLaunchKernelGGL(k_gain_rows, dim3((unsigned)blocks, (unsigned)nmat), dim3(256), 0, s, h, src_stride, gain,
                        g_stride, hg, dst_stride, per_mod, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_gain_planes(const bf16* h, const bf16* gain, bf16* out, long long rows, int d, hipStream_t s) {
+    const unsigned parts = (unsigned)((plane_pitch(d) / 16 + 63) / 64);
+    const unsigned blocks = (unsigned)(rows < 8192 ? rows : 8192);
+    hipLaunchKernelGGL(k_gain_planes, dim3(blocks, parts), dim3(64), 0, s, h, gain, out, rows, d);
     return hipGetLastError();
 }
 

@@ -27,6 +27,8 @@ bool flag_ok(int f) { return f == 0 || f == 1; }
 struct Plan {
     bool mfma = false;         // matrix-core family (either tiling)
     bool exact = false;        // fp32 family, bf16 storage: local loss and readout gradient in the exact form (k_mfma.hip)
+    bool planes = false;       // fp32 family, bf16 storage: forward-only products on plane copies (k_logits.hip)
+    size_t eval_room = 0;      // bytes at wtile that the forms of exit evaluation without tiled copies may use
     bool wide = false;         // the 16-row wide tiling of the matrix-core family (d = 2560)
     bool eval = false;
     bool ext = false;          // local-loss variant with per-chunk biases
@@ -75,10 +77,22 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     off = align_up(off + kt * 4);
     P->rowloss = off;
     off = align_up(off + kt * 4);
+    // bf16 storage in fp32: the product form of exit evaluation (plane copies of the
+    // rows, up to 16384 at a time, and the parts of its splits)
+    P->planes = !P->mfma && a.dtype == SOLO_BF16;
+    if (P->planes && eval) {
+        const size_t nvt = ((size_t)a.V + 255) / 256;
+        const size_t parts = kt * 32 * (nvt < solo::kMaxSplit ? nvt : solo::kMaxSplit);
+        P->eval_room = (kt < 16384 ? kt : 16384) * solo::plane_pitch(d) * 2 + 512 +
+                       (parts < (size_t(32) << 20) ? parts : (size_t(32) << 20));
+        P->wtile = off;
+        off = align_up(off + P->eval_room);
+    }
     // tiled copies of the readouts the local-loss pass and exit evaluation
     // stream: the terminal's W, and the heads' own matrix or matrices
     if (tiled_readout(*P)) {
         const size_t tv = (size_t)solo::tiled_elems(a.V, d) * 2;
+        P->eval_room = tv;
         P->nhead_tiles = (a.Wbar && K > 1) ? (a.readout_per_head ? K - 1 : 1) : 0;
         P->wtile = off;
         off = align_up(off + tv);
@@ -215,7 +229,7 @@ struct EvalPlan {
     long long pass_rows = 0;
 };
 
-double prod_tile_us(int d) { return 4.0 + 0.027 * d; }
+double prod_tile_us(int d, bool planes) { return 4.0 + (planes ? 0.054 : 0.027) * d; }
 double eval_chunk_us(int rows, int d) { return 0.2 + 0.0055 * rows + 0.45 * (double)rows * d / 131072.0; }
 
 EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
@@ -227,22 +241,26 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
     const double chunk = eval_chunk_us(rows, d);
     double best = (double)((tiles + 255) / 256) * (double)nch * chunk +
                   (1 + P.nhead_tiles) * (4.0 + 4.0 * (double)V * d / 4e6);
+    // (the fp32 kernels' pass: 32 rows against chunks of 256)
+    if (P.planes)
+        best = (double)(((long long)K * ((T + 31) / 32) + 255) / 256) * (double)((V + 255) / 256) * (2.0 + 0.08 * d);
     const double kt = (double)K * T;
-    const double room = (double)solo::tiled_elems(V, d) * 2.0;
+    const double room = (double)P.eval_room;
+    const double row_bytes = P.planes ? 2.0 * solo::plane_pitch(d) : 2.0 * d;
     double us = 0.0;
     // (row-major, a chunk's operand loads take 16 rows of 64 bytes each: 1.75 us at d = 2048)
     const SplitCost c = {1.05 * chunk > 0.00085 * d ? 1.05 * chunk : 0.00085 * d, 10.0, kt * 64.0 / 3e6};
     const int s = best_split(stiles, nch, c, room / (kt * 32.0), &us);
-    if (s > 1 && us < best) {
+    if (!P.planes && s > 1 && us < best) {
         E.form = EvalPlan::SPLIT;
         E.nsplit = s;
         best = us;
     }
     const long long lists = flat ? 1 : K, n = flat ? (long long)K * T : T;  // rows are one list, or one per module
     const long long nvt = ((long long)V + 255) / 256;
-    for (int sp = 1; sp <= 32 && sp <= nvt; ++sp) {
-        const double cap = (room - 512.0 - (sp > 1 ? kt * 32.0 * sp : 0.0)) / (2.0 * d);
-        if (cap < 256.0) break;
+    for (int sp = 1; sp <= solo::kMaxSplit && sp <= nvt; ++sp) {
+        const double cap = (room - 512.0 - (sp > 1 ? kt * 32.0 * sp : 0.0)) / row_bytes;
+        if (cap < (n < 256 ? (double)n : 256.0)) break;
         const long long np0 = (long long)((double)n / cap) + 1;
         for (long long np = np0; np < np0 + 4; ++np) {
             const long long pr = ((n + np - 1) / np + 255) / 256 * 256;
@@ -250,7 +268,7 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
             const long long whole = n / pr, rest = n - whole * pr;
             auto rounds = [&](long long r) { return (double)(((r + 255) / 256 * sp + 255) / 256); };
             const double t = (double)lists * ((whole * rounds(pr) + (rest ? rounds(rest) : 0.0)) *
-                                                  (double)((nvt + sp - 1) / sp) * prod_tile_us(d) +
+                                                  (double)((nvt + sp - 1) / sp) * prod_tile_us(d, P.planes) +
                                               (double)(whole + (rest > 0)) * 8.0) +
                              10.0 + kt * d * 4.0 / 4e6 + (sp > 1 ? 5.0 + kt * 64.0 * sp / 3e6 : 0.0);
             if (t < best) {
@@ -274,7 +292,7 @@ int prod_bgrad_splits(const Plan& P, int n, int K, int T, int d, int V) {
     const int rows = P.wide ? solo::kMfmaWideEvalRows : solo::mfma_eval_rows(d);
     const double chunk = 1.2 * eval_chunk_us(rows, d);
     const double fused = (double)(((((long long)V + rows - 1) / rows) * n + 255) / 256) * (double)((T + 15) / 16) * chunk;
-    const SplitCost c = {prod_tile_us(d), 4.0, (double)n * V * 8.0 / 3e6};
+    const SplitCost c = {prod_tile_us(d, false), 4.0, (double)n * V * 8.0 / 3e6};
     double us = 0.0;
     const int s = best_split((((long long)V + 255) / 256) * n, ((long long)T + 255) / 256, c,
                              1.0 + 3.0 * K * T / ((double)n * V), &us);
@@ -374,8 +392,8 @@ int run(const solo_readout_args& x, bool eval) {
     if (solo::launch_row_rstd(dt, x.h, (float*)(ws + P.rstd), (long long)K * T, d, x.eps, s) != hipSuccess)
         return SOLO_ERR_HIP;
     // exit evaluation of few rows: split over the vocabulary, no tiled copies
-    const bool flat = eval && P.mfma && !P.rot && !x.bias && !P.nhead_tiles;
-    const EvalPlan E = eval && P.mfma ? plan_eval(P, K, T, d, V, flat) : EvalPlan();
+    const bool flat = eval && !P.rot && !x.bias && !(x.Wbar && K > 1);
+    const EvalPlan E = eval && (P.mfma || P.planes) ? plan_eval(P, K, T, d, V, flat) : EvalPlan();
     a.split_stat = (float*)(ws + P.wtile);
     if (E.form == EvalPlan::SPLIT) {
         a.nsplit = E.nsplit;
@@ -456,6 +474,7 @@ int run(const solo_readout_args& x, bool eval) {
             l.Y = (const solo::bf16*)(flat || k == K - 1 ? a.Wt : (const void*)((const solo::bf16*)a.Wh + k * a.wh_stride));
             l.nY = V;
             l.d = d;
+            l.exact = P.planes;
             l.x_last = -1;
             l.nsplit = E.nsplit;
             l.parts = a.split_stat;
@@ -476,9 +495,11 @@ int run(const solo_readout_args& x, bool eval) {
                     const long long m = (l.row0 + r) / T;
                     const long long end = g.g_stride ? (m + 1) * T - l.row0 : nr;
                     const long long cnt = (end < nr ? end : nr) - r;
-                    if (solo::launch_gain_rows((const solo::bf16*)g.h + (l.row0 + r) * d, 0,
-                                               (const solo::bf16*)g.gain + m * g.g_stride, 0, copy + r * d, 0, 1, (int)cnt,
-                                               d, s) != hipSuccess)
+                    const solo::bf16* const src = (const solo::bf16*)g.h + (l.row0 + r) * d;
+                    const solo::bf16* const gn = (const solo::bf16*)g.gain + m * g.g_stride;
+                    if ((P.planes ? solo::launch_gain_planes(src, gn, copy + r * solo::plane_pitch(d), cnt, d, s)
+                                  : solo::launch_gain_rows(src, 0, gn, 0, copy + r * d, 0, 1, (int)cnt, d, s)) !=
+                        hipSuccess)
                         return false;
                     r += cnt;
                 }

@@ -120,6 +120,7 @@ struct LogitsArgs {
     const bf16* Y;          // [nY][d] streamed rows, module m y_stride further
     long long y_stride;
     int nX, nY, d;
+    int exact;              // 1: the copy of g * h is two bf16 planes (rows of plane_pitch(d) elements)
     int nsplit;             // workgroups the streamed tiles of a row tile are split over
     float* parts;           // nsplit > 1: exit evaluation [nsplit][part_rows][8] as FusedArgs::split_stat, at the
                             // global row; bias gradient [nsplit - 1][nmod][nX] sums
@@ -137,6 +138,9 @@ struct LogitsArgs {
     float* out;             // [nmod][nX]
     float inv_T;
 };
+__host__ __device__ inline int plane_pitch(int d) { return 2 * ((d + 63) / 64 * 64); }
+// copies of g * h as two planes: hi = bf16(g h) at [0, pitch / 2), lo = bf16(g h - hi) at [pitch / 2, pitch), zeros past d
+hipError_t launch_gain_planes(const bf16* h, const bf16* gain, bf16* out, long long rows, int d, hipStream_t s);
 hipError_t launch_logits_eval(const LogitsArgs& a, hipStream_t s);
 hipError_t launch_logits_bgrad(const LogitsArgs& a, int nmod, hipStream_t s);
 // the wide matrix-core kernels (k_mfma_wide.hip): d = 2560

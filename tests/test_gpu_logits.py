@@ -87,3 +87,28 @@ def test_bias_gradient(T, V, extras, final):
     compare(g, ref, "bf16", flags, f"product bias gradient {T} {V}")
     for k in range(3):
         assert rel_max_err(g["dbias"][k], ref["dbias"][k]) <= 2e-2
+
+
+# bf16 widths defined in fp32: the product on two planes of g * h
+PLANES = [("plain", 2, 300, 72, 1025, dict()), ("one-list", 3, 9, 640, 5000, dict(per_module_gain=True, tau=True)),
+          ("bias", 2, 257, 1000, 700, dict(bias=True)), ("per-head", 2, 130, 136, 600, dict(wbar="per_head")),
+          ("wide", 1, 33, 3080, 513, dict()), ("widest", 2, 5, 4096, 300, dict(tau=True)), ("narrow", 1, 700, 8, 257, dict())]
+
+
+@pytest.mark.parametrize("name,K,T,d,V,extras", PLANES, ids=[c[0] for c in PLANES])
+def test_eval_planes(name, K, T, d, V, extras):
+    from tests.gpu_helpers import row_loss_error_bound
+
+    x = make_extras(make_inputs("1b", seed=14, K=K, T=T, d=d, V=V), seed=14, **extras)
+    losses, row_loss, top1 = run_exit_eval(x)
+    check_exit_eval(x, losses, row_loss, top1, f"planes {name}", min_rows_for_agreement=100)
+    # fp32 logits: within the bound of fp32 operands and sums
+    ref = oracle.exit_eval(x["h"], x["gain"], x["W"], x["targets"], Wbar=x.get("Wbar"), tau=x.get("tau"),
+                           bias=x.get("bias"))
+    for k in range(K):
+        R = oracle.solo_oracle_general.readout_matrix(k, K, x["W"], x.get("Wbar"))
+        gk = x["gain"][k] if x["gain"].ndim == 2 else x["gain"]
+        tk = 1.0 if x.get("tau") is None else float(x["tau"][k])
+        bk = None if x.get("bias") is None else x["bias"][k]
+        bound = row_loss_error_bound(x["h"][k], gk, R, x["targets"][k], tk, "f32", bk)
+        assert np.all(np.abs(row_loss[k] - ref["row_loss"][k]) <= bound), (name, k)
