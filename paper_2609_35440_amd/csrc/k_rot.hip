@@ -136,29 +136,94 @@ __global__ __launch_bounds__(256, 2) void k_gemm_nt_mfma(const bf16* __restrict_
             }
 }
 
-// The same product in fp32 on the vector ALU (fp32 storage, and bf16 widths
-// the matrix-core tiling does not cover): one thread per element of C.
+// The same product in fp32 (fp32 storage, and bf16 widths the tiling above does
+// not cover) on the 32x32x2 fp32 matrix instructions: 64 x 64 tiles, 4 waves of
+// 32 x 32, k in slabs of 32 staged through LDS in fp32 (rows of 128 bytes,
+// 16-byte granule g of row r at g ^ (r & 7), so 8 rows of a read cover all
+// banks), the next slab's loads in flight during a slab's products.  Sums over k
+// in pieces of 256.  Bound by the fp32 matrix rate; one fp32
+// product of 2000 x 512 x 512 takes 24 us (one thread per element of C on the
+// vector ALU: 1.7 ms).  Any M; N and Kd multiples of 8.
+template <typename E> __device__ __forceinline__ f32x4 ld4f(const E* p) {
+    typedef E EV __attribute__((ext_vector_type(4)));
+    const EV v = *(const EV*)p;
+    return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
+
 template <typename AT, typename BT, typename CT>
-__global__ void k_gemm_nt_valu(const AT* __restrict__ A, long long a_mat, const BT* gain, int g_stride,
-                               const BT* __restrict__ B, long long b_mat, CT* __restrict__ C, long long c_mat, int M,
-                               int N, int Kd) {
-    const int mat = blockIdx.z;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (long long)M * N) return;
-    const int m = (int)(i / N), n = (int)(i % N);
-    const AT* a = A + mat * a_mat + (long long)m * Kd;
-    const BT* b = B + mat * b_mat + (long long)n * Kd;
+__global__ __launch_bounds__(256) void k_gemm_nt_f32(const AT* __restrict__ A, long long a_mat, const BT* gain,
+                                                    int g_stride, const BT* __restrict__ B, long long b_mat,
+                                                    CT* __restrict__ C, long long c_mat, int M, int N, int Kd) {
+    __shared__ __attribute__((aligned(16))) float As[64 * 32];
+    __shared__ __attribute__((aligned(16))) float Bs[64 * 32];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int mat = blockIdx.y;
+    const int nt = (N + 63) / 64;
+    const int m0 = (int)(blockIdx.x / nt) * 64, n0 = (int)(blockIdx.x % nt) * 64;
+    A += mat * a_mat;
+    B += mat * b_mat;
+    C += mat * c_mat;
     const BT* g = gain ? gain + (long long)mat * g_stride : nullptr;
-    float s = 0.f;
-    for (int k = 0; k < Kd; ++k) {
-        float av = (float)a[k];
-        if (g) {
-            av *= (float)g[k];
-            if (sizeof(BT) == 2) av = (float)(bf16)av;  // the product the bf16 local-loss pass rounds
+    // staging: thread takes granule tid % 8 of rows tid / 8 and tid / 8 + 32 of both tiles
+    const int gk = tid & 7, r = tid >> 3;
+    f32x4 av[2], bv[2];
+    auto load = [&](int k0) __attribute__((always_inline)) {
+        const int k = k0 + 4 * gk;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int m = m0 + r + 32 * i, n = n0 + r + 32 * i;
+            av[i] = bv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (k < Kd && m < M) {
+                av[i] = ld4f(A + (long long)m * Kd + k);
+                if (g) {
+                    av[i] *= ld4f(g + k);
+                    if (sizeof(BT) == 2) {  // the product the bf16 local-loss pass rounds
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) av[i][e] = (float)(bf16)av[i][e];
+                    }
+                }
+            }
+            if (k < Kd && n < N) bv[i] = ld4f(B + (long long)n * Kd + k);
         }
-        s = fmaf(av, (float)b[k], s);
+    };
+    const int wm = 32 * (w & 1), wn = 32 * (w >> 1);
+    const int l32 = lane & 31, hi = lane >> 5;
+    f32x16 acc, tot;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = tot[i] = 0.f;
+    load(0);
+    for (int k0 = 0; k0 < Kd; k0 += 32) {
+        __syncthreads();  // the previous slab has been read
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int row = r + 32 * i;
+            *(f32x4*)(As + row * 32 + 4 * (gk ^ (row & 7))) = av[i];
+            *(f32x4*)(Bs + row * 32 + 4 * (gk ^ (row & 7))) = bv[i];
+        }
+        __syncthreads();
+        if (k0 + 32 < Kd) load(k0 + 32);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int q = 4 * ((2 * s + hi) ^ (lane & 7));
+            const f32x4 a4 = *(const f32x4*)(As + (wm + l32) * 32 + q);
+            const f32x4 b4 = *(const f32x4*)(Bs + (wn + l32) * 32 + q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4[e], b4[e], acc, 0, 0, 0);
+        }
+        if ((k0 & 255) == 224 || k0 + 32 >= Kd) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                tot[i] += acc[i];
+                acc[i] = 0.f;
+            }
+        }
     }
-    C[mat * c_mat + (long long)m * N + n] = (CT)s;
+    const int n = n0 + wn + l32;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int m = m0 + wm + 8 * (i >> 2) + 4 * hi + (i & 3);
+        if (m < M && n < N) C[(long long)m * N + n] = (CT)tot[i];
+    }
 }
 
 // out[k][j][i] = in[k][i][j] for nmat d x d matrices
@@ -288,14 +353,14 @@ hipError_t gemm_mfma(const bf16* A, long long a_mat, int Kd, const bf16* gain, i
     return hipSuccess;
 }
 
-// the vector-ALU product, one thread per element of C
+// the fp32 product
 template <typename AT, typename BT, typename CT>
-hipError_t gemm_valu(const AT* A, long long a_mat, const BT* gain, int g_stride, const BT* B, long long b_mat, CT* C,
-                     long long c_mat, int nmat, int M, int N, int Kd, hipStream_t s) {
-    const long long blocks = ((long long)M * N + 255) / 256;
+hipError_t gemm_f32(const AT* A, long long a_mat, const BT* gain, int g_stride, const BT* B, long long b_mat, CT* C,
+                    long long c_mat, int nmat, int M, int N, int Kd, hipStream_t s) {
+    const long long blocks = ((long long)M + 63) / 64 * ((N + 63) / 64);
     if (blocks > 2147483647LL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_gemm_nt_valu<AT, BT, CT>), dim3((unsigned)blocks, 1, (unsigned)nmat), dim3(256), 0, s, A,
-                       a_mat, gain, g_stride, B, b_mat, C, c_mat, M, N, Kd);
+    hipLaunchKernelGGL((k_gemm_nt_f32<AT, BT, CT>), dim3((unsigned)blocks, (unsigned)nmat), dim3(256), 0, s, A, a_mat,
+                       gain, g_stride, B, b_mat, C, c_mat, M, N, Kd);
     return hipGetLastError();
 }
 
@@ -306,9 +371,9 @@ hipError_t launch_rot_rows(int dtype, const void* h, const void* gain, int g_str
         return gemm_mfma<bf16>((const bf16*)h, td, d, (const bf16*)gain, g_stride, (const bf16*)R, dd, d, (bf16*)u,
                                td, nmat, T, d, s);
     if (dtype == 0)
-        return gemm_valu<bf16, bf16, bf16>((const bf16*)h, td, (const bf16*)gain, g_stride, (const bf16*)R, dd,
+        return gemm_f32<bf16, bf16, bf16>((const bf16*)h, td, (const bf16*)gain, g_stride, (const bf16*)R, dd,
                                            (bf16*)u, td, nmat, T, d, d, s);
-    return gemm_valu<float, float, float>((const float*)h, td, (const float*)gain, g_stride, (const float*)R, dd,
+    return gemm_f32<float, float, float>((const float*)h, td, (const float*)gain, g_stride, (const float*)R, dd,
                                           (float*)u, td, nmat, T, d, d, s);
 }
 
@@ -321,9 +386,9 @@ hipError_t launch_rot_back(int dtype, bool planes, const void* e, const void* Rt
                                 s);
     }
     if (dtype == 0)
-        return gemm_valu<float, bf16, float>((const float*)e, td, nullptr, 0, (const bf16*)Rt, dd, D, td, nmat, T, d,
+        return gemm_f32<float, bf16, float>((const float*)e, td, nullptr, 0, (const bf16*)Rt, dd, D, td, nmat, T, d,
                                              d, s);
-    return gemm_valu<float, float, float>((const float*)e, td, nullptr, 0, (const float*)Rt, dd, D, td, nmat, T, d, d,
+    return gemm_f32<float, float, float>((const float*)e, td, nullptr, 0, (const float*)Rt, dd, D, td, nmat, T, d, d,
                                           s);
 }
 
