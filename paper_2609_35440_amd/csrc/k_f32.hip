@@ -2,7 +2,8 @@
 // (products and sums in fp32, on fp32 or bf16 storage).  They serve the fp32
 // configuration, where the products must be true fp32 products, and the bf16
 // widths that the bf16 matrix-core kernels do not tile (of those, the passes with a
-// second product up to d = 1536 run in the exact form of k_mfma.hip).  Same passes and notation as
+// second product run in the exact form of k_mfma.hip and k_exact_wide.hip from
+// d = 72 on, and exit evaluation as a product on planes, k_logits.hip).  Same passes and notation as
 // k_mfma.hip (z_tv = tau_k <R_kv, hhat_t> + b_kv, hhat = g_k * r_t h_t): a tile
 // of R stationary rows X, the other operand Y streamed in chunks of 256 rows,
 // the T x V logits never written.

@@ -27,6 +27,7 @@ bool flag_ok(int f) { return f == 0 || f == 1; }
 struct Plan {
     bool mfma = false;         // matrix-core family (either tiling)
     bool exact = false;        // fp32 family, bf16 storage: local loss and readout gradient in the exact form (k_mfma.hip)
+    bool xwide = false;        // the exact form's wide kernels (k_exact_wide.hip)
     bool planes = false;       // fp32 family, bf16 storage: forward-only products on plane copies (k_logits.hip)
     size_t eval_room = 0;      // bytes at wtile that the forms of exit evaluation without tiled copies may use
     bool wide = false;         // the 16-row wide tiling of the matrix-core family (d = 2560)
@@ -67,7 +68,8 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     const int K = a.K, T = a.T, d = a.d;
     P->wide = solo::mfma_wide_supported(a.dtype, d);
     P->mfma = solo::mfma_supported(a.dtype, d) || P->wide;
-    P->exact = !P->mfma && solo::exact_supported(a.dtype, d);
+    P->xwide = !P->mfma && a.dtype == SOLO_BF16 && d > 1536;
+    P->exact = P->xwide || (!P->mfma && solo::exact_supported(a.dtype, d));
     P->eval = eval;
     const size_t kt = (size_t)K * T;
     size_t off = 0;
@@ -99,7 +101,9 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
         P->whtile = off;
         off = align_up(off + tv * P->nhead_tiles);
     }
-    const int rows = P->wide ? solo::kMfmaWideRows : (P->mfma ? solo::mfma_rows(d) : (P->exact ? solo::exact_rows(d) : solo::f32_rows(d)));
+    const int rows = P->wide ? solo::kMfmaWideRows : (P->mfma ? solo::mfma_rows(d) : (P->xwide   ? solo::exact_wide_rows()
+                                                                 : P->exact ? solo::exact_rows(d)
+                                                                            : solo::f32_rows(d)));
     P->rows = rows;
     P->ntiles = (T + rows - 1) / rows;
     P->rot = a.rot != nullptr && K > 1;
@@ -441,6 +445,7 @@ int run(const solo_readout_args& x, bool eval) {
             case 1: {
                 const hipError_t e = P.wide    ? solo::launch_local_loss_mfma_wide(b, P.ext, n, s)
                                      : P.mfma  ? solo::launch_local_loss_mfma(b, P.ext, n, s)
+                                     : P.xwide ? solo::launch_local_loss_exact_wide(b, P.ext, n, s)
                                      : P.exact ? solo::launch_local_loss_exact(b, P.ext, n, s)
                                                : solo::launch_local_loss_f32(dt, b, n, s);
                 if (e != hipSuccess || b.nsplit == 1) return e;
@@ -450,6 +455,7 @@ int run(const solo_readout_args& x, bool eval) {
             case 2:
                 return P.wide    ? solo::launch_readout_grad_mfma_wide(b, n, s)
                        : P.mfma  ? solo::launch_readout_grad_mfma(b, n, s)
+                       : P.xwide ? solo::launch_readout_grad_exact_wide(b, n, s)
                        : P.exact ? solo::launch_readout_grad_exact(b, n, s)
                                  : solo::launch_readout_grad_f32(dt, b, n, s);
             default:

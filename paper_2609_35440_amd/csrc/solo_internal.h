@@ -111,6 +111,10 @@ bool exact_supported(int dtype, int d);
 int exact_rows(int d);
 hipError_t launch_local_loss_exact(const FusedArgs& a, bool ext, int nmod, hipStream_t s);
 hipError_t launch_readout_grad_exact(const FusedArgs& a, int nmod, hipStream_t s);
+// the same for wider rows (k_exact_wide.hip): any bf16 width up to 4096
+int exact_wide_rows();
+hipError_t launch_local_loss_exact_wide(const FusedArgs& a, bool ext, int nmod, hipStream_t s);
+hipError_t launch_readout_grad_exact_wide(const FusedArgs& a, int nmod, hipStream_t s);
 // forward-only passes as a tiled product (k_logits.hip): d % 256 == 0
 struct LogitsArgs {
     const bf16* X;          // [nX][d] stationary rows; module m of a launch x_stride elements further,
