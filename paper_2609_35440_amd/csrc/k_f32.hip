@@ -31,9 +31,8 @@
 // R = 32 while the accumulator fits the registers next to the streamed
 // operand (d <= 2048: 128 registers at 256 columns per wave), 16 above.
 //
-// Measured (K=2, T=1001, d=768, V=8003, fp32): 0.99 ms per training call, 14.7
-// with one thread per column on the vector ALU; K=2, T=1024, d=4096, V=32000,
-// bf16: 19.4 ms, 339 before.
+// Measured (K=2, T=1001, d=768, V=8003, fp32): 0.97 ms per training call, 14.7
+// with one thread per column on the vector ALU.
 //
 // Sums: a logit's k-sum is cut into pieces of 256, each summed by itself, so
 // its rounding does not grow with d as one chain would.
@@ -154,24 +153,6 @@ template <> struct Seg<bf16, 1> {
     }
     __device__ __forceinline__ float get(int) const { return bf16_bits_to_f32(r); }
 };
-template <> struct Seg<bf16, 2> {
-    int r;
-    __device__ __forceinline__ void ld(__amdgpu_buffer_rsrc_t rs, int vo) {
-        r = (int)__builtin_amdgcn_raw_buffer_load_b32(rs, vo, 0, 0);
-    }
-    __device__ __forceinline__ float get(int e) const {
-        return __int_as_float(e ? (r & (int)0xffff0000) : (r << 16));
-    }
-};
-template <> struct Seg<bf16, 4> {
-    i32x2 r;
-    __device__ __forceinline__ void ld(__amdgpu_buffer_rsrc_t rs, int vo) {
-        r = __builtin_bit_cast(i32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, vo, 0, 0));
-    }
-    __device__ __forceinline__ float get(int e) const {
-        return __int_as_float((e & 1) ? (r[e >> 1] & (int)0xffff0000) : (r[e >> 1] << 16));
-    }
-};
 
 // The column slices of the accumulator: NG groups of R CW columns per wave
 // (lane m of a group holds columns CW m .. + CW - 1); with YS > 1 only 8 / YS
@@ -191,7 +172,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
     constexpr int NCG = NW / YS;     // waves with distinct columns
     constexpr int FLUSH = 256 / KS;  // slabs per piece of a logit's k-sum
     constexpr int GBUF = PC ? R * YC : 4;
-    constexpr int U = NG * CW >= 24 ? (ES == 4 || NG * CW >= 32 ? 2 : 4) : (NG * CW >= 4 ? 4 : 8);
+    constexpr int U = NG * CW >= 24 ? 2 : (NG * CW >= 4 ? 4 : 8);
     __shared__ __attribute__((aligned(16))) char ys0[NW * YW * 128];
     __shared__ __attribute__((aligned(16))) char ys1[NW * YW * 128];
     __shared__ __attribute__((aligned(16))) float xs0[R * KS];
@@ -723,21 +704,25 @@ hipError_t launch_t(const FusedArgs& a, int nmod, hipStream_t s) {
     return hipGetLastError();
 }
 
-// passes with a second product: columns per wave by width
+// passes with a second product: columns per wave by width (bf16 storage up to 64:
+// wider rows run in the exact form)
 template <typename E, int MODE>
 hipError_t launch_w(const FusedArgs& a, int nmod, hipStream_t s) {
     const int d = a.d;
     if (d <= 32) return launch_t<E, MODE, 32, 1, 1, 8>(a, nmod, s);
     if (d <= 64) return launch_t<E, MODE, 32, 1, 1, 4>(a, nmod, s);
-    if (d <= 128) return launch_t<E, MODE, 32, 1, 1, 2>(a, nmod, s);
-    if (d <= 256) return launch_t<E, MODE, 32, 1, 1, 1>(a, nmod, s);
-    if (d <= 512) return launch_t<E, MODE, 32, 1, 2, 1>(a, nmod, s);
-    if (d <= 768) return launch_t<E, MODE, 32, 3, 1, 1>(a, nmod, s);
-    if (d <= 1024) return launch_t<E, MODE, 32, 1, 4, 1>(a, nmod, s);
-    if (d <= 1536) return launch_t<E, MODE, 32, 3, 2, 1>(a, nmod, s);
-    if (d <= 2048) return launch_t<E, MODE, 32, 2, 4, 1>(a, nmod, s);
-    if (d <= 3072) return launch_t<E, MODE, 16, 6, 4, 1>(a, nmod, s);
-    return launch_t<E, MODE, 16, 8, 4, 1>(a, nmod, s);
+    if constexpr (sizeof(E) == 4) {
+        if (d <= 128) return launch_t<E, MODE, 32, 1, 1, 2>(a, nmod, s);
+        if (d <= 256) return launch_t<E, MODE, 32, 1, 1, 1>(a, nmod, s);
+        if (d <= 512) return launch_t<E, MODE, 32, 1, 2, 1>(a, nmod, s);
+        if (d <= 768) return launch_t<E, MODE, 32, 3, 1, 1>(a, nmod, s);
+        if (d <= 1024) return launch_t<E, MODE, 32, 1, 4, 1>(a, nmod, s);
+        if (d <= 1536) return launch_t<E, MODE, 32, 3, 2, 1>(a, nmod, s);
+        if (d <= 2048) return launch_t<E, MODE, 32, 2, 4, 1>(a, nmod, s);
+        if (d <= 3072) return launch_t<E, MODE, 16, 6, 4, 1>(a, nmod, s);
+        return launch_t<E, MODE, 16, 8, 4, 1>(a, nmod, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace

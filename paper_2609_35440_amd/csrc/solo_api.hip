@@ -162,6 +162,8 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     off = align_up(off + (second ? kt * 16 : 0));
     P->hg = off;
     off = align_up(off + (size_t)(P->hg_hi - P->hg_lo) * (size_t)solo::tiled_elems(T, d) * 2);
+    // plane copies of the bias-gradient modules' rows
+    if (P->exact) off = align_up(off + (size_t)(P->bg_hi - P->bg_lo) * T * solo::plane_pitch(d) * 2);
     P->rowdtau = off;
     off = align_up(off + (a.dtau ? kt * 4 : 0));
     P->dgp = off;
@@ -293,10 +295,11 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
 // goes to the output, take the place of the row statistics and losses (3 K T
 // floats), which no later stage reads.
 int prod_bgrad_splits(const Plan& P, int n, int K, int T, int d, int V) {
-    const int rows = P.wide ? solo::kMfmaWideEvalRows : solo::mfma_eval_rows(d);
-    const double chunk = 1.2 * eval_chunk_us(rows, d);
+    // (outside the bf16 families the fused pass is the fp32 kernels': 32 rows, chunks of 256 tokens)
+    const int rows = P.exact ? 32 : (P.wide ? solo::kMfmaWideEvalRows : solo::mfma_eval_rows(d));
+    const double chunk = P.exact ? (2.0 + 0.08 * d) / 16.0 : 1.2 * eval_chunk_us(rows, d);
     const double fused = (double)(((((long long)V + rows - 1) / rows) * n + 255) / 256) * (double)((T + 15) / 16) * chunk;
-    const SplitCost c = {prod_tile_us(d, false), 4.0, (double)n * V * 8.0 / 3e6};
+    const SplitCost c = {prod_tile_us(d, P.exact), 4.0 + (P.exact ? (double)n * T * d * 6.0 / 4e6 : 0.0), (double)n * V * 8.0 / 3e6};
     double us = 0.0;
     const int s = best_split((((long long)V + 255) / 256) * n, ((long long)T + 255) / 256, c,
                              1.0 + 3.0 * K * T / ((double)n * V), &us);
@@ -554,10 +557,20 @@ int run(const solo_readout_args& x, bool eval) {
         return copies(ah, lo, K - 1, as_tiles) && copies(a, K - 1, hi, as_tiles);
     };
     const int nbg = P.bg_hi - P.bg_lo;
-    const int bsplit = !eval && P.mfma && nbg > 0 ? prod_bgrad_splits(P, nbg, K, T, d, V) : 0;
+    const int bsplit = !eval && (P.mfma || P.exact) && nbg > 0 ? prod_bgrad_splits(P, nbg, K, T, d, V) : 0;
     if (!eval && P.mfma &&
         (!gain_copies(P.rg_lo, P.rg_hi, tiled_rgrad(P)) || !gain_copies(P.bg_lo, P.bg_hi, bsplit == 0)))
         return SOLO_ERR_HIP;
+    if (P.exact && bsplit > 0) {
+        for (int m = P.bg_lo; m < P.bg_hi; ++m) {
+            const solo::FusedArgs& g = P.rot && m < K - 1 ? ah : a;
+            if (solo::launch_gain_planes((const solo::bf16*)g.h + (long long)m * T * d,
+                                         (const solo::bf16*)g.gain + (long long)m * g.g_stride,
+                                         (solo::bf16*)(ws + P.hg) + (long long)(m - P.bg_lo) * T * solo::plane_pitch(d), T,
+                                         d, s) != hipSuccess)
+                return SOLO_ERR_HIP;
+        }
+    }
     if (!eval && !pass_range(2, P.rg_lo, P.rg_hi)) return SOLO_ERR_HIP;
     if (!mark(3)) return SOLO_ERR_HIP;
     auto prod_bgrad = [&]() -> bool {
@@ -569,8 +582,9 @@ int run(const solo_readout_args& x, bool eval) {
         l.x_stride = lo < K - 1 ? a.wh_stride : 0;
         l.x_last = lo < K - 1 && P.bg_hi == K ? K - 1 - lo : -1;
         l.x_last_off = ((intptr_t)term - (intptr_t)(heads + (K - 1) * a.wh_stride)) / 2;
-        l.Y = (const solo::bf16*)a.hg + (long long)(lo - P.hg_lo) * solo::tiled_elems(T, d);
-        l.y_stride = solo::tiled_elems(T, d);
+        l.exact = P.exact;
+        l.y_stride = P.exact ? (long long)T * solo::plane_pitch(d) : solo::tiled_elems(T, d);
+        l.Y = (const solo::bf16*)a.hg + (P.exact ? 0 : (lo - P.hg_lo) * l.y_stride);
         l.nX = V;
         l.nY = T;
         l.d = d;

@@ -112,3 +112,17 @@ def test_eval_planes(name, K, T, d, V, extras):
         bk = None if x.get("bias") is None else x["bias"][k]
         bound = row_loss_error_bound(x["h"][k], gk, R, x["targets"][k], tk, "f32", bk)
         assert np.all(np.abs(row_loss[k] - ref["row_loss"][k]) <= bound), (name, k)
+
+
+@pytest.mark.parametrize("T,d,V,extras,final", [(1025, 136, 1025, dict(bias=True, tau=True), True),
+                                                (700, 640, 513, dict(wbar="per_head", bias=True), False),
+                                                (513, 1800, 600, dict(rot=True), True)], ids=["heads", "all", "rot"])
+def test_bias_gradient_planes(T, d, V, extras, final):
+    x = make_extras(make_inputs("1b", seed=15, K=3, T=T, d=d, V=V), seed=15, **extras)
+    flags = dict(final_module_dW=final, want_dtau=True, want_dbias=True)
+    g = run_general(x, flags)
+    ref = oracle_general(x, flags)
+    compare(g, ref, "bf16", flags, f"bias gradient on planes {T} {d} {V}")
+    if "rot" not in extras:  # (rotated rows are rounded to bf16)
+        for k in range(3):
+            assert rel_max_err(g["dbias"][k], ref["dbias"][k]) <= 1e-5, k
