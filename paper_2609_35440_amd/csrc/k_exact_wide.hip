@@ -328,7 +328,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
             const int xr_ = x0 + xo;
             if (SPL) {
                 if (xr_ < nX)
-                    *(f32x4*)(a.split_stat + 4 * ((long long)blockIdx.z * a.K * a.T + modoff + xr_)) =
+                    *(f32x4*)(a.split_stat + 4 * ((long long)blockIdx.z * a.part_rows + modoff + xr_)) =
                         (f32x4){m_run, sx, zy, 0.f};
             } else {
                 const RowEnd re = finish_row(m_run, sx, zy, own_tgt >= 0 && own_tgt < nY);
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
     }
     if (LL && SPL) {
         if (x0 + ex < nX) {
-            float* P = a.split_acc + ((long long)blockIdx.z * a.K * a.T + modoff + x0 + ex) * d;
+            float* P = a.split_acc + ((long long)blockIdx.z * a.part_rows + modoff + x0 + ex) * d;
             each([&](int b, int j, bool ok) __attribute__((always_inline)) {
                 if (ok) *(f32x4*)(P + j) = acc[b];
             });

@@ -531,7 +531,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
         }
         if (MODE == LOCAL && nsplit > 1) {
             if (w == 0 && lane < R && xok) {
-                const long long p = (long long)blockIdx.z * a.K * a.T + modoff + xg;
+                const long long p = (long long)blockIdx.z * a.part_rows + modoff + xg;
                 const f32x4 st = {m_run, sx, zy, 0.f};
                 *(f32x4*)(a.split_stat + 4 * p) = st;
             }
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
     if (MODE == LOCAL && nsplit > 1) {
         // the unnormalised partial sums of this split, for the merge
         if (own && xok) {
-            float* P = a.split_acc + ((long long)blockIdx.z * a.K * a.T + modoff + xg) * d;
+            float* P = a.split_acc + ((long long)blockIdx.z * a.part_rows + modoff + xg) * d;
             each([&](int g, int i, int j) __attribute__((always_inline)) {
                 float o[CV];
 #pragma unroll

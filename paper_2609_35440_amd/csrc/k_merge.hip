@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void k_merge(FusedArgs a) {
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
     const int d = a.d;
-    const long long KT = (long long)a.K * a.T;
+    const long long KT = a.part_rows;
     const long long row = (long long)k * a.T + blockIdx.x;
     const float tau = a.tau ? a.tau[k] : 1.f;
     const E* g = (const E*)a.gain + (long long)k * a.g_stride;
@@ -171,21 +171,33 @@ __global__ __launch_bounds__(256) void k_merge_eval(FusedArgs a, long long rows)
     const int lane = threadIdx.x & 63;
     const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
-    float m = -INFINITY, s_own = 0.f, zy = 0.f, best = -INFINITY;
+    // lane l holds splits l, l + 64, ..
+    float ms[kEvalSplits / 64], ss[kEvalSplits / 64], m = -INFINITY, zy = 0.f, best = -INFINITY;
     int best_v = -1;
-    if (lane < a.nsplit) {
-        const float* sp = a.split_stat + 8 * ((long long)lane * a.K * a.T + row);
-        const f32x4 st = *(const f32x4*)sp;
-        m = st[0];
-        s_own = st[1];
-        zy = st[2];
-        best = st[3];
-        best_v = __float_as_int(sp[4]);
+#pragma unroll
+    for (int i = 0; i < kEvalSplits / 64; ++i) {
+        const int s = 64 * i + lane;
+        ms[i] = -INFINITY;
+        ss[i] = 0.f;
+        if (s < a.nsplit) {
+            const float* sp = a.split_stat + 8 * (s * a.part_rows + row);
+            const f32x4 st = *(const f32x4*)sp;
+            const int v = __float_as_int(sp[4]);
+            ms[i] = st[0];
+            ss[i] = st[1];
+            zy += st[2];
+            m = fmaxf(m, st[0]);
+            if (st[3] > best || (st[3] == best && (unsigned)v < (unsigned)best_v)) {
+                best = st[3];
+                best_v = v;
+            }
+        }
     }
-    const float m_own = m;
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    float sx = m_own == m ? s_own : s_own * __builtin_amdgcn_exp2f(m_own - m);
-    if (lane >= a.nsplit) sx = 0.f;
+    float sx = 0.f;
+#pragma unroll
+    for (int i = 0; i < kEvalSplits / 64; ++i)
+        if (64 * i + lane < a.nsplit) sx += ms[i] == m ? ss[i] : ss[i] * __builtin_amdgcn_exp2f(ms[i] - m);
     for (int off = 32; off > 0; off >>= 1) {
         sx += __shfl_xor(sx, off, 64);
         zy += __shfl_xor(zy, off, 64);

@@ -585,7 +585,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             if (SPL) {
                 if (lane % LPR == 0 && x0 + xo[r] < nX) {
                     constexpr int SW = MODE == EVAL ? 8 : 4;  // floats per row and split
-                    float* sp = a.split_stat + SW * ((long long)blockIdx.z * a.K * a.T + modoff + x0 + xo[r]);
+                    float* sp = a.split_stat + SW * ((long long)blockIdx.z * a.part_rows + modoff + x0 + xo[r]);
                     *(f32x4*)sp = (f32x4){m_run[r], sx, zy, bst};
                     if (MODE == EVAL) *(f32x4*)(sp + 4) = (f32x4){__int_as_float(bv), 0.f, 0.f, 0.f};
                 }
@@ -617,7 +617,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         for (int h = 0; h < NR; ++h) {
             const int xg = x0 + 32 * h + ex;
             if (xg >= nX) continue;
-            float* P = a.split_acc + ((long long)blockIdx.z * a.K * a.T + modoff + xg) * d;
+            float* P = a.split_acc + ((long long)blockIdx.z * a.part_rows + modoff + xg) * d;
 #pragma unroll
             for (int b = 0; b < (PC ? G::NB : 1); ++b)
 #pragma unroll

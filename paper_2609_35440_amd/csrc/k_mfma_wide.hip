@@ -390,7 +390,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
             if (SPL) {
                 if (yy == 0 && wr[r] && x0 + xo[r] < nX) {
                     constexpr int SW = MODE == EVAL ? 8 : 4;  // floats per row and split
-                    float* sp = a.split_stat + SW * ((long long)blockIdx.z * a.K * a.T + modoff + x0 + xo[r]);
+                    float* sp = a.split_stat + SW * ((long long)blockIdx.z * a.part_rows + modoff + x0 + xo[r]);
                     *(f32x4*)sp = (f32x4){m_run[r], sx, zy, bst};
                     if (MODE == EVAL) *(f32x4*)(sp + 4) = (f32x4){__int_as_float(bv), 0.f, 0.f, 0.f};
                 }
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     if (MODE == LOCAL && SPL) {
         // the unnormalised partial sums of this split, for the merge
         if (x0 + ex < nX) {
-            float* P = a.split_acc + ((long long)blockIdx.z * a.K * a.T + modoff + x0 + ex) * d;
+            float* P = a.split_acc + ((long long)blockIdx.z * a.part_rows + modoff + x0 + ex) * d;
 #pragma unroll
             for (int b = 0; b < G::NB; ++b) *(f32x4*)(P + js + 16 * b + 4 * eg) = acc[b];
         }

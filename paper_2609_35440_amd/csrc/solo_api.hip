@@ -84,7 +84,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     P->planes = !P->mfma && a.dtype == SOLO_BF16;
     if (P->planes && eval) {
         const size_t nvt = ((size_t)a.V + 255) / 256;
-        const size_t parts = kt * 32 * (nvt < solo::kMaxSplit ? nvt : solo::kMaxSplit);
+        const size_t parts = kt * 32 * (nvt < solo::kEvalSplits ? nvt : solo::kEvalSplits);
         P->eval_room = (kt < 16384 ? kt : 16384) * solo::plane_pitch(d) * 2 + 512 +
                        (parts < (size_t(32) << 20) ? parts : (size_t(32) << 20));
         P->wtile = off;
@@ -185,10 +185,11 @@ struct SplitCost {
     double part_us;     // the parts of one split, written and read once
 };
 
-int best_split(long long tiles, long long nch, const SplitCost& c, double max_s, double* us_out = nullptr) {
+int best_split(long long tiles, long long nch, const SplitCost& c, double max_s, double* us_out = nullptr,
+               int limit = solo::kMaxSplit) {
     int best = 1;
     double best_us = (double)((tiles + 255) / 256) * (double)nch * c.chunk_us;
-    for (int s = 2; s <= solo::kMaxSplit && s <= nch && s <= max_s && tiles * (s - 1) < 512; ++s) {
+    for (int s = 2; s <= limit && s <= nch && s <= max_s && tiles * (s - 1) < 512; ++s) {
         const double us = (double)((tiles * s + 255) / 256) * (double)((nch + s - 1) / s) * c.chunk_us + c.merge_us +
                           s * c.part_us;
         if (us < best_us) {
@@ -207,12 +208,16 @@ int best_split(long long tiles, long long nch, const SplitCost& c, double max_s,
 // rows take 4 R d clocks at the fp32 matrix rate, 70% of it reached; a 16-row
 // chunk of the bf16 kernels measured 1.15 us at 65536 elements per tile (32 x
 // 2048 and 64 x 1024), of which about 0.5 us is the exchange and its barriers.
+// (A call whose modules together fill the chip is split only where ROT launches
+// them apart, and then has the room to itself; smaller calls share one bound
+// whatever they launch apart, so that ROT with R = I cuts alike more often.)
 int local_splits(const Plan& P, int n, int K, int T, int d, int V, size_t room) {
     const double td = (double)P.rows * d;
     const bool fused = P.mfma || P.exact;
     const SplitCost c = {fused ? 0.5 + 0.65 * td / 65536.0 : 4.0 * td / 1.6e3, 6.0, (double)n * T * d * 8.0 / 3e6};
     const int yc = fused ? 16 : 256;
-    return best_split((long long)P.ntiles * n, ((long long)V + yc - 1) / yc, c, (double)room / ((double)K * T * (d + 4)));
+    const double rows = (double)T * ((long long)P.ntiles * K >= 256 ? n : K);
+    return best_split((long long)P.ntiles * n, ((long long)V + yc - 1) / yc, c, (double)room / (rows * (d + 4)));
 }
 
 // Exit evaluation on the matrix-core families runs in one of three forms:
@@ -256,7 +261,7 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
     double us = 0.0;
     // (row-major, a chunk's operand loads take 16 rows of 64 bytes each: 1.75 us at d = 2048)
     const SplitCost c = {1.05 * chunk > 0.00085 * d ? 1.05 * chunk : 0.00085 * d, 10.0, kt * 64.0 / 3e6};
-    const int s = best_split(stiles, nch, c, room / (kt * 32.0), &us);
+    const int s = best_split(stiles, nch, c, room / (kt * 32.0), &us, solo::kEvalSplits);
     if (!P.planes && s > 1 && us < best) {
         E.form = EvalPlan::SPLIT;
         E.nsplit = s;
@@ -264,7 +269,7 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
     }
     const long long lists = flat ? 1 : K, n = flat ? (long long)K * T : T;  // rows are one list, or one per module
     const long long nvt = ((long long)V + 255) / 256;
-    for (int sp = 1; sp <= solo::kMaxSplit && sp <= nvt; ++sp) {
+    for (int sp = 1; sp <= solo::kEvalSplits && sp <= nvt; ++sp) {
         const double cap = (room - 512.0 - (sp > 1 ? kt * 32.0 * sp : 0.0)) / row_bytes;
         if (cap < (n < 256 ? (double)n : 256.0)) break;
         const long long np0 = (long long)((double)n / cap) + 1;
@@ -402,6 +407,7 @@ int run(const solo_readout_args& x, bool eval) {
     const bool flat = eval && !P.rot && !x.bias && !(x.Wbar && K > 1);
     const EvalPlan E = eval && (P.mfma || P.planes) ? plan_eval(P, K, T, d, V, flat) : EvalPlan();
     a.split_stat = (float*)(ws + P.wtile);
+    a.part_rows = (long long)K * T;
     if (E.form == EvalPlan::SPLIT) {
         a.nsplit = E.nsplit;
         a.flat = flat;
@@ -437,8 +443,11 @@ int run(const solo_readout_args& x, bool eval) {
         b.m0 = m0;
         if (which == 1) {
             b.nsplit = local_splits(P, n, K, T, d, V, room_floats);
-            b.split_acc = room;
-            b.split_stat = room + (size_t)b.nsplit * K * T * d;
+            if (b.nsplit > 1) {
+                b.part_rows = (long long)n * T;
+                b.split_acc = room - (long long)m0 * T * d;
+                b.split_stat = room + b.nsplit * b.part_rows * d - 4LL * m0 * T;
+            }
         }
         switch (which) {
             case 0:

@@ -69,9 +69,11 @@ struct FusedArgs {
                           // lo = bf16(e - hi) at [d, 2d) (the rotate-back product's operand as a 2d-deep
                           // bf16 row); the fp32 family writes e in fp32
     int nsplit;           // local-loss pass: workgroups the vocabulary of a row tile is split over (grid z)
-    float* split_acc;     // nsplit > 1: [nsplit][K T][d] unnormalised sums of exp(z - m) R_v of each split
-    float* split_stat;    // nsplit > 1: [nsplit][K T][4] {m (base 2), sum without the target, target logit, -};
-                          // exit evaluation: [nsplit][K T][8], the largest logit and its column after those three
+    long long part_rows;  // nsplit > 1: rows of the arrays of parts, whose pointers are such that a row's entry is
+                          // at its global index k T + t
+    float* split_acc;     // nsplit > 1: [nsplit][part_rows][d] unnormalised sums of exp(z - m) R_v of each split
+    float* split_stat;    // nsplit > 1: [nsplit][part_rows][4] {m (base 2), sum without the target, target logit, -};
+                          // exit evaluation: [nsplit][part_rows][8], the largest logit and its column after those three
     int flat;             // split exit evaluation: 1 takes the rows of all modules as one list (one readout, no bias)
 };
 
@@ -161,7 +163,8 @@ hipError_t launch_exit_eval_f32(int dtype, const FusedArgs& a, int nmod, hipStre
 // (form: what the form's gradient passes read, see k_merge)
 enum MergeForm { MERGE_BF16 = 0, MERGE_F32 = 1, MERGE_EXACT = 2 };
 hipError_t launch_merge(int dtype, MergeForm form, const FusedArgs& a, int nmod, int rows, hipStream_t s);
-constexpr int kMaxSplit = 64;  // splits of one row tile (a lane of the merge each)
+constexpr int kMaxSplit = 64;     // splits of one row tile (a lane of the merge each)
+constexpr int kEvalSplits = 256;  // the same in exit evaluation
 hipError_t launch_merge_eval(const FusedArgs& a, long long rows, hipStream_t s);
 // ROT (k_rot.hip): C = A B^T per matrix; transposes; a vector of ones; the
 // heads' RMSNorm backward from the rotated-back gradient D = e R_k
