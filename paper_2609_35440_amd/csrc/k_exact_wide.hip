@@ -90,7 +90,11 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int d = a.d;
     const int js = w * DS;
-    const int x0 = blockIdx.x * XR;
+    // (splits next to each other: the grid goes round-robin over the XCDs, whose L2s then
+    // stream a part of the vocabulary each)
+    const int tile = SPL ? (int)blockIdx.x / a.nsplit : (int)blockIdx.x;
+    const int sp = SPL ? (int)blockIdx.x % a.nsplit : 0;
+    const int x0 = tile * XR;
     const int k = a.m0 + (int)blockIdx.y;
     const long long modoff = (long long)k * a.T;
     const float tau_k = a.tau ? a.tau[k] : 1.f;
@@ -102,8 +106,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
     const int nX = LL ? a.T : a.V;
     const int nY = LL ? a.V : a.T;
     const int nchunks = (nY + YC - 1) / YC;
-    const int ck_lo = SPL ? (int)((long long)nchunks * blockIdx.z / a.nsplit) : 0;
-    const int ck_hi = SPL ? (int)((long long)nchunks * (blockIdx.z + 1) / a.nsplit) : nchunks;
+    const int ck_lo = SPL ? (int)((long long)nchunks * sp / a.nsplit) : 0;
+    const int ck_hi = SPL ? (int)((long long)nchunks * (sp + 1) / a.nsplit) : nchunks;
 
     LDS_AS char* const slice = (LDS_AS char*)(LDS_AS void*)ybuf + w * 2 * HALF;
     const unsigned slice_u = lds_addr(slice);
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
             const int xr_ = x0 + xo;
             if (SPL) {
                 if (xr_ < nX)
-                    *(f32x4*)(a.split_stat + 4 * ((long long)blockIdx.z * a.part_rows + modoff + xr_)) =
+                    *(f32x4*)(a.split_stat + 4 * ((long long)sp * a.part_rows + modoff + xr_)) =
                         (f32x4){m_run, sx, zy, 0.f};
             } else {
                 const RowEnd re = finish_row(m_run, sx, zy, own_tgt >= 0 && own_tgt < nY);
@@ -348,7 +352,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
     }
     if (LL && SPL) {
         if (x0 + ex < nX) {
-            float* P = a.split_acc + ((long long)blockIdx.z * a.part_rows + modoff + x0 + ex) * d;
+            float* P = a.split_acc + ((long long)sp * a.part_rows + modoff + x0 + ex) * d;
             each([&](int b, int j, bool ok) __attribute__((always_inline)) {
                 if (ok) *(f32x4*)(P + j) = acc[b];
             });
@@ -435,8 +439,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
 
 template <int MODE, int DS, bool EXT>
 hipError_t launch_ds(const FusedArgs& a, int nmod, hipStream_t s) {
-    const dim3 grid((unsigned)(((MODE == LOCAL ? a.T : a.V) + XR - 1) / XR), (unsigned)nmod,
-                    MODE == LOCAL ? (unsigned)a.nsplit : 1u);
+    const dim3 grid((unsigned)(((MODE == LOCAL ? a.T : a.V) + XR - 1) / XR * (MODE == LOCAL ? a.nsplit : 1)),
+                    (unsigned)nmod);
     if constexpr (MODE == LOCAL) {
         if (a.nsplit > 1) {
             hipLaunchKernelGGL((k_exact_wide<MODE, DS, EXT, true>), grid, dim3(NTHR), 0, s, a);

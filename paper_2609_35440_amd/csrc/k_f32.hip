@@ -191,7 +191,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
     const int ln = lane % R;  // stationary row of the lane (n), or operand row (m)
     const int kq = lane / R;
     const int d = a.d;
-    const int x0 = blockIdx.x * R;
+    const int nsplit = (MODE == LOCAL) ? a.nsplit : 1;
+    const int sp = (int)blockIdx.x % nsplit;  // (splits next to each other, as in k_mfma.hip)
+    const int x0 = ((int)blockIdx.x / nsplit) * R;
     const int k = a.m0 + (int)blockIdx.y;
     const long long modoff = (long long)k * a.T;
     const float tau = a.tau ? a.tau[k] : 1.f;
@@ -205,9 +207,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
     const int nY = LL ? a.V : a.T;
     const int nchunks = (nY + YC - 1) / YC;
     // chunks of this workgroup (the local-loss pass may be split over the vocabulary)
-    const int nsplit = (MODE == LOCAL) ? a.nsplit : 1;
-    const int c_lo = (int)((long long)nchunks * blockIdx.z / nsplit);
-    const int c_hi = (int)((long long)nchunks * (blockIdx.z + 1) / nsplit);
+    const int c_lo = (int)((long long)nchunks * sp / nsplit);
+    const int c_hi = (int)((long long)nchunks * (sp + 1) / nsplit);
     const int nslab = (d + KS - 1) / KS;
 
     const int xg = x0 + ln;  // the lane's stationary row
@@ -531,7 +532,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
         }
         if (MODE == LOCAL && nsplit > 1) {
             if (w == 0 && lane < R && xok) {
-                const long long p = (long long)blockIdx.z * a.part_rows + modoff + xg;
+                const long long p = (long long)sp * a.part_rows + modoff + xg;
                 const f32x4 st = {m_run, sx, zy, 0.f};
                 *(f32x4*)(a.split_stat + 4 * p) = st;
             }
@@ -588,7 +589,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
     if (MODE == LOCAL && nsplit > 1) {
         // the unnormalised partial sums of this split, for the merge
         if (own && xok) {
-            float* P = a.split_acc + ((long long)blockIdx.z * a.part_rows + modoff + xg) * d;
+            float* P = a.split_acc + ((long long)sp * a.part_rows + modoff + xg) * d;
             each([&](int g, int i, int j) __attribute__((always_inline)) {
                 float o[CV];
 #pragma unroll
@@ -699,7 +700,7 @@ template <typename E, int MODE, int R, int NG, int CW, int YS>
 hipError_t launch_t(const FusedArgs& a, int nmod, hipStream_t s) {
     const bool ll = MODE == LOCAL || MODE == EVAL;
     const int nx = ll ? a.T : a.V;
-    dim3 grid((unsigned)((nx + R - 1) / R), (unsigned)nmod, MODE == LOCAL ? (unsigned)a.nsplit : 1u);
+    dim3 grid((unsigned)((nx + R - 1) / R * (MODE == LOCAL ? a.nsplit : 1)), (unsigned)nmod);
     hipLaunchKernelGGL((k_fused_f32<E, MODE, R, NG, CW, YS>), grid, dim3(NTHR), 0, s, a);
     return hipGetLastError();
 }

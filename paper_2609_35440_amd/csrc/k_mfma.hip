@@ -121,8 +121,8 @@ __device__ __forceinline__ const bf16* tiled_readout_of(const FusedArgs& a, int 
 // MODE LOCAL / EVAL: grid (ceil(T/XR), nmod); MODE RGRAD / BGRAD: grid
 // (ceil(V/XR), nmod); module k = m0 + blockIdx.y.
 // EXT (LOCAL and EVAL): the variant with per-chunk biases, launched when the call has biases.
-// SPL (LOCAL and EVAL): the vocabulary of a row tile is split over the grid's z
-// dimension, and the workgroup leaves its part of every row for the merge
+// SPL (LOCAL and EVAL): the vocabulary of a row tile is split over a.nsplit
+// workgroups, and the workgroup leaves its part of every row for the merge
 // (k_merge.hip).  Exit evaluation then reads the readout row-major, 64 bytes of
 // 16 rows per load: few rows read it, so it comes from memory once and a tiled
 // copy would triple the traffic; and it can take the rows of all modules as one
@@ -181,7 +181,11 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     const int w = threadIdx.x >> 6;
     const int d = a.d;
     const int js = w * DS;
-    const int x0 = blockIdx.x * XR;
+    // (splits next to each other: the grid goes round-robin over the XCDs, whose L2s then
+    // stream a part of the vocabulary each)
+    const int tile = SPL ? (int)blockIdx.x / a.nsplit : (int)blockIdx.x;
+    const int sp = SPL ? (int)blockIdx.x % a.nsplit : 0;
+    const int x0 = tile * XR;
     const int k = flat ? a.K - 1 : a.m0 + (int)blockIdx.y;
     const long long modoff = flat ? 0 : (long long)k * a.T;
     const float tau_k = a.tau ? a.tau[k] : 1.f;
@@ -198,8 +202,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     const int nX = LL ? (flat ? a.K * a.T : a.T) : a.V;
     const int nY = LL ? a.V : a.T;
     const int nchunks = (nY + YC - 1) / YC;
-    const int ck_lo = SPL ? (int)((long long)nchunks * blockIdx.z / a.nsplit) : 0;
-    const int ck_hi = SPL ? (int)((long long)nchunks * (blockIdx.z + 1) / a.nsplit) : nchunks;
+    const int ck_lo = SPL ? (int)((long long)nchunks * sp / a.nsplit) : 0;
+    const int ck_hi = SPL ? (int)((long long)nchunks * (sp + 1) / a.nsplit) : nchunks;
 
     LDS_AS char* sliceA = (LDS_AS char*)(LDS_AS void*)ybufA + w * G::SLICE;
     LDS_AS char* sliceB = (LDS_AS char*)(LDS_AS void*)ybufB + w * G::SLICE;
@@ -585,9 +589,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             if (SPL) {
                 if (lane % LPR == 0 && x0 + xo[r] < nX) {
                     constexpr int SW = MODE == EVAL ? 8 : 4;  // floats per row and split
-                    float* sp = a.split_stat + SW * ((long long)blockIdx.z * a.part_rows + modoff + x0 + xo[r]);
-                    *(f32x4*)sp = (f32x4){m_run[r], sx, zy, bst};
-                    if (MODE == EVAL) *(f32x4*)(sp + 4) = (f32x4){__int_as_float(bv), 0.f, 0.f, 0.f};
+                    float* st = a.split_stat + SW * ((long long)sp * a.part_rows + modoff + x0 + xo[r]);
+                    *(f32x4*)st = (f32x4){m_run[r], sx, zy, bst};
+                    if (MODE == EVAL) *(f32x4*)(st + 4) = (f32x4){__int_as_float(bv), 0.f, 0.f, 0.f};
                 }
                 continue;
             }
@@ -617,7 +621,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         for (int h = 0; h < NR; ++h) {
             const int xg = x0 + 32 * h + ex;
             if (xg >= nX) continue;
-            float* P = a.split_acc + ((long long)blockIdx.z * a.part_rows + modoff + xg) * d;
+            float* P = a.split_acc + ((long long)sp * a.part_rows + modoff + xg) * d;
 #pragma unroll
             for (int b = 0; b < (PC ? G::NB : 1); ++b)
 #pragma unroll
@@ -837,7 +841,7 @@ hipError_t launch_ds(const FusedArgs& a, int nmod, hipStream_t s) {
     if constexpr (MODE == LOCAL || MODE == EVAL) {
         if (a.nsplit > 1 || a.flat) {
             const int rows = a.flat ? a.K * a.T : a.T;
-            const dim3 grid((unsigned)((rows + XR - 1) / XR), a.flat ? 1u : (unsigned)nmod, (unsigned)a.nsplit);
+            const dim3 grid((unsigned)((rows + XR - 1) / XR * a.nsplit), a.flat ? 1u : (unsigned)nmod);
             hipLaunchKernelGGL((k_fused<MODE, DS, EXT, true>), grid, dim3(NTHR), 0, s, a);
             return hipGetLastError();
         }
@@ -851,8 +855,8 @@ hipError_t launch_ds(const FusedArgs& a, int nmod, hipStream_t s) {
 template <int MODE, int DS, bool EXT>
 hipError_t launch_exact_ds(const FusedArgs& a, int nmod, hipStream_t s) {
     constexpr int XR = rows_of<DS, true, true>();
-    const dim3 grid((unsigned)(((MODE == LOCAL ? a.T : a.V) + XR - 1) / XR), (unsigned)nmod,
-                    MODE == LOCAL ? (unsigned)a.nsplit : 1u);
+    const dim3 grid((unsigned)(((MODE == LOCAL ? a.T : a.V) + XR - 1) / XR * (MODE == LOCAL ? a.nsplit : 1)),
+                    (unsigned)nmod);
     if constexpr (MODE == LOCAL) {
         if (a.nsplit > 1) {
             hipLaunchKernelGGL((k_fused<MODE, DS, EXT, true, true>), grid, dim3(NTHR), 0, s, a);

@@ -76,7 +76,7 @@ __device__ __forceinline__ const bf16* readout_of(const FusedArgs& a, int k) {
 // (ceil(V/XR), nmod); module k = m0 + blockIdx.y.
 // XR = 16 with a second product (LOCAL, RGRAD), 48 without (EVAL, BGRAD).
 // EXT (LOCAL and EVAL): the variant with per-chunk biases, launched when the call has biases.
-// SPL (LOCAL and EVAL): the vocabulary split over the grid's z dimension, and
+// SPL (LOCAL and EVAL): the vocabulary split over a.nsplit workgroups, and
 // exit evaluation then row-major and over the rows of all modules (a.flat), as
 // in k_mfma.hip.
 template <int MODE, int DS, bool EXT, bool SPL>
@@ -108,7 +108,11 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int d = a.d;
     const int js = w * DS;
-    const int x0 = blockIdx.x * XR;
+    // (splits next to each other: the grid goes round-robin over the XCDs, whose L2s then
+    // stream a part of the vocabulary each)
+    const int tile = SPL ? (int)blockIdx.x / a.nsplit : (int)blockIdx.x;
+    const int sp = SPL ? (int)blockIdx.x % a.nsplit : 0;
+    const int x0 = tile * XR;
     const int k = flat ? a.K - 1 : a.m0 + (int)blockIdx.y;
     const long long modoff = flat ? 0 : (long long)k * a.T;
     const float tau_k = a.tau ? a.tau[k] : 1.f;
@@ -120,8 +124,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     const int nX = LL ? (flat ? a.K * a.T : a.T) : a.V;
     const int nY = LL ? a.V : a.T;
     const int nchunks = (nY + YC - 1) / YC;
-    const int ck_lo = SPL ? (int)((long long)nchunks * blockIdx.z / a.nsplit) : 0;
-    const int ck_hi = SPL ? (int)((long long)nchunks * (blockIdx.z + 1) / a.nsplit) : nchunks;
+    const int ck_lo = SPL ? (int)((long long)nchunks * sp / a.nsplit) : 0;
+    const int ck_hi = SPL ? (int)((long long)nchunks * (sp + 1) / a.nsplit) : nchunks;
     // this wave's k-step 0 of chunk 0 in the tiled streamed operand; k-step kk
     // of chunk c is 512 kk + 16 d c elements further, the lane's 16 bytes 8 lane
     const bf16* __restrict__ Yw = RM ? Rk :
@@ -390,9 +394,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
             if (SPL) {
                 if (yy == 0 && wr[r] && x0 + xo[r] < nX) {
                     constexpr int SW = MODE == EVAL ? 8 : 4;  // floats per row and split
-                    float* sp = a.split_stat + SW * ((long long)blockIdx.z * a.part_rows + modoff + x0 + xo[r]);
-                    *(f32x4*)sp = (f32x4){m_run[r], sx, zy, bst};
-                    if (MODE == EVAL) *(f32x4*)(sp + 4) = (f32x4){__int_as_float(bv), 0.f, 0.f, 0.f};
+                    float* st = a.split_stat + SW * ((long long)sp * a.part_rows + modoff + x0 + xo[r]);
+                    *(f32x4*)st = (f32x4){m_run[r], sx, zy, bst};
+                    if (MODE == EVAL) *(f32x4*)(st + 4) = (f32x4){__int_as_float(bv), 0.f, 0.f, 0.f};
                 }
                 continue;
             }
@@ -419,7 +423,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
     if (MODE == LOCAL && SPL) {
         // the unnormalised partial sums of this split, for the merge
         if (x0 + ex < nX) {
-            float* P = a.split_acc + ((long long)blockIdx.z * a.part_rows + modoff + x0 + ex) * d;
+            float* P = a.split_acc + ((long long)sp * a.part_rows + modoff + x0 + ex) * d;
 #pragma unroll
             for (int b = 0; b < G::NB; ++b) *(f32x4*)(P + js + 16 * b + 4 * eg) = acc[b];
         }
@@ -542,7 +546,7 @@ hipError_t launch_ds(const FusedArgs& a, int nmod, hipStream_t s) {
     if constexpr (MODE == LOCAL || MODE == EVAL) {
         if (a.nsplit > 1 || a.flat) {
             const int rows = a.flat ? a.K * a.T : a.T;
-            const dim3 sgrid((unsigned)((rows + XR - 1) / XR), a.flat ? 1u : (unsigned)nmod, (unsigned)a.nsplit);
+            const dim3 sgrid((unsigned)((rows + XR - 1) / XR * a.nsplit), a.flat ? 1u : (unsigned)nmod);
             hipLaunchKernelGGL((k_fused_wide<MODE, DS, EXT, true>), sgrid, dim3(NTHR), 0, s, a);
             return hipGetLastError();
         }

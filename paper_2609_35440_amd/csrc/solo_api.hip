@@ -189,11 +189,15 @@ int best_split(long long tiles, long long nch, const SplitCost& c, double max_s,
                int limit = solo::kMaxSplit) {
     int best = 1;
     double best_us = (double)((tiles + 255) / 256) * (double)nch * c.chunk_us;
-    for (int s = 2; s <= limit && s <= nch && s <= max_s && tiles * (s - 1) < 512; ++s) {
+    // (of the s with the same chunks per part the least is best: only those are looked at)
+    for (long long per = nch; per > 1;) {
+        const long long s = (nch + per - 2) / (per - 1);  // the least s with fewer chunks per part
+        if (s > limit || s > max_s || tiles * (s - 1) >= 512) break;
+        per = (nch + s - 1) / s;
         const double us = (double)((tiles * s + 255) / 256) * (double)((nch + s - 1) / s) * c.chunk_us + c.merge_us +
                           s * c.part_us;
         if (us < best_us) {
-            best = s;
+            best = (int)s;
             best_us = us;
         }
     }
@@ -269,7 +273,11 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
     }
     const long long lists = flat ? 1 : K, n = flat ? (long long)K * T : T;  // rows are one list, or one per module
     const long long nvt = ((long long)V + 255) / 256;
-    for (int sp = 1; sp <= solo::kEvalSplits && sp <= nvt; ++sp) {
+    // (as in best_split: the least split of each number of tiles per part)
+    for (long long per = nvt + 1; per > 1;) {
+        const int sp = (int)((nvt + per - 2) / (per - 1));
+        if (sp > solo::kEvalSplits) break;
+        per = (nvt + sp - 1) / sp;
         const double cap = (room - 512.0 - (sp > 1 ? kt * 32.0 * sp : 0.0)) / row_bytes;
         if (cap < (n < 256 ? (double)n : 256.0)) break;
         const long long np0 = (long long)((double)n / cap) + 1;

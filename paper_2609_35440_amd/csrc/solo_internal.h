@@ -68,7 +68,7 @@ struct FusedArgs {
                           // matrix-core families write two bf16 planes, hi = bf16(e) at [0, d) and
                           // lo = bf16(e - hi) at [d, 2d) (the rotate-back product's operand as a 2d-deep
                           // bf16 row); the fp32 family writes e in fp32
-    int nsplit;           // local-loss pass: workgroups the vocabulary of a row tile is split over (grid z)
+    int nsplit;           // local-loss pass: workgroups the vocabulary of a row tile is split over
     long long part_rows;  // nsplit > 1: rows of the arrays of parts, whose pointers are such that a row's entry is
                           // at its global index k T + t
     float* split_acc;     // nsplit > 1: [nsplit][part_rows][d] unnormalised sums of exp(z - m) R_v of each split
