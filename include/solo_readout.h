@@ -87,6 +87,9 @@ const char* solo_status_string(int status);
  * "mfma_wide" family also one tiled bf16 copy of W (V*d*2 bytes, V rounded up
  * to 16), and the same for each distinct heads' readout of the general
  * entry point.  Returns 0 for arguments that solo_readout_fwd_bwd would reject.
+ * (For the bf16 widths outside the matrix-core families the sizes of the
+ * general entry point with dbias and of exit evaluation include copies of rows
+ * that only save time: a workspace short of those alone is accepted.)
  */
 size_t solo_readout_workspace_size(int K, int T, int d, int V, int dtype, int final_module_dW);
 
@@ -98,7 +101,8 @@ size_t solo_readout_workspace_size(int K, int T, int d, int V, int dtype, int fi
  * in the forward-only passes) or
  * "valu" (the fp32 family, for SOLO_F32 and for every other bf16 width: fp32
  * products and sums, on the fp32 matrix instructions; the name is that of the
- * vector-ALU kernels that served these calls first).  Returns "invalid" for arguments solo_readout_fwd_bwd would reject.
+ * vector-ALU kernels that served these calls first).  Returns "invalid" for
+ * arguments solo_readout_fwd_bwd would reject.
  */
 const char* solo_readout_kernel_family(int K, int T, int d, int V, int dtype);
 

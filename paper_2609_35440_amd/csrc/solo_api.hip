@@ -57,8 +57,10 @@ struct Plan {
 bool tiled_readout(const Plan& P) { return P.wide || (P.mfma && P.eval); }
 bool tiled_rgrad(const Plan& P) { return P.wide; }
 
-// Sizes, dtype and flags only (no pointer is dereferenced).
-bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
+// Sizes, dtype and flags only (no pointer is dereferenced).  `spare` false lays
+// the workspace out without the copies that bf16 storage in fp32 can do without.
+bool make_plan(const solo_readout_args& a, bool eval, Plan* P, bool spare = true) {
+    *P = Plan();
     if (a.dtype != SOLO_BF16 && a.dtype != SOLO_F32) return false;
     if (!shape_ok(a.K, a.T, a.d, a.V)) return false;
     if (!flag_ok(a.gain_per_module) || !flag_ok(a.readout_per_head) || !flag_ok(a.final_module_dW) ||
@@ -81,7 +83,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     off = align_up(off + kt * 4);
     // bf16 storage in fp32: the product form of exit evaluation (plane copies of the
     // rows, up to 16384 at a time, and the parts of its splits)
-    P->planes = !P->mfma && a.dtype == SOLO_BF16;
+    P->planes = spare && !P->mfma && a.dtype == SOLO_BF16 && (eval || P->exact);
     if (P->planes && eval) {
         const size_t nvt = ((size_t)a.V + 255) / 256;
         const size_t parts = kt * 32 * (nvt < solo::kEvalSplits ? nvt : solo::kEvalSplits);
@@ -163,7 +165,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P) {
     P->hg = off;
     off = align_up(off + (size_t)(P->hg_hi - P->hg_lo) * (size_t)solo::tiled_elems(T, d) * 2);
     // plane copies of the bias-gradient modules' rows
-    if (P->exact) off = align_up(off + (size_t)(P->bg_hi - P->bg_lo) * T * solo::plane_pitch(d) * 2);
+    if (P->planes) off = align_up(off + (size_t)(P->bg_hi - P->bg_lo) * T * solo::plane_pitch(d) * 2);
     P->rowdtau = off;
     off = align_up(off + (a.dtau ? kt * 4 : 0));
     P->dgp = off;
@@ -354,6 +356,9 @@ int check(const solo_readout_args& a, bool eval, Plan* P) {
         if ((a.gain_per_module || a.final_module_dW) && !aligned(a.dgain, 4)) return SOLO_ERR_ALIGN;
     }
     if (!make_plan(a, eval, P)) return SOLO_ERR_SHAPE;
+    // (a workspace without room for the plane copies still serves: the products
+    // then run on the fp32 kernels, which need none)
+    if (a.workspace_bytes < P->total && P->planes && !make_plan(a, eval, P, false)) return SOLO_ERR_SHAPE;
     if (a.workspace_bytes < P->total) return SOLO_ERR_WORKSPACE;
     return SOLO_OK;
 }
@@ -574,7 +579,7 @@ int run(const solo_readout_args& x, bool eval) {
         return copies(ah, lo, K - 1, as_tiles) && copies(a, K - 1, hi, as_tiles);
     };
     const int nbg = P.bg_hi - P.bg_lo;
-    const int bsplit = !eval && (P.mfma || P.exact) && nbg > 0 ? prod_bgrad_splits(P, nbg, K, T, d, V) : 0;
+    const int bsplit = !eval && (P.mfma || P.planes) && nbg > 0 ? prod_bgrad_splits(P, nbg, K, T, d, V) : 0;
     if (!eval && P.mfma &&
         (!gain_copies(P.rg_lo, P.rg_hi, tiled_rgrad(P)) || !gain_copies(P.bg_lo, P.bg_hi, bsplit == 0)))
         return SOLO_ERR_HIP;

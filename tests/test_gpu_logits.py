@@ -126,3 +126,39 @@ def test_bias_gradient_planes(T, d, V, extras, final):
     if "rot" not in extras:  # (rotated rows are rounded to bf16)
         for k in range(3):
             assert rel_max_err(g["dbias"][k], ref["dbias"][k]) <= 1e-5, k
+
+
+def test_workspace_without_plane_copies(monkeypatch):
+    """The plane copies are a matter of speed: a workspace of the statistics alone serves too,
+    within the same fp32 bounds, and one byte less is refused."""
+    from paper_2609_35440_amd import binding
+
+    al = lambda n: -(-n // 256) * 256
+    K, T, d, V = 2, 300, 72, 1025
+    x = make_extras(make_inputs("1b", seed=14, K=K, T=T, d=d, V=V), seed=14, bias=True)
+    full = run_exit_eval(x)
+    monkeypatch.setattr(binding, "exit_eval_workspace_size", lambda a: 3 * al(K * T * 4))
+    losses, row_loss, top1 = run_exit_eval(x)
+    check_exit_eval(x, losses, row_loss, top1, "eval without copies", min_rows_for_agreement=100)
+    assert np.abs(row_loss - full[1]).max() <= 1e-4 and np.array_equal(top1, full[2])
+    monkeypatch.setattr(binding, "exit_eval_workspace_size", lambda a: 3 * al(K * T * 4) - 1)
+    with pytest.raises(Exception, match="(?i)workspace"):
+        run_exit_eval(x)
+
+    T, d, V = 1025, 136, 1025
+    x = make_extras(make_inputs("1b", seed=15, K=3, T=T, d=d, V=V), seed=15, bias=True, tau=True)
+    flags = dict(final_module_dW=True, want_dtau=True, want_dbias=True)
+    size = binding.general_workspace_size
+
+    def least(a):  # the terminal's bias gradient is free: without dbias there are no copies
+        kept, a.dbias = a.dbias, None
+        n = size(a)
+        a.dbias = kept
+        return n
+
+    monkeypatch.setattr(binding, "general_workspace_size", least)
+    g = run_general(x, flags)
+    ref = oracle_general(x, flags)
+    compare(g, ref, "bf16", flags, "bias gradient without copies")
+    for k in range(3):
+        assert rel_max_err(g["dbias"][k], ref["dbias"][k]) <= 1e-5, k
