@@ -180,7 +180,11 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P, bool spare = true
 // one workgroup per CU, so a launch of `tiles` row tiles, each cut s ways, takes
 // ceil(tiles s / 256) rounds of ceil(chunks / s) chunks; the merge of the parts
 // adds its launch and what it reads and writes.  The rules below take the s
-// with the least of that sum, so a launch whose tiles fill the chip stays whole.
+// with the least of that sum, so a launch whose tiles fill whole rounds stays whole.
+// Up to 1024 parts beside the whole tiles are looked at: 192 tiles (3 x 2048 x
+// 2048) want 4 ways, three full rounds of a quarter: training against V = 32000
+// 2.97 ms whole, 2.47 cut; 320 tiles (5 x 2048) 4.20 and 3.93; 3 x 1024 x 2560 3.40
+// and 2.58; ROT of 4 x 2048 x 2048 4.05 and 3.56.  More cuts gain little more.
 struct SplitCost {
     double chunk_us;    // one chunk of streamed rows of one workgroup
     double merge_us;    // the merge's launch
@@ -194,7 +198,7 @@ int best_split(long long tiles, long long nch, const SplitCost& c, double max_s,
     // (of the s with the same chunks per part the least is best: only those are looked at)
     for (long long per = nch; per > 1;) {
         const long long s = (nch + per - 2) / (per - 1);  // the least s with fewer chunks per part
-        if (s > limit || s > max_s || tiles * (s - 1) >= 512) break;
+        if (s > limit || s > max_s || tiles * (s - 1) >= 1024) break;
         per = (nch + s - 1) / s;
         const double us = (double)((tiles * s + 255) / 256) * (double)((nch + s - 1) / s) * c.chunk_us + c.merge_us +
                           s * c.part_us;

@@ -56,3 +56,25 @@ def test_eval_ties_across_splits():
                           torch.zeros(K, T, dtype=torch.int32, device="cuda"))
     assert int(r.top1[0, 0]) == 70
     assert np.isfinite(r.losses.cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("K,T,d,V", [(3, 2048, 2048, 25600), (1, 2900, 2560, 12000)], ids=["mfma", "wide"])
+def test_more_tiles_than_half_the_chip(K, T, d, V):
+    """Row tiles between half the chip and the whole of it are cut too (192 and 182 tiles, 4 ways).  Against the
+    same rows without a readout gradient, which has no room for parts and is not cut."""
+    import torch
+
+    from paper_2609_35440_amd import binding
+
+    g = torch.Generator(device="cuda").manual_seed(5)
+    h = torch.randn(K, T, d, generator=g, device="cuda").to(torch.bfloat16)
+    W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).to(torch.bfloat16)
+    y = torch.randint(0, V, (K, T), generator=g, device="cuda", dtype=torch.int32)
+    gain = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    cut = binding.readout_fwd_bwd(h, gain, W, y, final_module_dW=True, row_loss=True)
+    whole = binding.readout_fwd_bwd(h, gain, W, y, final_module_dW=False, row_loss=True)
+    # the same fp32 logits; sums of up to 1600 chunks in another order: 2 x 1600 x 2^-24
+    assert float((cut.row_loss - whole.row_loss).abs().max()) <= 2 * 1600 * 2.0**-24
+    # one rounding of each output (2^-8 relative)
+    a, b = cut.dh.float(), whole.dh.float()
+    assert float((a - b).norm() / b.norm()) <= 2.0**-7
