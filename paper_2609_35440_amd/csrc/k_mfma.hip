@@ -334,7 +334,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     float db_part[ER];  // RGRAD / BGRAD: sum_t (p - onehot) for row xo[r]
 #pragma unroll
     for (int r = 0; r < ER; ++r) {
-        m_run[r] = -INFINITY;
+        m_run[r] = kNoMax;
         s_part[r] = zy_part[r] = db_part[r] = 0.f;
         best[r] = -INFINITY;
         best_v[r] = -1;

@@ -26,6 +26,11 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr float kLog2e = 1.44269504088896341f;
 constexpr float kLn2 = 0.693147180559945309f;
 constexpr float kLazyThresh2 = 11.0f;
+// The running maximum of a row that has met no logit above -inf yet, where the
+// elementwise step has no select for masked entries: finite, so that 2^(z - m) of a
+// masked entry (a bias of -inf) is 0 and not 2^(-inf + inf); the first logit past the
+// threshold re-bases it, with a factor of 0 on sums that are 0.
+constexpr float kNoMax = -3.402823466e38f;
 
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
