@@ -369,8 +369,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
         const bf16* hrow = hk + (long long)(xok ? xg : 0) * d;
         const bf16* wrow = Rk + (long long)(tok ? tgt : 0) * d;
         const bool want_dg = a.dg_mode == 2 || (a.dg_mode == 1 && k == a.K - 1);
-        float* dgp = want_dg ? a.dgain_part + ((long long)(a.dg_mode == 2 ? k : 0) * gridDim.x + blockIdx.x) * d
-                             : nullptr;
+        // the gain partials of the tile's two groups of 8 rows
+        const long long ngp = (a.T + kF32GainRows - 1) / kF32GainRows;
+        float* dgp = want_dg ? a.dgain_part + ((a.dg_mode == 2 ? k : 0) * ngp + (x0 + ex) / kF32GainRows) * d : nullptr;
         // e = (acc / s + (p_y - 1) R_y) / T and the row sums of e g n
         float cp = 0.f;
         each([&](int b, int j, bool ok) __attribute__((always_inline)) {
@@ -414,10 +415,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
                 for (int e = 0; e < 4; ++e) {
                     const float n = rx * bf16_bits_to_f32(hv[e]);
                     o[e] = (bf16)(rx * (tau_k * bf16_bits_to_f32(gv[e]) * acc[b][e] - cmean * n));
-                    if (want_dg) pv[e] = row16_sum(tau_k * acc[b][e] * n);  // rx = 0 masks rows past the end
+                    if (want_dg) pv[e] = row8_sum(tau_k * acc[b][e] * n);  // rx = 0 masks rows past the end
                 }
                 if (ok && xok) *(bf16x4*)(dhrow + j) = o;
-                if (want_dg && ok && ex == 0) *(f32x4*)(dgp + j) = pv;
+                if (want_dg && ok && xok && ex % kF32GainRows == 0) *(f32x4*)(dgp + j) = pv;
             });
         }
     }

@@ -649,8 +649,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
             return;
         }
         E* out = (E*)a.dh + (modoff + (xok ? xg : 0)) * (long long)d;
-        float* dgp = want_dg ? a.dgain_part + ((long long)(a.dg_mode == 2 ? k : 0) * gridDim.x + blockIdx.x) * d
-                             : nullptr;
+        // the gain partials of the tile's groups of 8 rows
+        const long long ngp = (a.T + kF32GainRows - 1) / kF32GainRows;
+        float* dgp = want_dg ? a.dgain_part + ((a.dg_mode == 2 ? k : 0) * ngp + (x0 + ln) / kF32GainRows) * d : nullptr;
         each([&](int g, int i, int j) __attribute__((always_inline)) {
             const int jc = j < d ? j : 0;
             float gv[CV], hv[CV], o[CV];
@@ -662,10 +663,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
                 const float dhat = tau * acc[g][e][i];
                 o[e] = rx * (gv[e] * dhat - cmean * n);
                 if (want_dg) {
-                    // the tile's partial of sum_t dhhat_t n_t (rx = 0 masks rows past the end)
-                    float t = row16_sum(dhat * n);
-                    if (R == 32) t += __shfl_xor(t, 16, 64);
-                    if (j < d && ln == 0) dgp[j + e] = t;
+                    // sum_t dhhat_t n_t over 8 rows (rx = 0 masks rows past the end)
+                    const float t = row8_sum(dhat * n);
+                    if (j < d && ln % kF32GainRows == 0 && xok) dgp[j + e] = t;
                 }
             }
             if (j < d && xok) stv<CV>(out + j, o);

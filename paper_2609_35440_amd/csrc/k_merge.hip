@@ -141,8 +141,9 @@ __global__ __launch_bounds__(256) void k_merge(FusedArgs a) {
     }
 }
 
-// The token tiles' partials of dgain = sum_t tau e_t n_t: one thread per four
-// columns of a tile of `rows` tokens.
+// The partials of dgain = sum_t tau e_t n_t over `rows` tokens each: one thread per
+// four columns of a partial.  Summed in 64 bits, as the partials are later on: a chain
+// of up to 64 fp32 sums would cost more bits than the unsplit passes' trees.
 template <typename E>
 __global__ __launch_bounds__(256) void k_merge_dgain(FusedArgs a, int rows) {
     const int k = a.m0 + (int)blockIdx.y;
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(256) void k_merge_dgain(FusedArgs a, int rows) {
     const int t0 = blockIdx.x * rows;
     const int t1 = t0 + rows < a.T ? t0 + rows : a.T;
     const float tau = a.tau ? a.tau[k] : 1.f;
-    f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
+    double s4[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int t = t0; t < t1; ++t) {
         const long long row = (long long)k * a.T + t;
@@ -160,9 +161,10 @@ __global__ __launch_bounds__(256) void k_merge_dgain(FusedArgs a, int rows) {
         const f32x4 ev = *(const f32x4*)(a.split_acc + row * a.d + j);
         const f32x4 hv = ld4((const E*)a.h + row * a.d + j);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s4[e] = __builtin_fmaf(tau * ev[e], r * hv[e], s4[e]);
+        for (int e = 0; e < 4; ++e) s4[e] = __builtin_fma((double)(tau * ev[e]), (double)(r * hv[e]), s4[e]);
     }
-    *(f32x4*)(a.dgain_part + ((long long)(a.dg_mode == 2 ? k : 0) * gridDim.x + blockIdx.x) * a.d + j) = s4;
+    *(f32x4*)(a.dgain_part + ((long long)(a.dg_mode == 2 ? k : 0) * gridDim.x + blockIdx.x) * a.d + j) =
+        (f32x4){(float)s4[0], (float)s4[1], (float)s4[2], (float)s4[3]};
 }
 
 // Exit evaluation split over the vocabulary: the row's loss and top-1 (the

@@ -636,7 +636,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     if (MODE == LOCAL && !SPL) {
         __syncthreads();
         const bool want_dg = a.dg_mode == 2 || (a.dg_mode == 1 && k == a.K - 1);
-        float* dgp = want_dg ? a.dgain_part + ((long long)(a.dg_mode == 2 ? k : 0) * gridDim.x + blockIdx.x) * d
+        // (XA: one partial per 8 rows, see kF32GainRows)
+        const long long ngp = XA ? (a.T + kF32GainRows - 1) / kF32GainRows : gridDim.x;
+        float* dgp = want_dg ? a.dgain_part + ((a.dg_mode == 2 ? k : 0) * ngp +
+                                               (XA ? (x0 + ex) / kF32GainRows : blockIdx.x)) * d
                              : nullptr;
         bool xok[NR], tok[NR];
         float rx[NR];
@@ -787,11 +790,18 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                         const u16x4 hv = *(const u16x4*)(hrow[h] + (XA && j >= d ? 0 : j));  // rx = 0 masks rows past the end
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const float t = row16_sum(tau_k * acc[b][h][4 * i4 + e] * (rx[h] * bf16_bits_to_f32(hv[e])));
-                            pv[e] += t + __shfl_xor(t, 16, 64);
+                            const float n = rx[h] * bf16_bits_to_f32(hv[e]);
+                            if constexpr (XA) {
+                                pv[e] = row8_sum(tau_k * acc[b][h][4 * i4 + e] * n);
+                            } else {
+                                const float t = row16_sum(tau_k * acc[b][h][4 * i4 + e] * n);
+                                pv[e] += t + __shfl_xor(t, 16, 64);
+                            }
                         }
+                        if (XA && j < d && xok[h] && ex % kF32GainRows == 0)
+                            *(f32x4*)(dgp + 32 / kF32GainRows * h * d + j) = pv;
                     }
-                    if (ex == 0 && (!XA || j < d)) *(f32x4*)(dgp + j) = pv;
+                    if (!XA && ex == 0) *(f32x4*)(dgp + j) = pv;
                 }
             }
         }

@@ -251,9 +251,9 @@ __global__ void k_fill_one(E* __restrict__ p, int n) {
 
 // The RMSNorm backward of ROT heads from the rotated-back gradient D = e R_k
 // (fp32, [T][d] per head): dhat = tau D, dn = g * dhat, c = mean(dn * n),
-// dh = r (dn - c n); with a per-module gain also the tile's partial sums of
-// dhat * n (tiles of rows rows, those of the local-loss pass).  One workgroup
-// per tile of one head; wave w takes the tile's rows w, w + 4, ..., one row at
+// dh = r (dn - c n); with a per-module gain also the gain-gradient partials, sums of
+// dhat * n over `rows` rows (as in the local-loss pass).  One workgroup
+// per partial of one head; wave w takes the rows w, w + 4, ..., one row at
 // a time with lane l on columns 4 l + 256 q .. + 3 (a row's mean is a wave reduction:
 // no barrier inside the loop); the row is read twice, the second time from
 // cache.  Each wave sums its gain partials in its own LDS row; the four rows

@@ -36,6 +36,7 @@ struct Plan {
     int dg_mode = 0;           // 0 none, 1 terminal only, 2 every module
     int slots = 0;             // gain-gradient partial slots
     int ntiles = 0;            // token tiles of the local-loss pass
+    int dg_rows = 0;           // token rows per gain-gradient partial: a tile's, or 8 outside the bf16 families
     int rg_lo = 0, rg_hi = 0;  // modules of the readout-gradient pass
     int bg_lo = 0, bg_hi = 0;  // modules of the bias-gradient pass
     int hg_lo = 0, hg_hi = 0;  // modules whose gain-scaled copy the matrix-core gradient passes stream
@@ -108,6 +109,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P, bool spare = true
                                                                             : solo::f32_rows(d)));
     P->rows = rows;
     P->ntiles = (T + rows - 1) / rows;
+    P->dg_rows = P->mfma ? rows : solo::kF32GainRows;
     P->rot = a.rot != nullptr && K > 1;
     if (P->rot) {
         const size_t es = a.dtype == SOLO_BF16 ? 2 : 4;
@@ -169,9 +171,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P, bool spare = true
     P->rowdtau = off;
     off = align_up(off + (a.dtau ? kt * 4 : 0));
     P->dgp = off;
-    // (the fp32 family's partials leave part of their piece unused: it holds one per 8 rows)
-    const size_t dg_tiles = P->mfma ? (size_t)P->ntiles : ((size_t)T + solo::kF32GainRows - 1) / solo::kF32GainRows;
-    off = align_up(off + (size_t)P->slots * dg_tiles * d * 4);
+    off = align_up(off + (size_t)P->slots * (((size_t)T + P->dg_rows - 1) / P->dg_rows) * d * 4);
     P->total = off;
     return true;
 }
@@ -479,7 +479,7 @@ int run(const solo_readout_args& x, bool eval) {
                                                : solo::launch_local_loss_f32(dt, b, n, s);
                 if (e != hipSuccess || b.nsplit == 1) return e;
                 return solo::launch_merge(dt, P.mfma ? solo::MERGE_BF16 : (P.exact ? solo::MERGE_EXACT : solo::MERGE_F32),
-                                          b, n, P.rows, s);
+                                          b, n, P.dg_rows, s);
             }
             case 2:
                 return P.wide    ? solo::launch_readout_grad_mfma_wide(b, n, s)
@@ -557,7 +557,7 @@ int run(const solo_readout_args& x, bool eval) {
             solo::launch_rot_back(dt, P.mfma, ws + P.ebuf, ws + P.rtr, (float*)(ws + P.dbuf), K - 1, T, d, s) !=
                 hipSuccess ||
             solo::launch_rot_post(dt, (const float*)(ws + P.dbuf), x.h, x.gain, a.g_stride, (const float*)(ws + P.rstd),
-                                  x.tau, x.dh, P.dg_mode == 2 ? a.dgain_part : nullptr, K - 1, T, d, P.rows,
+                                  x.tau, x.dh, P.dg_mode == 2 ? a.dgain_part : nullptr, K - 1, T, d, P.dg_rows,
                                   s) != hipSuccess)
             return SOLO_ERR_HIP;
     }
@@ -625,7 +625,7 @@ int run(const solo_readout_args& x, bool eval) {
     if (!eval && (bsplit > 0 ? !prod_bgrad() : !pass_range(3, P.bg_lo, P.bg_hi))) return SOLO_ERR_HIP;
     if (!mark(4)) return SOLO_ERR_HIP;
     if (!eval && P.slots) {
-        if (solo::launch_dgain_reduce(a.dgain_part, x.dgain, P.slots, P.ntiles, d, s) != hipSuccess)
+        if (solo::launch_dgain_reduce(a.dgain_part, x.dgain, P.slots, (T + P.dg_rows - 1) / P.dg_rows, d, s) != hipSuccess)
             return SOLO_ERR_HIP;
     }
     if (!mark(5)) return SOLO_ERR_HIP;

@@ -57,7 +57,7 @@ struct FusedArgs {
     float* rowdtau;       // [K][T] or null: per-token share of d loss / d tau
     int32_t* top1;        // [K][T] or null: exit evaluation, argmax of the logits (lowest index on ties)
     void* dh;             // [K][T][d] elem
-    float* dgain_part;    // [slots][gridDim.x][d]: per-tile partial sums of dhhat * n
+    float* dgain_part;    // [slots][partials][d]: sums of dhhat * n over a row tile, or over 8 rows (kF32GainRows)
     int dg_mode;          // 0: no gain gradient; 1: module K-1 only (slot 0); 2: every module (slot k)
     float* dWt;           // [V][d] or null: d loss_{K-1} / d W
     float* dWh;           // [K-1][V][d] or null: d loss_k / d readout_k of the heads
@@ -80,7 +80,11 @@ struct FusedArgs {
 // Tile sizes of the two kernel families (the workspace depends on them).
 constexpr int kMfmaRows = 32;      // stationary rows per workgroup of the matrix-core kernels at d > 1024
 constexpr int kMfmaWideRows = 16;  // stationary rows per workgroup (wide matrix-core kernels, d = 2560)
-constexpr int kF32GainRows = 8;    // token rows per gain-gradient partial that the fp32 family's workspace is sized for
+// Token rows per gain-gradient partial outside the bf16 families (which write one per row
+// tile): the partials meet in 64 bits, so short ones keep the fp32 part of the sum short.
+// dgain's error against 64 bits (2 x 100 x 72): 1.5e-7 with one partial per tile of 64
+// rows, 8.3e-8 with 8 rows.
+constexpr int kF32GainRows = 8;
 int f32_rows(int d);               // stationary rows per workgroup of the fp32 kernels at width d (32 or 16)
 
 // small kernels (k_small.hip)
@@ -158,8 +162,8 @@ hipError_t launch_readout_grad_mfma_wide(const FusedArgs& a, int nmod, hipStream
 hipError_t launch_bias_grad_mfma_wide(const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_local_loss_f32(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
 hipError_t launch_exit_eval_f32(int dtype, const FusedArgs& a, int nmod, hipStream_t s);
-// the tokens' ends of a local-loss pass split over the vocabulary, modules m0 .. m0 + nmod - 1, gain partials
-// per tile of rows tokens (k_merge.hip)
+// the tokens' ends of a local-loss pass split over the vocabulary, modules m0 .. m0 + nmod - 1, one gain
+// partial per `rows` tokens (k_merge.hip)
 // (form: what the form's gradient passes read, see k_merge)
 enum MergeForm { MERGE_BF16 = 0, MERGE_F32 = 1, MERGE_EXACT = 2 };
 hipError_t launch_merge(int dtype, MergeForm form, const FusedArgs& a, int nmod, int rows, hipStream_t s);
