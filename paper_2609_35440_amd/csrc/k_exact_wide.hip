@@ -192,7 +192,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
     f32x4 acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, s_part = 0.f, zy_part = 0.f, db_part = 0.f;
+    float m_run = -INFINITY, s_part = 0.f, zy_part = 0.f;
+    double db_part = 0.0;  // (a lane's share of a sum over all tokens)
 
     auto step = [&](LDS_AS float* side, unsigned side_nxt, int c) __attribute__((always_inline)) {
         const int y0 = c * YC;
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
         }
     }
     if (!LL) {
-        const float db = row16_sum(db_part);
+        const float db = row16_sum((float)db_part);
         if (a.dbias && yy == 0 && wr && x0 + xo < nX) a.dbias[(long long)k * a.V + x0 + xo] = db * a.inv_T;
         const int v = x0 + ex;
         float* dwrow = ((k == a.K - 1) ? a.dWt : a.dWh + (long long)k * a.V * d) + (long long)(v < nX ? v : 0) * d;

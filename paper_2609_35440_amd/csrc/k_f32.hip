@@ -267,7 +267,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
     const int cg = w % NCG, ysub = w / NCG;
     const int js = cg * (R * CW * NG);
 
-    float m_run = -INFINITY, s_part = 0.f, zy_part = 0.f, db_part = 0.f;
+    float m_run = -INFINITY, s_part = 0.f, zy_part = 0.f;
+    double db_part = 0.0;  // (a sum over all tokens: four at a time in fp32, then in 64 bits)
     float best = -INFINITY;
     int best_v = -1;
 
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
 #pragma unroll
                 for (int i4 = 0; i4 < NR / 4; ++i4) {
                     const int yl = ylow + b * R + 8 * i4 + 4 * kq;
-                    f32x4 g;
+                    f32x4 g, dl;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const f32x4 r4 = *(const f32x4*)(rec + 4 * (yl + e));
@@ -422,10 +423,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
                                         recs[yl + e];
                         // tokens past the end are masked; the target's entry of delta is the
                         // exact p_y - 1 of the local-loss pass
-                        const float dl = yl + e < rows ? (__float_as_int(r4[2]) == xg ? r4[3] : p) : 0.f;
-                        db_part += dl;
-                        g[e] = dl * (r4[1] * (kLn2 * a.inv_T));  // times r tau / T
+                        dl[e] = yl + e < rows ? (__float_as_int(r4[2]) == xg ? r4[3] : p) : 0.f;
+                        g[e] = dl[e] * (r4[1] * (kLn2 * a.inv_T));  // times r tau / T
                     }
+                    db_part += (double)((dl[0] + dl[1]) + (dl[2] + dl[3]));
                     if (PC) *(f32x4*)(gbuf + ln * YC + 4 * ((yl >> 2) ^ (ln & 7))) = g;
                 }
         }
@@ -675,13 +676,13 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
         // bias gradient of the stationary readout rows
 #pragma unroll
         for (int off = R; off < 64; off <<= 1) db_part += __shfl_xor(db_part, off, 64);
-        if (lane < R) wred[w * R + ln] = db_part;
+        if (lane < R) wred[w * R + ln] = (float)db_part;
         __syncthreads();
         if (a.dbias && w == 0 && lane < R && xok) {
-            float db = 0.f;
+            double db = 0.0;
 #pragma unroll
-            for (int ww = 0; ww < NW; ++ww) db += wred[ww * R + ln];
-            a.dbias[(long long)k * a.V + xg] = db * a.inv_T;
+            for (int ww = 0; ww < NW; ++ww) db += (double)wred[ww * R + ln];
+            a.dbias[(long long)k * a.V + xg] = (float)db * a.inv_T;
         }
     }
     if (MODE == RGRAD && own && xok) {

@@ -201,6 +201,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
 
     // ---- per-lane state of X rows x0 + 64 wn + 32 j + l32, j = 0, 1
     float r2[2], m_run[2], sum[2], zy[2], best[2], bx2[2];
+    double dsum[2] = {0.0, 0.0};  // BGRAD
     int tgt[2], best_v[2];
     long long grow[2];
 #pragma unroll
@@ -317,7 +318,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 4; ++i) {
+                // a lane's 16 tokens of a block in fp32, pairs first, then in 64 bits: one
+                // chain over its T / 4 tokens lost up to 2.7 times the fp32 kernels' bits
+                float blk[2] = {0.f, 0.f}, dl[2][4];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     // record {lse log2 e, r tau log2 e, target, p_y - 1}; the target's entry
@@ -328,10 +332,13 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][e], r4[1], bx2[j] - r4[0]));
-                        const float dl = __float_as_int(r4[2]) == tgt[j] ? r4[3] : p;
-                        sum[j] += in ? dl : 0.f;
+                        dl[j][e & 3] = in ? (__float_as_int(r4[2]) == tgt[j] ? r4[3] : p) : 0.f;
+                        if ((e & 3) == 3) blk[j] += (dl[j][0] + dl[j][1]) + (dl[j][2] + dl[j][3]);
                     }
                 }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) dsum[j] += (double)blk[j];
+            }
         }
         zero();
     }
@@ -343,8 +350,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     for (int j = 0; j < 2; ++j) {
         const int xl = 64 * wn + 32 * j + l32;
         if (MODE == BGRAD) {
-            sum[j] += __shfl_xor(sum[j], 32, 64);
-            if (hi == 0) red[wm * BT + xl] = sum[j];
+            dsum[j] += __shfl_xor(dsum[j], 32, 64);
+            if (hi == 0) red[wm * BT + xl] = (float)dsum[j];
             continue;
         }
         // a lane that saw no finite logit has no maximum
@@ -410,9 +417,9 @@ __global__ void k_db_sum(const float* __restrict__ parts, float* __restrict__ ou
                          float inv_T) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    float s = 0.f;
-    for (int k = 0; k < nsplit - 1; ++k) s += parts[k * n + i];
-    out[i] = (s + out[i]) * inv_T;
+    double s = out[i];
+    for (int k = 0; k < nsplit - 1; ++k) s += (double)parts[k * n + i];
+    out[i] = (float)s * inv_T;
 }
 
 template <int MODE, bool EXT, bool XA>

@@ -49,6 +49,8 @@
 // would still have to be written to LDS for the transposing read, and those
 // ds_write_b128 measured slower than the direct-to-LDS stream and the
 // row-wise reads together at d = 2048, so those passes keep the stream.
+#include <type_traits>
+
 #include "mfma_common.h"
 
 namespace solo {
@@ -331,11 +333,14 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
     float m_run[ER], s_part[ER], zy_part[ER];
     float best[ER];   // EVAL: largest logit seen by this lane, and its column
     int best_v[ER];
-    float db_part[ER];  // RGRAD / BGRAD: sum_t (p - onehot) for row xo[r]
+    // RGRAD / BGRAD: sum_t (p - onehot) for row xo[r] (the exact form: in 64 bits, as a lane's
+    // chain of T / 8 sums in fp32 is longer than that of the fp32 kernels)
+    typename std::conditional<XA && !LL, double, float>::type db_part[ER];
 #pragma unroll
     for (int r = 0; r < ER; ++r) {
         m_run[r] = kNoMax;
-        s_part[r] = zy_part[r] = db_part[r] = 0.f;
+        s_part[r] = zy_part[r] = 0.f;
+        db_part[r] = 0;
         best[r] = -INFINITY;
         best_v[r] = -1;
     }
@@ -462,6 +467,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                     }
                     if (MODE == LOCAL) abuf[xo[r]] = alpha;  // the lanes of a row store the same value
                 } else {
+                    float dsum = 0.f;
 #pragma unroll
                     for (int e = 0; e < EWC; ++e) {
                         // record {lse log2 e, r tau log2 e, target, p_y - 1}; tokens past
@@ -473,8 +479,13 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                         const float dlt =
                             (yy + e < ylim) ? (__float_as_int(r4[2]) == x0 + xo[r] ? r4[3] : p) : 0.f;
                         gval[e] = dlt * (r4[1] * (kLn2 * a.inv_T));  // times r tau / T
-                        db_part[r] += dlt;
+                        if (XA) {
+                            dsum += dlt;
+                        } else {
+                            db_part[r] += dlt;
+                        }
                     }
+                    if (XA) db_part[r] += dsum;
                 }
                 if (PC) {
 #pragma unroll
@@ -810,7 +821,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         // bias gradient of the stationary readout rows: sum over the lanes of the row
 #pragma unroll
         for (int r = 0; r < ER; ++r) {
-            const float db = group_sum<LPR>(db_part[r]);
+            const float db = group_sum<LPR>((float)db_part[r]);
             if (a.dbias && lane % LPR == 0 && x0 + xo[r] < nX)
                 a.dbias[(long long)k * a.V + x0 + xo[r]] = db * a.inv_T;
         }

@@ -33,3 +33,26 @@ def test_gain_gradient(dtype, d):
     r = binding.readout_general(h, gain.repeat(2, 1), W, y)
     assert torch.isfinite(r.dgain).all() and float(r.dgain.abs().max()) > 0
     assert torch.equal(r.dgain[0], 8 * r.dgain[1])
+
+
+@pytest.mark.parametrize("T,V", [(4096, 600), (100, 40)], ids=["many", "few"])
+@pytest.mark.parametrize("dtype,d", FORMS, ids=[f"{a}-{b}" for a, b in FORMS])
+def test_bias_gradient(dtype, d, T, V):
+    """T equal tokens: db_v = p_v (less one at the target), of the head (the bias-gradient
+    pass) and, outside the bf16 families, of the terminal (the readout-gradient pass).  A chain of n equal terms in fp32
+    is off by up to n 2^-25; what is allowed is the error of one p: its log-sum-exp, about
+    9 + log2(8) in base 2, stored with 24 bits (2^-21 ln 2 at most), and the rounding and
+    sums of logits below 1 in magnitude, 2^-24 each over up to d / 16 steps of one sum."""
+    import torch
+
+    from paper_2609_35440_amd import binding
+
+    h, gain, W, y = _inputs(2, T, d, V, dtype)
+    r = binding.readout_general(h, gain, W, y, want_dbias=True)
+    z = (h[0, 0].double() * torch.rsqrt(h[0, 0].double().square().mean() + 1e-6)) @ W.double().t()
+    p = torch.softmax(z, 0)
+    p[3] -= 1.0
+    tol = 2.0**-21 + (8 + d / 16) * 2.0**-24
+    for k in range(1 if dtype == "bf16" and d % 256 == 0 else 2):
+        err = ((r.dbias[k].double() - p) / p).abs().max()
+        assert float(err) <= tol, (k, float(err), tol)
