@@ -336,7 +336,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
                     *(f32x4*)(a.split_stat + 4 * ((long long)sp * a.part_rows + modoff + xr_)) =
                         (f32x4){m_run, sx, zy, 0.f};
             } else {
-                const RowEnd re = finish_row(m_run, sx, zy, own_tgt >= 0 && own_tgt < nY);
+                const RowEnd re = finish_row<true>(m_run, sx, zy, own_tgt >= 0 && own_tgt < nY);
                 if (xr_ < nX) {
                     const long long t = modoff + xr_;
                     a.lse[t] = 1.f;  // (the bias-gradient pass of these widths scales by it)

@@ -539,7 +539,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
             }
         } else if (w == 0 && lane < R) {
             const bool tok = own_tgt >= 0 && own_tgt < nY;
-            const RowEnd re = finish_row(m_run, sx, zy, tok);
+            const RowEnd re = finish_row<true>(m_run, sx, zy, tok);
             if (xok) {
                 const long long t = modoff + xg;
                 a.rowloss[t] = re.loss;

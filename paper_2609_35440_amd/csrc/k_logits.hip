@@ -403,7 +403,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     const long long row = a.row0 + x;
     if (S == 1) {
         const int ty = a.targets[row];
-        a.rowloss[row] = finish_row(m, sa + sb, z, ty >= 0 && ty < a.nY).loss;
+        a.rowloss[row] = finish_row<XA>(m, sa + sb, z, ty >= 0 && ty < a.nY).loss;
         if (a.top1) a.top1[row] = v0;
     } else {
         float* p = a.parts + 8 * (sp * a.part_rows + row);

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void k_merge(FusedArgs a) {
     }
     const int tgt = a.targets[row];
     const bool tok = tgt >= 0 && tgt < a.V;
-    const RowEnd re = finish_row(m, sx, zy, tok);
+    const RowEnd re = finish_row<FORM != MERGE_BF16>(m, sx, zy, tok);
     const float r = a.rstd[row];
     if (threadIdx.x == 0) {
         a.rowloss[row] = re.loss;
@@ -169,6 +169,7 @@ __global__ __launch_bounds__(256) void k_merge_dgain(FusedArgs a, int rows) {
 
 // Exit evaluation split over the vocabulary: the row's loss and top-1 (the
 // larger logit, then the lower column) from the splits' parts; one row per wave.
+template <bool FINE>
 __global__ __launch_bounds__(256) void k_merge_eval(FusedArgs a, long long rows) {
     const int lane = threadIdx.x & 63;
     const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(256) void k_merge_eval(FusedArgs a, long long rows)
     }
     if (lane == 0) {
         const int tgt = a.targets[row];
-        a.rowloss[row] = finish_row(m, sx, zy, tgt >= 0 && tgt < a.V).loss;
+        a.rowloss[row] = finish_row<FINE>(m, sx, zy, tgt >= 0 && tgt < a.V).loss;
         if (a.top1) a.top1[row] = best_v;
     }
 }
@@ -230,8 +231,13 @@ hipError_t launch_t(const FusedArgs& a, int nmod, int rows, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_merge_eval(const FusedArgs& a, long long rows, hipStream_t s) {
-    hipLaunchKernelGGL(k_merge_eval, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, a, rows);
+hipError_t launch_merge_eval(const FusedArgs& a, bool fine, long long rows, hipStream_t s) {
+    const dim3 grid((unsigned)((rows + 3) / 4));
+    if (fine) {
+        hipLaunchKernelGGL(k_merge_eval<true>, grid, dim3(256), 0, s, a, rows);
+    } else {
+        hipLaunchKernelGGL(k_merge_eval<false>, grid, dim3(256), 0, s, a, rows);
+    }
     return hipGetLastError();
 }
 

@@ -609,7 +609,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             if (lane % LPR == 0) {
                 const int xr_ = x0 + xo[r];
                 const bool tok = own_tgt >= 0 && own_tgt < nY;
-                const RowEnd re = finish_row(m_run[r], sx, zy, tok);
+                const RowEnd re = finish_row<XA>(m_run[r], sx, zy, tok);
                 if (xr_ < nX) {
                     const long long t = modoff + xr_;
                     a.lse[t] = XA ? 1.f : re.lse2 * kLn2;  // (the fp32 family's gradient passes scale by it)

@@ -403,7 +403,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_wide(FusedArgs a) {
             if (yy == 0 && wr[r]) {
                 const int xr_ = x0 + xo[r];
                 const bool tok = own_tgt[r] >= 0 && own_tgt[r] < nY;
-                const RowEnd re = finish_row(m_run[r], sx, zy, tok);
+                const RowEnd re = finish_row<false>(m_run[r], sx, zy, tok);
                 if (xr_ < nX) {
                     const long long t = modoff + xr_;
                     a.lse[t] = re.lse2 * kLn2;

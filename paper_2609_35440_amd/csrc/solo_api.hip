@@ -547,7 +547,7 @@ int run(const solo_readout_args& x, bool eval) {
     if (E.form == EvalPlan::PROD ? !prod_eval() : !pass_range(eval ? 0 : 1, 0, K)) return SOLO_ERR_HIP;
     if (E.nsplit > 1) {
         a.nsplit = E.nsplit;
-        if (solo::launch_merge_eval(a, (long long)K * T, s) != hipSuccess) return SOLO_ERR_HIP;
+        if (solo::launch_merge_eval(a, !P.mfma, (long long)K * T, s) != hipSuccess) return SOLO_ERR_HIP;
         a.nsplit = 1;
     }
     if (P.rot && !eval) {

@@ -169,7 +169,8 @@ enum MergeForm { MERGE_BF16 = 0, MERGE_F32 = 1, MERGE_EXACT = 2 };
 hipError_t launch_merge(int dtype, MergeForm form, const FusedArgs& a, int nmod, int rows, hipStream_t s);
 constexpr int kMaxSplit = 64;     // splits of one row tile (a lane of the merge each)
 constexpr int kEvalSplits = 256;  // the same in exit evaluation
-hipError_t launch_merge_eval(const FusedArgs& a, long long rows, hipStream_t s);
+// (fine: see finish_row)
+hipError_t launch_merge_eval(const FusedArgs& a, bool fine, long long rows, hipStream_t s);
 // ROT (k_rot.hip): C = A B^T per matrix; transposes; a vector of ones; the
 // heads' RMSNorm backward from the rotated-back gradient D = e R_k
 // u[m] = bf16(R_m bf16(g_m * h_m)) per row, heads m < nmat (gain g_m at gain + m g_stride)

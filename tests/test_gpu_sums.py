@@ -56,3 +56,32 @@ def test_bias_gradient(dtype, d, T, V):
     for k in range(1 if dtype == "bf16" and d % 256 == 0 else 2):
         err = ((r.dbias[k].double() - p) / p).abs().max()
         assert float(err) <= tol, (k, float(err), tol)
+
+
+@pytest.mark.parametrize("op", ["train", "eval"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 48), ("bf16", 200), ("bf16", 640), ("bf16", 1800), ("f32", 264)],
+                         ids=["bf16-48", "bf16-200", "bf16-640", "bf16-1800", "f32-264"])
+def test_row_losses_are_not_biased(op, dtype, d):
+    """Calls defined in fp32: a row loss near 8 rounds by at most 2.4e-7, the sums before it by
+    as much, to either side.  The mean over 2048 rows is then within 5e-7 / sqrt(2048) = 1.1e-8
+    of the truth, one standard error; ten are allowed (a logarithm that reads half a unit low
+    is off by 3e-7)."""
+    import torch
+
+    from paper_2609_35440_amd import binding
+
+    K, T, V = 2, 1024, 2001
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(6)
+    h = torch.randn(K, T, d, generator=g, device="cuda").to(dt)
+    W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).to(dt)
+    y = torch.randint(0, V, (K, T), generator=g, device="cuda", dtype=torch.int32)
+    gain = (1 + 0.1 * torch.randn(d, generator=g, device="cuda")).to(dt)
+    if op == "train":
+        got = binding.readout_fwd_bwd(h, gain, W, y, row_loss=True).row_loss
+    else:
+        got = binding.exit_eval(h, gain, W, y).row_loss
+    n = h.double() * torch.rsqrt(h.double().square().mean(2, keepdim=True) + 1e-6)
+    z = (n * gain.double()) @ W.double().t()
+    ref = torch.logsumexp(z, 2) - z.gather(2, y.long()[..., None])[..., 0]
+    assert abs(float((got.double() - ref).mean())) <= 1.1e-7
