@@ -63,12 +63,19 @@ __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(
 
 // XA: logits exact to fp32, for the bf16 widths whose calls are defined in fp32:
 // one operand is the copy of g * h (16 significant bits) as two bf16 planes side by side,
-// rows of 2 dp elements (dp = d rounded up to 64, zeros past d), and the readout
+// rows of 2 dp elements (dp = d rounded up to 64, zeros past d; the lower plane first,
+// so that only the upper one's sums round at the logit's size), and the readout
 // is read once per plane; its columns past d read as zeros.
-template <int MODE, bool EXT, bool XA>
+// NI: 32-row blocks of Y per wave.  4, or 2 for XA past d = 2560: tiles of 128 rows of Y, whose
+// accumulators leave room for a second set, so that the k-sum is cut into pieces of 512.
+template <int MODE, bool EXT, bool XA, int NI>
 __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
-    __shared__ __attribute__((aligned(16))) char sA0[STAGE];
-    __shared__ __attribute__((aligned(16))) char sA1[STAGE];
+    constexpr int BY = 64 * NI;       // rows of a tile of Y
+    constexpr int WY = 32 * NI;       // rows of Y per wave
+    constexpr bool CUT = NI < 4;      // the k-sum in pieces
+    constexpr int STA = BY * BK * 2;  // bytes of a stage of Y
+    __shared__ __attribute__((aligned(16))) char sA0[STA];
+    __shared__ __attribute__((aligned(16))) char sA1[STA];
     __shared__ __attribute__((aligned(16))) char sB0[STAGE];
     __shared__ __attribute__((aligned(16))) char sB1[STAGE];
     // side data of a tile of Y, two tiles in turn: its biases (exit evaluation) or token records
@@ -88,7 +95,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     const bf16* __restrict__ X = a.X + mod * a.x_stride + (mod == a.x_last ? a.x_last_off : 0);
     const bf16* __restrict__ Y = a.Y + mod * a.y_stride;
     const int x0 = xt * BT;
-    const int nt = (a.nY + BT - 1) / BT;
+    const int nt = (a.nY + BY - 1) / BY;
     const int t_lo = (int)((long long)nt * sp / S), t_hi = (int)((long long)nt * (sp + 1) / S);
     // stages per tile: an even number (d % 256 == 0, or two planes)
     const int nkd = (d + BK - 1) / BK;
@@ -102,23 +109,24 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     LDS_AS char* const pB0 = (LDS_AS char*)(LDS_AS void*)sB0;
     LDS_AS char* const pB1 = (LDS_AS char*)(LDS_AS void*)sB1;
 
-    // ---- stream: instruction i of wave w fills rows 32 w + 8 i .. + 7 of a stage
+    // ---- stream: instruction i of wave w fills rows 32 w + 8 i .. + 7 of a stage of X, and
+    // rows 8 NI w + 8 i .. + 7 of one of Y
     const int gr = (lane & 7) ^ (lane >> 3);  // the lane's granule of a row
-    int voA[4], voB[4];
+    int voA[NI], voB[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        voA[i] = (32 * w + 8 * i + (lane >> 3)) * dY * 2 + 16 * gr;
-        voB[i] = XA ? (32 * w + 8 * i + (lane >> 3)) * dX * 2 + 16 * gr : voA[i];
-    }
-    auto rows_rsrc = [&](const bf16* __restrict__ P, int n, int r0, int pitch) __attribute__((always_inline)) {
-        const int rows = n - r0 < BT ? n - r0 : BT;
+    for (int i = 0; i < NI; ++i) voA[i] = (8 * NI * w + 8 * i + (lane >> 3)) * dY * 2 + 16 * gr;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        voB[i] = XA ? (32 * w + 8 * i + (lane >> 3)) * dX * 2 + 16 * gr : voA[i < NI ? i : 0];
+    auto rows_rsrc = [&](const bf16* __restrict__ P, int n, int r0, int pitch, int most) __attribute__((always_inline)) {
+        const int rows = n - r0 < most ? n - r0 : most;
         return make_rsrc(P + (long long)r0 * pitch, (unsigned)rows * (unsigned)pitch * 2u);
     };
-    const i32x4 brs = rows_rsrc(X, a.nX, x0, dX);
-    const unsigned uA[2] = {lds_addr(pA0) + w * 4096, lds_addr(pA1) + w * 4096};
+    const i32x4 brs = rows_rsrc(X, a.nX, x0, dX, BT);
+    const unsigned uA[2] = {lds_addr(pA0) + w * (STA / NW), lds_addr(pA1) + w * (STA / NW)};
     const unsigned uB[2] = {lds_addr(pB0) + w * 4096, lds_addr(pB1) + w * 4096};
     int it = t_lo, ik = 0;  // the next stage to stream
-    i32x4 ars = rows_rsrc(Y, a.nY, t_lo * BT, dY);
+    i32x4 ars = rows_rsrc(Y, a.nY, t_lo * BY, dY, BY);
     auto issue = [&](int buf) __attribute__((always_inline)) {
         if (it >= t_hi) return;
         // XA: the readout's k of this stage, and whether the lane's granule of it is past d
@@ -126,7 +134,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
         const bool past = XA && kr * BK + 8 * gr >= d;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            buffer_load_lds16s(ars, uA[buf] + i * 1024, MODE == EVAL && past ? 0x40000000 : voA[i],
+            if (i < NI) buffer_load_lds16s(ars, uA[buf] + i * 1024, MODE == EVAL && past ? 0x40000000 : voA[i < NI ? i : 0],
                                (MODE == EVAL ? kr : ik) * (BK * 2));
             buffer_load_lds16s(brs, uB[buf] + i * 1024, MODE == BGRAD && past ? 0x40000000 : voB[i],
                                (MODE == EVAL ? ik : kr) * (BK * 2));
@@ -135,18 +143,18 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
             // the tile's side data, long before its end: every wave has left the
             // tile before the last by now
             const unsigned ds = lds_addr((LDS_AS char*)(LDS_AS void*)side[it & 1]);
-            const int y0 = it * BT;
-            const int rows = a.nY - y0 < BT ? a.nY - y0 : BT;
-            if (MODE == BGRAD && w < 4)
+            const int y0 = it * BY;
+            const int rows = a.nY - y0 < BY ? a.nY - y0 : BY;
+            if (MODE == BGRAD && w < NI)
                 buffer_load_lds16(make_rsrc(a.rowrec + 4 * (mod * (long long)a.nY + y0), (unsigned)rows * 16u),
                                   ds + w * 1024, (64 * w + lane) * 16);
-            if (MODE == EVAL && EXT && w < 4)
+            if (MODE == EVAL && EXT && w < NI)
                 buffer_load_lds4(make_rsrc(a.bias + y0, (unsigned)rows * 4u), ds + w * 256, (64 * w + lane) * 4);
         }
         if (++ik == nk) {
             ik = 0;
             ++it;
-            if (it < t_hi) ars = rows_rsrc(Y, a.nY, it * BT, dY);
+            if (it < t_hi) ars = rows_rsrc(Y, a.nY, it * BY, dY, BY);
         }
     };
 
@@ -154,25 +162,35 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     int go[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) go[s] = l32 * 128 + 16 * ((2 * s + hi) ^ (lane & 7));
-    bf16x8 fa[2][4], fb[2][2];
+    bf16x8 fa[2][NI], fb[2][2];
     auto read = [&](LDS_AS const char* A, LDS_AS const char* B, int s, int q) __attribute__((always_inline)) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) fb[q][b] = *(LDS_AS const bf16x8*)(B + (64 * wn + 32 * b) * 128 + go[s]);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) fa[q][b] = *(LDS_AS const bf16x8*)(A + (128 * wm + 32 * b) * 128 + go[s]);
+        for (int b = 0; b < NI; ++b) fa[q][b] = *(LDS_AS const bf16x8*)(A + (WY * wm + 32 * b) * 128 + go[s]);
     };
-    f32x16 acc[4][2];
+    f32x16 acc[NI][2];
+    f32x16 tot[CUT ? NI : 1][2];  // CUT: the sum of the pieces before this one
     auto zero = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
     };
-    auto mul = [&](int q, int b0) __attribute__((always_inline)) {
+    auto add_piece = [&](bool first) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = b0; i < b0 + 2; ++i)
+        for (int i = 0; i < (CUT ? NI : 1); ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) tot[i][j][e] = first ? acc[i][j][e] : tot[i][j][e] + acc[i][j][e];
+    };
+    // (the products of half of the blocks)
+    auto mul = [&](int q, int half) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = half * (NI / 2); i < (half + 1) * (NI / 2); ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j) acc[i][j] = mfma32(fa[q][i], fb[q][j], acc[i][j]);
     };
@@ -186,7 +204,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
         for (int s = 0; s < 3; ++s) {
             read(A, B, s + 1, (s + 1) & 1);
             mul(s & 1, 0);
-            mul(s & 1, 2);
+            mul(s & 1, 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         mul(1, 0);
@@ -195,7 +213,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
         lds_barrier();  // everyone's; and everyone has read this one
         issue(buf);
         read(An, Bn, 0, 0);
-        mul(1, 2);
+        mul(1, 1);
         __builtin_amdgcn_sched_barrier(0);
     };
 
@@ -227,26 +245,39 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     __syncthreads();
     read(pA0, pB0, 0, 0);
     for (int t = t_lo; t < t_hi; ++t) {
+#pragma nounroll
         for (int kt = 0; kt < nk; kt += 2) {
             stage(0);
             stage(1);
+            if (CUT && kt % 8 == 6 && kt + 2 < nk) {
+                add_piece(kt < 8);
+                zero();
+            }
+        }
+        if (CUT && nk > 8) {
+#pragma unroll
+            for (int i = 0; i < (CUT ? NI : 1); ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] += tot[i][j][e];
         }
         // ---- the tile's end.  acc[i][j][e]: row y = yb + 32 i + 8 (e / 4) + 4 hi + e % 4 of Y,
-        // yb = 256 t + 128 wm; column: the lane's X row j
-        const int yb = t * BT + 128 * wm;
-        const bool ragged = t * BT + BT > a.nY;  // wave-uniform
+        // yb = BY t + WY wm; column: the lane's X row j
+        const int yb = t * BY + WY * wm;
+        const bool ragged = t * BY + BY > a.nY;  // wave-uniform
         LDS_AS const float* sd = (LDS_AS const float*)(LDS_AS void*)side[t & 1];
         if (MODE == EVAL) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 float zmax = -INFINITY;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < NI; ++i)
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         const int yl = 32 * i + 8 * g + 4 * hi;
                         f32x4 bv = {0.f, 0.f, 0.f, 0.f};
-                        if (EXT) bv = *(LDS_AS const f32x4*)(sd + 128 * wm + yl);
+                        if (EXT) bv = *(LDS_AS const f32x4*)(sd + WY * wm + yl);
                         float z[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
@@ -260,7 +291,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
                     // rows past the end: z = -inf
                     zmax = -INFINITY;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
+                    for (int i = 0; i < NI; ++i) {
                         const int left = a.nY - (yb + 32 * i + 4 * hi);
 #pragma unroll
                         for (int e = 0; e < 16; ++e) {
@@ -274,7 +305,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
                 if (__any(zmax > best[j])) {
                     int at = 0;
 #pragma unroll
-                    for (int i = 3; i >= 0; --i) {
+                    for (int i = NI - 1; i >= 0; --i) {
 #pragma unroll
                         for (int e = 15; e >= 0; --e)
                             at = acc[i][j][e] == zmax ? 32 * i + 8 * (e >> 2) + (e & 3) : at;
@@ -285,17 +316,22 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
                     best[j] = fmaxf(best[j], zmax);
                 }
                 // the running maximum is the lane's own; it is re-based past the
-                // threshold, and as long as it has no term yet
-                if (zmax > m_run[j] + kLazyThresh2 || (sum[j] == 0.f && zmax > -INFINITY)) {
-                    sum[j] = sum[j] == 0.f ? 0.f : sum[j] * __builtin_amdgcn_exp2f(m_run[j] - zmax);
-                    m_run[j] = zmax;
+                // threshold, and as long as it has no term yet (selects under a branch that the
+                // wave takes as one: of a lane's branch with both conditions, the compiler kept
+                // only the first one's maximum past the loop in the two-block form)
+                const bool none = sum[j] == 0.f;
+                const bool up = (zmax > m_run[j] + kLazyThresh2) | (none & (zmax > -INFINITY));
+                if (__any(up)) {
+                    const float scaled = none ? 0.f : sum[j] * __builtin_amdgcn_exp2f(m_run[j] - zmax);
+                    sum[j] = up ? scaled : sum[j];
+                    m_run[j] = up ? zmax : m_run[j];
                 }
                 float s0 = 0.f, s1 = 0.f;
                 const int rel = tgt[j] - yb - 4 * hi;
-                if (__any(rel >= 0 && rel < 128)) {
+                if (__any(rel >= 0 && rel < WY)) {
                     // some row's target is in the tile: its term stays out of the sum (finish_row)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
+                    for (int i = 0; i < NI; ++i) {
 #pragma unroll
                         for (int e = 0; e < 16; ++e) {
                             const bool is_y = rel == 32 * i + 8 * (e >> 2) + (e & 3);
@@ -307,7 +343,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
                     }
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < NI; ++i)
 #pragma unroll
                         for (int e = 0; e < 16; e += 2) {
                             s0 += __builtin_amdgcn_exp2f(acc[i][j][e] - m_run[j]);
@@ -318,7 +354,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < NI; ++i) {
                 // a lane's 16 tokens of a block in fp32, pairs first, then in 64 bits: one
                 // chain over its T / 4 tokens lost up to 2.7 times the fp32 kernels' bits
                 float blk[2] = {0.f, 0.f}, dl[2][4];
@@ -327,7 +363,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
                     // record {lse log2 e, r tau log2 e, target, p_y - 1}; the target's entry
                     // of delta is the exact p_y - 1 of the local-loss pass
                     const int yl = 32 * i + 8 * (e >> 2) + 4 * hi + (e & 3);
-                    const f32x4 r4 = *(LDS_AS const f32x4*)(sd + 4 * (128 * wm + yl));
+                    const f32x4 r4 = *(LDS_AS const f32x4*)(sd + 4 * (WY * wm + yl));
                     const bool in = !ragged || yl < a.nY - yb;
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
@@ -346,6 +382,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
     // ---- the lane halves, then the two waves of a column of blocks
     __syncthreads();  // the stages are free
     float* red = (float*)sA0;  // [wm][state][256 rows of X]
+    static_assert(2 * 5 * BT * 4 <= STA, "the rows' states fit a stage");
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int xl = 64 * wn + 32 * j + l32;
@@ -422,17 +459,26 @@ __global__ void k_db_sum(const float* __restrict__ parts, float* __restrict__ ou
     out[i] = (float)s * inv_T;
 }
 
-template <int MODE, bool EXT, bool XA>
+template <int MODE, bool EXT, bool XA, int NI = 4>
 hipError_t launch_t(const LogitsArgs& a, int nmod, hipStream_t s) {
     const int tiles = (a.nX + BT - 1) / BT;
-    hipLaunchKernelGGL((k_logits<MODE, EXT, XA>), dim3((unsigned)(((long long)tiles * a.nsplit + 7) / 8 * 8), (unsigned)nmod),
+    hipLaunchKernelGGL((k_logits<MODE, EXT, XA, NI>), dim3((unsigned)(((long long)tiles * a.nsplit + 7) / 8 * 8), (unsigned)nmod),
                        dim3(NTHR), 0, s, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
+// The planes' rows of Y per tile in exit evaluation.  The upper plane's chain of d / 16 sums
+// rounds at the logit's size: the row losses' error (rms of 2 x 1000 rows) is 3.3e-7 at d = 2040,
+// where it was 4.0e-7 on the vector ALU (4.2 at 3072), and grows with d to the same size near
+// d = 3000.  Past 2560 the k-sum is therefore cut (2.8e-7 at 3072, 3.1 at 4096), on half the
+// tile: 4 x 8192 x 32000 rows take 12.8 ms at 3072 and 20.1 at 4096; uncut 10.2 and 14.2.
+int logits_eval_tile(bool exact, int d) { return exact && d > 2560 ? 128 : 256; }
+
 hipError_t launch_logits_eval(const LogitsArgs& a, hipStream_t s) {
+    if (logits_eval_tile(a.exact, a.d) == 128)
+        return a.bias ? launch_t<EVAL, true, true, 2>(a, 1, s) : launch_t<EVAL, false, true, 2>(a, 1, s);
     if (a.exact) return a.bias ? launch_t<EVAL, true, true>(a, 1, s) : launch_t<EVAL, false, true>(a, 1, s);
     return a.bias ? launch_t<EVAL, true, false>(a, 1, s) : launch_t<EVAL, false, false>(a, 1, s);
 }

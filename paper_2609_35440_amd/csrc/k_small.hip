@@ -92,8 +92,8 @@ __global__ void k_gain_rows(const bf16* __restrict__ h, long long src_stride, co
     }
 }
 
-// g * h (16 significant bits) as two bf16 planes side by side, rows of
-// plane_pitch(d) elements; 8 elements of a row per thread (d % 8 == 0)
+// g * h (16 significant bits) as two bf16 planes side by side, the lower one first,
+// rows of plane_pitch(d) elements; 8 elements of a row per thread (d % 8 == 0)
 __global__ void k_gain_planes(const bf16* __restrict__ h, const bf16* __restrict__ gain, bf16* __restrict__ out,
                               long long rows, int d) {
     typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -114,8 +114,8 @@ __global__ void k_gain_planes(const bf16* __restrict__ h, const bf16* __restrict
                 lo[e] = (bf16)(p - (float)hi[e]);
             }
         }
-        *(bf16x8*)(out + r * (2LL * half) + j) = hi;
-        *(bf16x8*)(out + r * (2LL * half) + half + j) = lo;
+        *(bf16x8*)(out + r * (2LL * half) + j) = lo;
+        *(bf16x8*)(out + r * (2LL * half) + half + j) = hi;
     }
 }
 

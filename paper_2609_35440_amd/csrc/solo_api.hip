@@ -251,6 +251,9 @@ struct EvalPlan {
 };
 
 double prod_tile_us(int d, bool planes) { return 4.0 + (planes ? 0.054 : 0.027) * d; }
+double prod_eval_tile_us(int d, bool planes) {
+    return solo::logits_eval_tile(planes, d) == 128 ? 2.0 + 0.036 * d : prod_tile_us(d, planes);
+}
 double eval_chunk_us(int rows, int d) { return 0.2 + 0.0055 * rows + 0.45 * (double)rows * d / 131072.0; }
 
 EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
@@ -278,7 +281,8 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
         best = us;
     }
     const long long lists = flat ? 1 : K, n = flat ? (long long)K * T : T;  // rows are one list, or one per module
-    const long long nvt = ((long long)V + 255) / 256;
+    const int vt = solo::logits_eval_tile(P.planes, d);
+    const long long nvt = ((long long)V + vt - 1) / vt;
     // (as in best_split: the least split of each number of tiles per part)
     for (long long per = nvt + 1; per > 1;) {
         const int sp = (int)((nvt + per - 2) / (per - 1));
@@ -293,7 +297,7 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
             const long long whole = n / pr, rest = n - whole * pr;
             auto rounds = [&](long long r) { return (double)(((r + 255) / 256 * sp + 255) / 256); };
             const double t = (double)lists * ((whole * rounds(pr) + (rest ? rounds(rest) : 0.0)) *
-                                                  (double)((nvt + sp - 1) / sp) * prod_tile_us(d, P.planes) +
+                                                  (double)((nvt + sp - 1) / sp) * prod_eval_tile_us(d, P.planes) +
                                               (double)(whole + (rest > 0)) * 8.0) +
                              10.0 + kt * d * 4.0 / 4e6 + (sp > 1 ? 5.0 + kt * 64.0 * sp / 3e6 : 0.0);
             if (t < best) {

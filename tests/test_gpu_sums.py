@@ -58,6 +58,31 @@ def test_bias_gradient(dtype, d, T, V):
         assert float(err) <= tol, (k, float(err), tol)
 
 
+def _row_losses(op, dtype, d, T=1024, V=2001, bias=None):
+    """The calls' row losses of 2 x T rows, and the same in 64 bits."""
+    import torch
+
+    from paper_2609_35440_amd import binding
+
+    K = 2
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(6)
+    h = torch.randn(K, T, d, generator=g, device="cuda").to(dt)
+    W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).to(dt)
+    y = torch.randint(0, V, (K, T), generator=g, device="cuda", dtype=torch.int32)
+    gain = (1 + 0.1 * torch.randn(d, generator=g, device="cuda")).to(dt)
+    b = 0.1 * torch.randn(K, V, generator=g, device="cuda") if bias else None
+    if op == "train":
+        got = binding.readout_general(h, gain, W, y, bias=b, row_loss=True).row_loss
+    else:
+        got = binding.exit_eval(h, gain, W, y, bias=b).row_loss
+    n = h.double() * torch.rsqrt(h.double().square().mean(2, keepdim=True) + 1e-6)
+    z = (n * gain.double()) @ W.double().t()
+    if bias:
+        z = z + b.double()[:, None, :]
+    return got.double(), torch.logsumexp(z, 2) - z.gather(2, y.long()[..., None])[..., 0]
+
+
 @pytest.mark.parametrize("op", ["train", "eval"])
 @pytest.mark.parametrize("dtype,d", [("bf16", 48), ("bf16", 200), ("bf16", 640), ("bf16", 1800), ("f32", 264)],
                          ids=["bf16-48", "bf16-200", "bf16-640", "bf16-1800", "f32-264"])
@@ -66,22 +91,21 @@ def test_row_losses_are_not_biased(op, dtype, d):
     as much, to either side.  The mean over 2048 rows is then within 5e-7 / sqrt(2048) = 1.1e-8
     of the truth, one standard error; ten are allowed (a logarithm that reads half a unit low
     is off by 3e-7)."""
-    import torch
+    got, ref = _row_losses(op, dtype, d)
+    assert abs(float((got - ref).mean())) <= 1.1e-7
 
-    from paper_2609_35440_amd import binding
 
-    K, T, V = 2, 1024, 2001
-    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    g = torch.Generator(device="cuda").manual_seed(6)
-    h = torch.randn(K, T, d, generator=g, device="cuda").to(dt)
-    W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).to(dt)
-    y = torch.randint(0, V, (K, T), generator=g, device="cuda", dtype=torch.int32)
-    gain = (1 + 0.1 * torch.randn(d, generator=g, device="cuda")).to(dt)
-    if op == "train":
-        got = binding.readout_fwd_bwd(h, gain, W, y, row_loss=True).row_loss
-    else:
-        got = binding.exit_eval(h, gain, W, y).row_loss
-    n = h.double() * torch.rsqrt(h.double().square().mean(2, keepdim=True) + 1e-6)
-    z = (n * gain.double()) @ W.double().t()
-    ref = torch.logsumexp(z, 2) - z.gather(2, y.long()[..., None])[..., 0]
-    assert abs(float((got.double() - ref).mean())) <= 1.1e-7
+@pytest.mark.parametrize("bias", [False, True], ids=["", "bias"])
+@pytest.mark.parametrize("T,V", [(1024, 2001), (130, 120)], ids=["many", "few"])
+@pytest.mark.parametrize("d", [200, 1496, 2040, 2552, 2568, 3080, 4096])
+def test_row_losses_of_wide_rows(d, T, V, bias):
+    """Exit evaluation of the bf16 widths defined in fp32.  The target's logit has a deviation of
+    s = 0.02 sqrt(d); summed 16 products at a time in n steps its partial sums round by 2^-25
+    (rms, about) of sqrt(k / n) s each, together sqrt(n / 2) 2^-25 s, with n = d / 16 up to d = 2560
+    and 32 past it, where sixteen such pieces at most add to as much again.  The row's end rounds
+    by 3e-7 at most.  (A chain of both planes was off by 9.3e-7 at d = 4096.)"""
+    got, ref = _row_losses("eval", "bf16", d, T, V, bias)
+    n = d / 16 if d <= 2560 else 2 * 32
+    tol = 3e-7 + (n / 2) ** 0.5 * 2.0**-25 * 0.02 * d**0.5
+    err = (got - ref).square().mean().sqrt()
+    assert float(err) <= tol, (float(err), tol)
