@@ -92,10 +92,29 @@ __global__ void k_gain_rows(const bf16* __restrict__ h, long long src_stride, co
     }
 }
 
+// bf16(g * h) of a list of rows (from the global row row0 on) with their modules' gains;
+// 8 elements of a row per thread
+__global__ void k_gain_list(const bf16* __restrict__ h, const bf16* __restrict__ gain, int g_stride,
+                            bf16* __restrict__ out, long long rows, long long row0, int T, int d) {
+    typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+    const int per = d / 8;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < rows * per;
+         i += (long long)gridDim.x * blockDim.x) {
+        const long long r = i / per;
+        const int j = 8 * (int)(i - r * per);
+        const bf16x8 hv = *(const bf16x8*)(h + i * 8);
+        const bf16x8 gv = *(const bf16x8*)(gain + (row0 + r) / T * g_stride + j);
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (bf16)((float)hv[e] * (float)gv[e]);
+        *(bf16x8*)(out + i * 8) = o;
+    }
+}
+
 // g * h (16 significant bits) as two bf16 planes side by side, the lower one first,
-// rows of plane_pitch(d) elements; 8 elements of a row per thread (d % 8 == 0)
-__global__ void k_gain_planes(const bf16* __restrict__ h, const bf16* __restrict__ gain, bf16* __restrict__ out,
-                              long long rows, int d) {
+// rows of plane_pitch(d) elements (a list of rows, as in k_gain_list); 8 elements of a row per thread (d % 8 == 0)
+__global__ void k_gain_planes(const bf16* __restrict__ h, const bf16* __restrict__ gain, int g_stride,
+                              bf16* __restrict__ out, long long rows, long long row0, int T, int d) {
     typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
     const int half = plane_pitch(d) / 2;
     const int j = 8 * (blockIdx.y * blockDim.x + threadIdx.x);
@@ -106,7 +125,8 @@ __global__ void k_gain_planes(const bf16* __restrict__ h, const bf16* __restrict
         for (int e = 0; e < 8; ++e) hi[e] = lo[e] = (bf16)0.f;
         if (j < d) {
             const bf16x8 hv = *(const bf16x8*)(h + r * d + j);
-            const bf16x8 gv = *(const bf16x8*)(gain + j);
+            const bf16* const g = gain + (g_stride ? (row0 + r) / T * g_stride : 0);
+            const bf16x8 gv = *(const bf16x8*)(g + j);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float p = (float)hv[e] * (float)gv[e];
@@ -192,10 +212,21 @@ hipError_t launch_gain_rows(const bf16* h, long long src_stride, const bf16* gai
     return hipGetLastError();
 }
 
-hipError_t launch_gain_planes(const bf16* h, const bf16* gain, bf16* out, long long rows, int d, hipStream_t s) {
+hipError_t launch_gain_list(const bf16* h, const bf16* gain, int g_stride, bf16* out, long long rows, long long row0,
+                            int T, int d, hipStream_t s) {
+    if (!g_stride) return launch_gain_rows(h, 0, gain, 0, out, 0, 1, (int)rows, d, s);
+    long long blocks = (rows * (d / 8) + 255) / 256;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_gain_list, dim3((unsigned)blocks), dim3(256), 0, s, h, gain, g_stride, out, rows, row0, T, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_gain_planes(const bf16* h, const bf16* gain, int g_stride, bf16* out, long long rows, long long row0,
+                              int T, int d, hipStream_t s) {
     const unsigned parts = (unsigned)((plane_pitch(d) / 16 + 63) / 64);
     const unsigned blocks = (unsigned)(rows < 8192 ? rows : 8192);
-    hipLaunchKernelGGL(k_gain_planes, dim3(blocks, parts), dim3(64), 0, s, h, gain, out, rows, d);
+    hipLaunchKernelGGL(k_gain_planes, dim3(blocks, parts), dim3(64), 0, s, h, gain, g_stride, out, rows, row0,
+                       T, d);
     return hipGetLastError();
 }
 

@@ -530,18 +530,11 @@ int run(const solo_readout_args& x, bool eval) {
                 l.row0 = (flat ? 0 : (long long)k * T) + r0;
                 l.nX = (int)nr;
                 // the rows' products with their modules' gains
-                for (long long r = 0; r < nr;) {
-                    const long long m = (l.row0 + r) / T;
-                    const long long end = g.g_stride ? (m + 1) * T - l.row0 : nr;
-                    const long long cnt = (end < nr ? end : nr) - r;
-                    const solo::bf16* const src = (const solo::bf16*)g.h + (l.row0 + r) * d;
-                    const solo::bf16* const gn = (const solo::bf16*)g.gain + m * g.g_stride;
-                    if ((P.planes ? solo::launch_gain_planes(src, gn, copy + r * solo::plane_pitch(d), cnt, d, s)
-                                  : solo::launch_gain_rows(src, 0, gn, 0, copy + r * d, 0, 1, (int)cnt, d, s)) !=
-                        hipSuccess)
-                        return false;
-                    r += cnt;
-                }
+                const solo::bf16* const src = (const solo::bf16*)g.h + l.row0 * d;
+                const solo::bf16* const gn = (const solo::bf16*)g.gain;
+                if ((P.planes ? solo::launch_gain_planes(src, gn, g.g_stride, copy, nr, l.row0, T, d, s)
+                              : solo::launch_gain_list(src, gn, g.g_stride, copy, nr, l.row0, T, d, s)) != hipSuccess)
+                    return false;
                 l.X = copy;
                 if (solo::launch_logits_eval(l, s) != hipSuccess) return false;
             }
@@ -592,13 +585,15 @@ int run(const solo_readout_args& x, bool eval) {
         (!gain_copies(P.rg_lo, P.rg_hi, tiled_rgrad(P)) || !gain_copies(P.bg_lo, P.bg_hi, bsplit == 0)))
         return SOLO_ERR_HIP;
     if (P.exact && bsplit > 0) {
-        for (int m = P.bg_lo; m < P.bg_hi; ++m) {
+        // (under ROT the heads' rotated rows and the terminal's own are two lists)
+        for (int m = P.bg_lo; m < P.bg_hi;) {
+            const int end = P.rot && m < K - 1 && P.bg_hi == K ? K - 1 : P.bg_hi;
             const solo::FusedArgs& g = P.rot && m < K - 1 ? ah : a;
-            if (solo::launch_gain_planes((const solo::bf16*)g.h + (long long)m * T * d,
-                                         (const solo::bf16*)g.gain + (long long)m * g.g_stride,
-                                         (solo::bf16*)(ws + P.hg) + (long long)(m - P.bg_lo) * T * solo::plane_pitch(d), T,
-                                         d, s) != hipSuccess)
+            if (solo::launch_gain_planes((const solo::bf16*)g.h + (long long)m * T * d, (const solo::bf16*)g.gain, g.g_stride,
+                                         (solo::bf16*)(ws + P.hg) + (long long)(m - P.bg_lo) * T * solo::plane_pitch(d),
+                                         (long long)(end - m) * T, (long long)m * T, T, d, s) != hipSuccess)
                 return SOLO_ERR_HIP;
+            m = end;
         }
     }
     if (!eval && !pass_range(2, P.rg_lo, P.rg_hi)) return SOLO_ERR_HIP;

@@ -150,7 +150,12 @@ struct LogitsArgs {
 };
 __host__ __device__ inline int plane_pitch(int d) { return 2 * ((d + 63) / 64 * 64); }
 // copies of g * h as two planes, hi = bf16(g h) at [pitch / 2, pitch) and lo = bf16(g h - hi) at [0, pitch / 2), zeros past d
-hipError_t launch_gain_planes(const bf16* h, const bf16* gain, bf16* out, long long rows, int d, hipStream_t s);
+// (rows row0, row0 + 1, .. of the list of all modules' rows, h being the first of them, each with its module's gain)
+hipError_t launch_gain_planes(const bf16* h, const bf16* gain, int g_stride, bf16* out, long long rows, long long row0,
+                              int T, int d, hipStream_t s);
+// the same, copies bf16(g * h) of rows of d
+hipError_t launch_gain_list(const bf16* h, const bf16* gain, int g_stride, bf16* out, long long rows, long long row0,
+                            int T, int d, hipStream_t s);
 int logits_eval_tile(bool exact, int d);  // streamed rows per tile of exit evaluation (256 or 128)
 hipError_t launch_logits_eval(const LogitsArgs& a, hipStream_t s);
 hipError_t launch_logits_bgrad(const LogitsArgs& a, int nmod, hipStream_t s);

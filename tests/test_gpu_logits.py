@@ -22,7 +22,8 @@ pytestmark = pytest.mark.gpu
 EVAL = [("plain", 2, 1537, 16129, dict()), ("one-list", 2, 1537, 16129, dict(per_module_gain=True, tau=True)),
         ("bias", 2, 1537, 16129, dict(bias=True)),
         ("per-head", 2, 1537, 16129, dict(wbar="per_head", bias=True, tau=True)),
-        ("two-passes", 2, 6017, 12289, dict(per_module_gain=True))]
+        ("two-passes", 2, 6017, 12289, dict(per_module_gain=True)),
+        ("many-modules", 70, 45, 12289, dict(per_module_gain=True))]
 
 
 @pytest.mark.parametrize("name,K,T,V,extras", EVAL, ids=[c[0] for c in EVAL])
@@ -92,7 +93,7 @@ def test_bias_gradient(T, V, extras, final):
 # bf16 widths defined in fp32: the product on two planes of g * h
 PLANES = [("plain", 2, 300, 72, 1025, dict()), ("one-list", 3, 9, 640, 5000, dict(per_module_gain=True, tau=True)),
           ("bias", 2, 257, 1000, 700, dict(bias=True)), ("per-head", 2, 130, 136, 600, dict(wbar="per_head")),
-          ("wide", 1, 33, 3080, 513, dict()), ("widest", 2, 5, 4096, 300, dict(tau=True)), ("narrow", 1, 700, 8, 257, dict())]
+          ("many-modules", 40, 33, 136, 2049, dict(per_module_gain=True, tau=True)), ("wide", 1, 33, 3080, 513, dict()), ("widest", 2, 5, 4096, 300, dict(tau=True)), ("narrow", 1, 700, 8, 257, dict())]
 
 
 @pytest.mark.parametrize("name,K,T,d,V,extras", PLANES, ids=[c[0] for c in PLANES])
