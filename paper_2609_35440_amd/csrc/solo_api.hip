@@ -288,12 +288,14 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
         const int sp = (int)((nvt + per - 2) / (per - 1));
         if (sp > solo::kEvalSplits) break;
         per = (nvt + sp - 1) / sp;
-        const double cap = (room - 512.0 - (sp > 1 ? kt * 32.0 * sp : 0.0)) / row_bytes;
-        if (cap < (n < 256 ? (double)n : 256.0)) break;
-        const long long np0 = (long long)((double)n / cap) + 1;
+        // rows whose copies fit next to the parts, and the least number of passes over them
+        const double left = room - 512.0 - (sp > 1 ? kt * 32.0 * sp : 0.0);
+        const long long cap = left > 0.0 ? (long long)(left / row_bytes) : 0;
+        if (cap < (n < 256 ? n : 256)) break;
+        const long long np0 = (n + cap - 1) / cap;
         for (long long np = np0; np < np0 + 4; ++np) {
             const long long pr = ((n + np - 1) / np + 255) / 256 * 256;
-            if ((double)(pr < n ? pr : n) > cap) continue;
+            if ((pr < n ? pr : n) > cap) continue;
             const long long whole = n / pr, rest = n - whole * pr;
             auto rounds = [&](long long r) { return (double)(((r + 255) / 256 * sp + 255) / 256); };
             const double t = (double)lists * ((whole * rounds(pr) + (rest ? rounds(rest) : 0.0)) *
@@ -309,6 +311,13 @@ EvalPlan plan_eval(const Plan& P, int K, int T, int d, int V, bool flat) {
         }
     }
     return E;
+}
+
+// The rows of exit evaluation as one list (one readout, no biases); and the floats that the
+// parts of split local-loss passes may use: a readout gradient, written by a later pass.
+bool flat_list(const Plan& P, const solo_readout_args& x) { return !P.rot && !x.bias && !(x.Wbar && x.K > 1); }
+size_t split_room(const Plan& P, const solo_readout_args& x) {
+    return x.final_module_dW || P.rg_hi > P.rg_lo ? (size_t)x.V * x.d : 0;
 }
 
 // The bias-gradient pass over n modules as a tiled product (the readout rows
@@ -425,7 +434,7 @@ int run(const solo_readout_args& x, bool eval) {
     if (solo::launch_row_rstd(dt, x.h, (float*)(ws + P.rstd), (long long)K * T, d, x.eps, s) != hipSuccess)
         return SOLO_ERR_HIP;
     // exit evaluation of few rows: split over the vocabulary, no tiled copies
-    const bool flat = eval && !P.rot && !x.bias && !(x.Wbar && K > 1);
+    const bool flat = eval && flat_list(P, x);
     const EvalPlan E = eval && (P.mfma || P.planes) ? plan_eval(P, K, T, d, V, flat) : EvalPlan();
     a.split_stat = (float*)(ws + P.wtile);
     a.part_rows = (long long)K * T;
@@ -454,9 +463,9 @@ int run(const solo_readout_args& x, bool eval) {
         ah.ebuf = eval ? nullptr : (void*)(ws + P.ebuf);
     }
     if (!mark(0)) return SOLO_ERR_HIP;
-    // scratch of split local-loss passes: a readout gradient, written by a later pass
+    // scratch of split local-loss passes
     float* const room = eval ? nullptr : (x.final_module_dW ? x.dW : (P.rg_hi > P.rg_lo ? x.dWbar : nullptr));
-    const size_t room_floats = room ? (size_t)V * d : 0;
+    const size_t room_floats = eval ? 0 : split_room(P, x);
     // one launch over modules [m0, m0 + n) of a pass, with the arguments g
     auto pass = [&](int which, const solo::FusedArgs& g, int m0, int n) -> hipError_t {
         if (n <= 0) return hipSuccess;
@@ -783,6 +792,34 @@ size_t solo_readout_exit_eval_workspace_size(const solo_readout_args* args) {
 int solo_readout_exit_eval(const solo_readout_args* args) {
     if (!args) return SOLO_ERR_NULL;
     return run(*args, true);
+}
+
+// Which forms a call of these sizes, flags and workspace_bytes runs in, for the tests that are about
+// one of them (host only; not in the public header).  Exit evaluation: route[0] the form of
+// EvalPlan, route[1] its splits, route[2] the rows of one pass of the product.  Training: route[0]
+// the splits of the local-loss pass (under ROT the heads'), route[1] the terminal's, route[2] the
+// splits of the bias gradient's product (0: the fused pass).  SOLO_OK, or the status of such a call's sizes.
+__attribute__((visibility("default"))) int solo_readout_route(const solo_readout_args* args, int exit_eval,
+                                                             long long* route) {
+    if (!args || !route) return SOLO_ERR_NULL;
+    const solo_readout_args& x = *args;
+    Plan P;
+    if (!make_plan(x, exit_eval != 0, &P)) return SOLO_ERR_SHAPE;
+    if (x.workspace_bytes < P.total && P.planes && !make_plan(x, exit_eval != 0, &P, false)) return SOLO_ERR_SHAPE;
+    if (x.workspace_bytes < P.total) return SOLO_ERR_WORKSPACE;
+    if (exit_eval) {
+        const EvalPlan E = P.mfma || P.planes ? plan_eval(P, x.K, x.T, x.d, x.V, flat_list(P, x)) : EvalPlan();
+        route[0] = E.form;
+        route[1] = E.nsplit;
+        route[2] = E.pass_rows;
+        return SOLO_OK;
+    }
+    const size_t room = split_room(P, x);
+    const int nbg = P.bg_hi - P.bg_lo;
+    route[0] = local_splits(P, P.rot ? x.K - 1 : x.K, x.K, x.T, x.d, x.V, room);
+    route[1] = P.rot ? local_splits(P, 1, x.K, x.T, x.d, x.V, room) : route[0];
+    route[2] = (P.mfma || P.planes) && nbg > 0 ? prod_bgrad_splits(P, nbg, x.K, x.T, x.d, x.V) : 0;
+    return SOLO_OK;
 }
 
 }  // extern "C"
