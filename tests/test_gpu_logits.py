@@ -5,20 +5,20 @@ their own gains and temperatures, one list per module (biases, one readout per
 head), more rows than one pass holds, invalid targets, vocabulary entries masked
 by a bias of -inf, the largest negative bias, and ties across tiles.
 
-The calls are sized so that the product form is the one taken (see plan_eval and
-prod_bgrad_splits in solo_api.hip)."""
+Every test asserts that the product form is the one taken (tests/routes.py)."""
 import numpy as np
 import pytest
 
 import oracle
 from solo_inputs import make_extras, make_inputs
 from tests.gpu_helpers import rel_max_err
+from tests.routes import FUSED, PROD, P, route, route_of
 from tests.test_gpu_general import check_exit_eval, compare, oracle_general, run_exit_eval, run_general
 
 pytestmark = pytest.mark.gpu
 
 
-# a last tile of one row of either operand; the last case takes two passes of rows
+# a last tile of one row of either operand; two passes of rows; more than two modules per tile
 EVAL = [("plain", 2, 1537, 16129, dict()), ("one-list", 2, 1537, 16129, dict(per_module_gain=True, tau=True)),
         ("bias", 2, 1537, 16129, dict(bias=True)),
         ("per-head", 2, 1537, 16129, dict(wbar="per_head", bias=True, tau=True)),
@@ -29,8 +29,18 @@ EVAL = [("plain", 2, 1537, 16129, dict()), ("one-list", 2, 1537, 16129, dict(per
 @pytest.mark.parametrize("name,K,T,V,extras", EVAL, ids=[c[0] for c in EVAL])
 def test_eval(name, K, T, V, extras):
     x = make_extras(make_inputs("1b", seed=12, K=K, T=T, d=256, V=V), seed=12, **extras)
+    form, _, rows = route_of(x, True)
+    assert form == PROD and (rows < K * T) == (name in ("two-passes", "bias", "per-head"))
     losses, row_loss, top1 = run_exit_eval(x)
     check_exit_eval(x, losses, row_loss, top1, f"product eval {name}", min_rows_for_agreement=100)
+
+
+@pytest.mark.parametrize("d,V", [(1024, 16129), (2048, 4097)])
+def test_eval_wide(d, V):
+    x = make_inputs("1b", seed=12, K=2, T=1537, d=d, V=V)
+    assert route_of(x, True)[0] == PROD
+    losses, row_loss, top1 = run_exit_eval(x)
+    check_exit_eval(x, losses, row_loss, top1, f"product eval d={d}", min_rows_for_agreement=100)
 
 
 def _device(K, T, d, V, seed=4):
@@ -49,6 +59,7 @@ def test_eval_masks_ties_and_invalid_targets():
     from paper_2609_35440_amd import binding
 
     K, T, d, V = 1, 3073, 256, 12289
+    assert route(True, K, T, d, V)[0] == PROD and route(True, K, T, d, V, bias=P)[0] == PROD
     h, gain, W, y = _device(K, T, d, V)
     W[12288] = W[70] = W[2500] = (0.1 * h[0, 7].float()).to(torch.bfloat16)
     y[0, 11] = V + 5
@@ -83,6 +94,7 @@ def test_eval_masks_ties_and_invalid_targets():
 def test_bias_gradient(T, V, extras, final):
     x = make_extras(make_inputs("1b", seed=13, K=3, T=T, d=256, V=V), seed=13, **extras)
     flags = dict(final_module_dW=final, want_dtau=True, want_dbias=True)
+    assert route_of(x, False, **flags)[2] > 1
     g = run_general(x, flags)
     ref = oracle_general(x, flags)
     compare(g, ref, "bf16", flags, f"product bias gradient {T} {V}")
@@ -90,10 +102,14 @@ def test_bias_gradient(T, V, extras, final):
         assert rel_max_err(g["dbias"][k], ref["dbias"][k]) <= 2e-2
 
 
-# bf16 widths defined in fp32: the product on two planes of g * h
+# bf16 widths defined in fp32: the product on two planes of g * h; the last ones
+# up to d = 64, where a tile has two stages, with several tiles per split, and past 2560
 PLANES = [("plain", 2, 300, 72, 1025, dict()), ("one-list", 3, 9, 640, 5000, dict(per_module_gain=True, tau=True)),
-          ("bias", 2, 257, 1000, 700, dict(bias=True)), ("per-head", 2, 130, 136, 600, dict(wbar="per_head")),
-          ("many-modules", 40, 33, 136, 2049, dict(per_module_gain=True, tau=True)), ("wide", 1, 33, 3080, 513, dict()), ("widest", 2, 5, 4096, 300, dict(tau=True)), ("narrow", 1, 700, 8, 257, dict())]
+          ("bias", 2, 257, 1000, 700, dict(bias=True)), ("per-head", 2, 300, 136, 2049, dict(wbar="per_head")),
+          ("many-modules", 40, 33, 136, 2049, dict(per_module_gain=True, tau=True)),
+          ("wide", 1, 33, 3080, 513, dict()), ("wide-bias", 2, 130, 3080, 1500, dict(bias=True)),
+          ("widest", 2, 5, 4096, 300, dict(tau=True)), ("narrow", 1, 700, 8, 7000, dict()),
+          ("two-stages", 1, 4100, 64, 9000, dict(bias=True))]
 
 
 @pytest.mark.parametrize("name,K,T,d,V,extras", PLANES, ids=[c[0] for c in PLANES])
@@ -101,6 +117,8 @@ def test_eval_planes(name, K, T, d, V, extras):
     from tests.gpu_helpers import row_loss_error_bound
 
     x = make_extras(make_inputs("1b", seed=14, K=K, T=T, d=d, V=V), seed=14, **extras)
+    form, splits, _ = route_of(x, True)
+    assert form == PROD and (name != "two-stages" or 2 * splits <= V // 256)
     losses, row_loss, top1 = run_exit_eval(x)
     check_exit_eval(x, losses, row_loss, top1, f"planes {name}", min_rows_for_agreement=100)
     # fp32 logits: within the bound of fp32 operands and sums
@@ -121,6 +139,7 @@ def test_eval_planes(name, K, T, d, V, extras):
 def test_bias_gradient_planes(T, d, V, extras, final):
     x = make_extras(make_inputs("1b", seed=15, K=3, T=T, d=d, V=V), seed=15, **extras)
     flags = dict(final_module_dW=final, want_dtau=True, want_dbias=True)
+    assert route_of(x, False, **flags)[2] > 1
     g = run_general(x, flags)
     ref = oracle_general(x, flags)
     compare(g, ref, "bf16", flags, f"bias gradient on planes {T} {d} {V}")
@@ -135,8 +154,10 @@ def test_workspace_without_plane_copies(monkeypatch):
     from paper_2609_35440_amd import binding
 
     al = lambda n: -(-n // 256) * 256
-    K, T, d, V = 2, 300, 72, 1025
+    K, T, d, V = 2, 300, 72, 4097
     x = make_extras(make_inputs("1b", seed=14, K=K, T=T, d=d, V=V), seed=14, bias=True)
+    assert route_of(x, True)[0] == PROD
+    assert route_of(x, True, workspace_bytes=3 * al(K * T * 4))[0] == FUSED
     full = run_exit_eval(x)
     monkeypatch.setattr(binding, "exit_eval_workspace_size", lambda a: 3 * al(K * T * 4))
     losses, row_loss, top1 = run_exit_eval(x)
@@ -157,6 +178,10 @@ def test_workspace_without_plane_copies(monkeypatch):
         a.dbias = kept
         return n
 
+    kt = 3 * T
+    least_bytes = 3 * al(kt * 4) + al(kt * 16) + al(kt * 4) + al(-(-T // 8) * d * 4)
+    assert route_of(x, False, **flags)[2] > 0
+    assert route_of(x, False, workspace_bytes=least_bytes, **flags)[2] == 0
     monkeypatch.setattr(binding, "general_workspace_size", least)
     g = run_general(x, flags)
     ref = oracle_general(x, flags)

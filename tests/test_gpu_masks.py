@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 from solo_inputs import make_extras, make_inputs
+from tests.routes import FUSED, PROD, SPLIT, route_of
 from tests.test_gpu_general import check_exit_eval, compare, oracle_general, run_exit_eval, run_general
 
 pytestmark = pytest.mark.gpu
@@ -41,6 +42,7 @@ def check(x, few, lo, hi, flags, what):
     compare(g, oracle_general(few, flags), x["cfg"].dtype, flags, what)
 
 
+# (splits beyond one are asserted, so that parts start inside a mask)
 # few tokens (split) of both bf16 tilings, the exact forms and the fp32 kernels; the last ones are not split
 TRAIN = [("1b", 2, 40, 1024, 4001), ("1b", 3, 20, 2048, 3000), ("2b", 2, 20, 2560, 3001), ("1b", 2, 40, 640, 3001),
          ("1b", 2, 20, 1800, 2001), ("1b", 2, 40, 48, 3001), ("tiny", 2, 40, 264, 3001),
@@ -51,8 +53,10 @@ TRAIN = [("1b", 2, 40, 1024, 4001), ("1b", 3, 20, 2048, 3000), ("2b", 2, 20, 256
 @pytest.mark.parametrize("keep", list(KEEP))
 @pytest.mark.parametrize("cfg,K,T,d,V", TRAIN, ids=["-".join(map(str, c)) for c in TRAIN])
 def test_train(cfg, K, T, d, V, keep, low):
-    check(*masked(cfg, K, T, d, V, keep, low, tau=True),
-          dict(final_module_dW=True, want_dtau=True, want_dbias=True), f"masked {keep} {low} d={d}")
+    m = masked(cfg, K, T, d, V, keep, low, tau=True)
+    flags = dict(final_module_dW=True, want_dtau=True, want_dbias=True)
+    assert (route_of(m[0], False, **flags)[0] > 4) == (V > 100)
+    check(*m, flags, f"masked {keep} {low} d={d}")
 
 
 @pytest.mark.parametrize("keep", list(KEEP))
@@ -70,5 +74,7 @@ EVAL = [("1b", 3, 30, 512, 8003), ("1b", 2, 16, 2048, 8000), ("2b", 2, 30, 2560,
 @pytest.mark.parametrize("cfg,K,T,d,V", EVAL, ids=["-".join(map(str, c)) for c in EVAL])
 def test_eval(cfg, K, T, d, V, keep, low):
     x, few, lo, hi = masked(cfg, K, T, d, V, keep, low)
+    form = PROD if d == 72 else (SPLIT if cfg != "tiny" and V > 100 else FUSED)
+    assert route_of(x, True)[0] == form
     losses, row_loss, top1 = run_exit_eval(x)
     check_exit_eval(few, losses, row_loss, top1 - lo, f"masked eval {keep} {low} d={d}", min_rows_for_agreement=100)

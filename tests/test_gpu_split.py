@@ -9,6 +9,7 @@ import pytest
 import oracle
 from solo_inputs import make_extras, make_inputs
 from tests.gpu_helpers import check_close, log, run_gpu
+from tests.routes import SPLIT, route, route_of
 from tests.test_gpu_general import check_exit_eval, compare, oracle_general, run_exit_eval, run_general
 
 pytestmark = pytest.mark.gpu
@@ -21,6 +22,7 @@ TRAIN = [("1b", 4, 3, 256, 2065), ("1b", 2, 65, 1024, 1999), ("1b", 3, 33, 2048,
 def test_train(cfg, K, T, d, V):
     x = make_inputs(cfg, seed=8, K=K, T=T, d=d, V=V)
     log(f"split {cfg} {K} {T} {d} {V}")
+    assert route_of(x, False)[0] > 1
     check_close(run_gpu(x, True), oracle.readout_fwd_bwd(x["h"], x["gain"], x["W"], x["targets"], True),
                 x["cfg"].dtype, what=f"split d={d}")
 
@@ -30,6 +32,7 @@ def test_general(cfg, d):
     x = make_extras(make_inputs(cfg, seed=9, K=3, T=37, d=d, V=1500), seed=9, per_module_gain=True, tau=True,
                     bias=True)
     flags = dict(final_module_dW=True, want_dtau=True, want_dbias=True)
+    assert route_of(x, False, **flags)[0] > 1
     compare(run_general(x, flags), oracle_general(x, flags), x["cfg"].dtype, flags, f"split general d={d}")
 
 
@@ -38,6 +41,7 @@ def test_general(cfg, d):
 @pytest.mark.parametrize("cfg,d", [("1b", 512), ("1b", 2048), ("2b", 2560)])
 def test_eval(cfg, d, extras):
     x = make_extras(make_inputs(cfg, seed=10, K=3, T=30, d=d, V=2003), seed=10, **extras)
+    assert route_of(x, True)[0] == SPLIT
     losses, row_loss, top1 = run_exit_eval(x)
     check_exit_eval(x, losses, row_loss, top1, f"split eval d={d}", min_rows_for_agreement=60)
 
@@ -48,6 +52,7 @@ def test_eval_ties_across_splits():
     from paper_2609_35440_amd import binding
 
     K, T, d, V = 2, 3, 1024, 4000
+    assert route(True, K, T, d, V)[:2] == [SPLIT, 250]
     g = torch.Generator().manual_seed(3)
     h = torch.randn(K, T, d, generator=g).to(torch.bfloat16).cuda()
     W = (0.02 * torch.randn(V, d, generator=g)).to(torch.bfloat16)
@@ -71,6 +76,7 @@ def test_more_tiles_than_half_the_chip(K, T, d, V):
     W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).to(torch.bfloat16)
     y = torch.randint(0, V, (K, T), generator=g, device="cuda", dtype=torch.int32)
     gain = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    assert route(False, K, T, d, V)[0] == 4 and route(False, K, T, d, V, final_module_dW=0)[0] == 1
     cut = binding.readout_fwd_bwd(h, gain, W, y, final_module_dW=True, row_loss=True)
     whole = binding.readout_fwd_bwd(h, gain, W, y, final_module_dW=False, row_loss=True)
     # the same fp32 logits; sums of up to 1600 chunks in another order: 2 x 1600 x 2^-24
