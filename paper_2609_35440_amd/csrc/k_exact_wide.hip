@@ -161,7 +161,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
         own_r2 = a.rstd[modoff + x0 + xo] * tau_k * kLog2e;
         own_tgt = a.targets[modoff + x0 + xo];
     }
-    if (!LL && a.bias && x0 + xo < nX) bx2 = a.bias[(long long)k * a.V + x0 + xo] * kLog2e;
+    if (!LL && a.bias && x0 + xo < nX) bx2 = bias2(a.bias[(long long)k * a.V + x0 + xo]);
 
     if (RAW) {
         for (int j = 8 * threadIdx.x; j < NW * DS; j += 8 * NTHR) {
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
             float gval = 0.f;
             if (LL) {
                 float ymask = yg < nY ? 0.f : -INFINITY;
-                if (BZ) ymask += side[yy] * kLog2e;
+                if (BZ) ymask += bias2(side[yy]);
                 const float zc = __builtin_fmaf(sxy, own_r2, ymask);
                 float alpha = 1.f;
                 if (__builtin_expect(__any(zc > m_run + kLazyThresh2), 0)) {  // wave-uniform

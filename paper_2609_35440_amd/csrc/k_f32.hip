@@ -220,7 +220,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
         own_r2 = a.rstd[modoff + xg] * tau * kLog2e;
         own_tgt = a.targets[modoff + xg];
     }
-    if (!LL && bk && xok) bx2 = bk[xg] * kLog2e;
+    if (!LL && bk && xok) bx2 = bias2(bk[xg]);
 
     // ---- streams
     // Y slab: instruction q writes rows 8 q + lane / 8 of the wave's 32, 16-byte
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused_f32(FusedArgs a) {
                 for (int i = 0; i < NR; ++i) {
                     const int yl = ylow + b * R + (R == 32 ? 8 * (i >> 2) : 0) + 4 * kq + (i & 3);
                     float zc = St[b][i] * own_r2;
-                    if (bk) zc = __builtin_fmaf(St[b][i], own_r2, (yl < rows ? bk[y0 + yl] : 0.f) * kLog2e);
+                    if (bk) zc = __builtin_fmaf(St[b][i], own_r2, yl < rows ? bias2(bk[y0 + yl]) : 0.f);
                     zc = yl < rows ? zc : -INFINITY;
                     St[b][i] = zc;
                     zmax = fmaxf(zmax, zc);

@@ -235,7 +235,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
             r2[j] = a.rstd[grow[j]] * (a.tau ? a.tau[grow[j] / a.T] : 1.f) * kLog2e;
             tgt[j] = a.targets[grow[j]];
         }
-        if (MODE == BGRAD && a.bias && ok) bx2[j] = a.bias[mod * (long long)a.nX + x] * kLog2e;
+        if (MODE == BGRAD && a.bias && ok) {
+            const float b = a.bias[mod * (long long)a.nX + x];
+            bx2[j] = XA ? bias2(b) : b * kLog2e;
+        }
     }
 
     issue(0);
@@ -281,7 +284,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_logits(LogitsArgs a) {
                         float z[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            z[e] = EXT ? __builtin_fmaf(acc[i][j][4 * g + e], r2[j], bv[e] * kLog2e)
+                            z[e] = EXT ? __builtin_fmaf(acc[i][j][4 * g + e], r2[j], XA ? bias2(bv[e]) : bv[e] * kLog2e)
                                        : acc[i][j][4 * g + e] * r2[j];
                             acc[i][j][4 * g + e] = z[e];
                         }

@@ -234,7 +234,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
             own_r2[r] = a.rstd[modoff + x0 + xo[r]] * tau_r * kLog2e;
             tgt_rel[r] = a.targets[modoff + x0 + xo[r]] - yy;
         }
-        if (!LL && a.bias && x0 + xo[r] < nX) bx2[r] = a.bias[(long long)k * a.V + x0 + xo[r]] * kLog2e;
+        if (!LL && a.bias && x0 + xo[r] < nX) {
+            const float b = a.bias[(long long)k * a.V + x0 + xo[r]];
+            bx2[r] = XA ? bias2(b) : b * kLog2e;
+        }
     }
     const bool has_bias = BZ || a.bias != nullptr;  // the bias variant always has one
 
@@ -438,7 +441,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
 #pragma unroll
                     for (int e = 0; e < EWC; ++e) {
                         float ymask = (yy + e < ylim) ? 0.f : -INFINITY;
-                        if (BZ && has_bias) ymask += side[yy + e] * kLog2e;
+                        if (BZ && has_bias) ymask += XA ? bias2(side[yy + e]) : side[yy + e] * kLog2e;
                         zc[e] = __builtin_fmaf(sxy[e], own_r2[r], ymask);
                         zmax = fmaxf(zmax, zc[e]);
                     }

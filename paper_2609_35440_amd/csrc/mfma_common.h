@@ -32,6 +32,14 @@ constexpr float kLazyThresh2 = 11.0f;
 // threshold re-bases it, with a factor of 0 on sums that are 0.
 constexpr float kNoMax = -3.402823466e38f;
 
+// A bias in base 2 for the calls defined in fp32: a finite one stays finite (the type's lowest
+// value, a common mask, times log2 e is past the range), so that a row whose target or
+// whose every entry is masked by it keeps a finite loss.
+__device__ __forceinline__ float bias2(float b) {
+    const float z = b * kLog2e;
+    return __builtin_isfinite(b) ? __builtin_amdgcn_fmed3f(z, kNoMax, -kNoMax) : z;
+}
+
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }

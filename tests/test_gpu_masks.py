@@ -78,3 +78,30 @@ def test_eval(cfg, K, T, d, V, keep, low):
     assert route_of(x, True)[0] == form
     losses, row_loss, top1 = run_exit_eval(x)
     check_exit_eval(few, losses, row_loss, top1 - lo, f"masked eval {keep} {low} d={d}", min_rows_for_agreement=100)
+
+
+@pytest.mark.parametrize("dtype,T,d,V", [("bf16", 40, 48, 3001), ("bf16", 40, 640, 3001), ("bf16", 9, 640, 100),
+                                         ("bf16", 20, 1800, 2001), ("bf16", 300, 72, 4097), ("bf16", 9, 3080, 600),
+                                         ("f32", 40, 264, 3001)])
+def test_lowest_value_everywhere_or_at_the_target(dtype, T, d, V):
+    """Calls defined in fp32: the type's lowest value is finite, and so is the loss of a row whose
+    every entry is masked by it (all alike: log V), or whose target is (the mask itself,
+    short of what base 2 can hold)."""
+    import torch
+
+    from paper_2609_35440_amd import binding
+
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(7)
+    h = torch.randn(2, T, d, generator=g, device="cuda").to(dt)
+    W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).to(dt)
+    gain = torch.ones(d, dtype=dt, device="cuda")
+    y = torch.full((2, T), V // 2, dtype=torch.int32, device="cuda")
+    low = torch.finfo(torch.float32).min
+    bias = torch.zeros(2, V, device="cuda")
+    bias[0] = low
+    bias[1, V // 2] = low
+    for r in (binding.readout_general(h, gain, W, y, bias=bias, row_loss=True), binding.exit_eval(h, gain, W, y, bias=bias)):
+        assert float((r.row_loss[0] - np.log(V)).abs().max()) <= 1e-5
+        assert bool((r.row_loss[1] > 2e38).all()) and bool(torch.isfinite(r.row_loss[1]).all())
+    assert bool((r.top1[0] == 0).all())
