@@ -124,7 +124,7 @@ __device__ __forceinline__ RowEnd finish_row(float m, float sx, float zy, bool t
         full = ((m - zy) + __log2f(s)) * kLn2;
     }
     o.inv_s = 1.f / s;
-    o.py1 = tok ? -sx * o.inv_s : 0.f;
+    o.py1 = tok ? (FINE ? -sx / s : -sx * o.inv_s) : 0.f;
     o.loss = !tok ? __int_as_float(0x7fc00000) : (ey > sx ? log1pf(sx / ey) : full);
     return o;
 }
