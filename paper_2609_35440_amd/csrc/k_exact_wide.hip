@@ -65,7 +65,8 @@ __device__ __forceinline__ int key(int r) {
     return GH % 16 == 0 ? (((r & 7) << 1) ^ ((r >> 2) & 1)) : (r & 7);
 }
 
-template <int MODE, int DS, bool EXT, bool SPL>
+// CS (LOCAL): see kChunkSums.
+template <int MODE, int DS, bool EXT, bool SPL, bool CS = false>
 __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
     constexpr bool LL = MODE == LOCAL;
     constexpr int NK = DS / 32, NB = DS / 16;
@@ -291,8 +292,33 @@ __global__ __launch_bounds__(NTHR, 1) void k_exact_wide(FusedArgs a) {
             const i32x4 nrs = chunk_rsrc(more ? c + 1 : c);
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
+                if constexpr (CS) {
+                    // a few blocks at a time, smallest plane first; the additions are kept here (see k_mfma.hip)
+                    constexpr int FLY = DS == 256 ? 8 : (DS == 384 ? 3 : 4);
+                    static_assert(NB / 2 % FLY == 0, "whole groups");
 #pragma unroll
-                for (int b = hf * (NB / 2); b < (hf + 1) * (NB / 2); ++b) {
+                    for (int b = hf * (NB / 2); b < (hf + 1) * (NB / 2); b += FLY) {
+                        bf16x4 t[FLY];
+                        f32x4 c4[FLY];
+#pragma unroll
+                        for (int i = 0; i < FLY; ++i) {
+                            t[i] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(slice + tr_off(b + i)));
+                            c4[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        }
+#pragma unroll
+                        for (int pl = 2; pl >= 0; --pl)
+#pragma unroll
+                            for (int i = 0; i < FLY; ++i) c4[i] = mfma16k16(t[i], gf[pl], c4[i]);
+#pragma unroll
+                        for (int i = 0; i < FLY; ++i) {
+                            acc[b + i] += c4[i];
+                            asm volatile("" : "+v"(acc[b + i]));
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+#pragma unroll
+                for (int b = hf * (NB / 2); !CS && b < (hf + 1) * (NB / 2); ++b) {
                     const bf16x4 t = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(slice + tr_off(b)));
 #pragma unroll
                     for (int pl = 0; pl < 3; ++pl) acc[b] = mfma16k16(t, gf[pl], acc[b]);
@@ -446,6 +472,10 @@ hipError_t launch_ds(const FusedArgs& a, int nmod, hipStream_t s) {
     if constexpr (MODE == LOCAL) {
         if (a.nsplit > 1) {
             hipLaunchKernelGGL((k_exact_wide<MODE, DS, EXT, true>), grid, dim3(NTHR), 0, s, a);
+            return hipGetLastError();
+        }
+        if (exact_chunk_sums(a, nmod)) {
+            hipLaunchKernelGGL((k_exact_wide<MODE, DS, EXT, false, true>), grid, dim3(NTHR), 0, s, a);
             return hipGetLastError();
         }
     }

@@ -138,15 +138,21 @@ __device__ __forceinline__ const bf16* tiled_readout_of(const FusedArgs& a, int 
 // slower rate.  Y is then the raw operand (R or h; dR_v = g * the sum).  The
 // width d is any multiple of 8 up to 8 DS; columns past it read as zeros and
 // are not written.
-template <int MODE, int DS, bool EXT, bool SPL, bool XA = false>
-__global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
+// CS (XA, LOCAL): a chunk's second product summed by itself before it joins the
+// accumulator (see kChunkSums).
+// (at d <= 256 two workgroups share a CU: at most 128 registers, 4 waves per SIMD)
+template <int MODE, int DS, bool EXT, bool SPL, bool XA = false, bool CS = false>
+__global__ __launch_bounds__(NTHR, CS && DS == 32 ? 4 : 1) void k_fused(FusedArgs a) {
     constexpr bool PC = MODE == LOCAL || MODE == RGRAD;     // second product
     static_assert(!XA || PC, "the exact form is of the passes with a second product");
+    static_assert(!CS || (XA && MODE == LOCAL && !SPL), "chunk sums");
     using G = Geo<DS, PC, XA>;
     constexpr int XR = G::XR;
     constexpr int NR = G::NR;
     constexpr int PR = G::PR;
     constexpr bool LL = MODE == LOCAL || MODE == EVAL;      // X = h, Y = readout
+    // per-lane addresses computed anew in every step where CS leaves no registers to hold them
+    constexpr bool ANEW = CS && (DS == 96 || DS == 192);
     constexpr bool RF = !PC;                                // operand registers fed from the tiled copy
     constexpr bool BZ = (MODE == LOCAL || MODE == EVAL) && EXT;  // per-chunk biases through LDS
     constexpr bool RM = RF && SPL;                               // operand registers fed row-major
@@ -358,6 +364,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         const int y0 = c * YC;
         const bool more = c + 1 < ck_hi;
         const i32x4 nrs = ChunkStream<DS>::rsrc(Y, nY, d, y0 + YC);
+        ChunkStream<DS> strm = stream;
+        if constexpr (ANEW) strm.template init<XA>(d, js, lane_now());
         // register-fed passes reload the operand registers with the next chunk
         // (the last chunk reloads itself: no branch around the loads)
         const __amdgpu_buffer_rsrc_t yn = rsrc_of(more ? c + 1 : c);
@@ -371,7 +379,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         if (PC) {
             // the widest slices recompute the per-lane part of the row-wise read
             // address each step (no register left to hold it)
-            const int ao = DS >= 224 ? layout::rowread_off<DS>(lane_now()) : a_off;
+            const int ao = DS >= 224 || ANEW ? layout::rowread_off<DS>(lane_now()) : a_off;
 #pragma unroll
             for (int kk = 0; kk < G::NK; ++kk) ay[kk] = *(LDS_AS bf16x8*)(cur + ao + 64 * kk);
         }
@@ -394,7 +402,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                     for (int xb = 0; xb < G::NXB; ++xb) S[xb] = mfma16(ay[kk], xlo[XA ? xb : 0][kk], S[xb]);
                 }
                 if (kk < kDmaA) {
-                    if (more) stream.issue_one(nrs, d, nxt, kk);
+                    if (more) strm.issue_one(nrs, d, nxt, kk);
                     __builtin_amdgcn_sched_barrier(0);  // keeps the instruction between these products
                 }
             }
@@ -512,7 +520,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
                 }
             }
         }
-        if (PC && more) stream.template issue_range<kDmaA, G::NI>(nrs, d, nxt);
+        if (PC && more) strm.template issue_range<kDmaA, G::NI>(nrs, d, nxt);
         if (!G::TWO) lds_barrier();
 
         // 64-row tiles: the second product runs at raised wave priority, so that
@@ -521,7 +529,52 @@ __global__ __launch_bounds__(NTHR, 1) void k_fused(FusedArgs a) {
         // d = 2048 with 32-row tiles it is 0.5% slower and not used)
         constexpr bool PRIO = PC && XR == 64;
         if (PRIO) __builtin_amdgcn_s_setprio(2);
-        if (PC) {
+        if constexpr (CS) {
+            // ---- second product as below, a half of the rows at a time, and each block's sum over the
+            // chunk, smallest plane first, added to the accumulator by itself.  One sum is in
+            // flight: the other wave of the SIMD fills the gaps, and there are no registers for more.
+            constexpr int NA = NR == 1 ? 2 : G::NB;  // transposed operands held (one half: read one block ahead)
+            bf16x4 tlo[NA], thi[NA];
+            const int l = ANEW ? lane_now() : lane;
+            const int t_lo = ANEW ? layout::trread_off<DS>(l, 0) : c_lo;
+            const int t_hi = ANEW ? layout::trread_off<DS>(l, 1) : c_hi;
+            auto rd = [&](int b) __attribute__((always_inline)) {
+                tlo[b % NA] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(cur + t_lo + 64 * b));
+                thi[b % NA] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(cur + t_hi + 64 * b));
+            };
+#pragma unroll
+            for (int b = 0; b < (NR == 1 ? 1 : G::NB); ++b) rd(b);
+#pragma unroll
+            for (int h = 0; h < NR; ++h) {
+                bf16x8 gfrag[G::NGP];
+                const int xg = 32 * h + (l & 31);
+#pragma unroll
+                for (int pl = 0; pl < G::NGP; ++pl)
+                    gfrag[pl] = *(bf16x8*)(gbuf + (pl * XR + xg) * YC + 8 * ((l >> 5) ^ ((xg >> 2) & 1)));
+                const float al = abuf[xg];
+                if (__any(al != 1.f)) {
+#pragma unroll
+                    for (int b = 0; b < G::NB; ++b)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) acc[b][h][i] *= al;
+                }
+#pragma unroll
+                for (int b = 0; b < G::NB; ++b) {
+                    if (NR == 1 && b + 1 < G::NB) rd(b + 1);
+                    bf16x8 at;
+                    at[0] = tlo[b % NA][0]; at[1] = tlo[b % NA][1]; at[2] = tlo[b % NA][2]; at[3] = tlo[b % NA][3];
+                    at[4] = thi[b % NA][0]; at[5] = thi[b % NA][1]; at[6] = thi[b % NA][2]; at[7] = thi[b % NA][3];
+                    f32x16 t = {};
+#pragma unroll
+                    for (int pl = G::NGP - 1; pl >= 0; --pl) t = mfma32(at, gfrag[pl], t);
+                    acc[b][h] += t;
+                    // here and now (the additions would sink to the next chunk, and with them
+                    // every block's sum would stay in registers)
+                    asm volatile("" : "+v"(acc[b][h]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else if (PC) {
             // ---- second product: acc[j][x] += sum_y Y[y][j] G[x][y] over this wave's columns
             bf16x8 gfrag[G::NGP][NR];
 #pragma unroll
@@ -884,6 +937,10 @@ hipError_t launch_exact_ds(const FusedArgs& a, int nmod, hipStream_t s) {
     if constexpr (MODE == LOCAL) {
         if (a.nsplit > 1) {
             hipLaunchKernelGGL((k_fused<MODE, DS, EXT, true, true>), grid, dim3(NTHR), 0, s, a);
+            return hipGetLastError();
+        }
+        if (exact_chunk_sums(a, nmod)) {
+            hipLaunchKernelGGL((k_fused<MODE, DS, EXT, false, true, true>), grid, dim3(NTHR), 0, s, a);
             return hipGetLastError();
         }
     }

@@ -117,6 +117,19 @@ bool exact_supported(int dtype, int d);
 int exact_rows(int d);
 hipError_t launch_local_loss_exact(const FusedArgs& a, bool ext, int nmod, hipStream_t s);
 hipError_t launch_readout_grad_exact(const FusedArgs& a, int nmod, hipStream_t s);
+// Whether a whole (unsplit) local-loss launch of the exact form sums each chunk's second
+// product by itself before it joins the accumulator: where rows' gain gradients are summed up (in
+// fp32; the other outputs are bf16 or do not see it) over more than 2048 readout rows.  The
+// matrix instruction cuts every product at the last bit of what it adds to, and over thousands of
+// chunks the cuts showed in dgain: its error at 16384 x 640 x 64000 is 1.2e-7 without chunk
+// sums, 4.1e-8 with (6.1e-8 on the vector ALU); at 2000 readout rows the same either way.  The
+// parts of split launches are short and meet in the merge.  4 x 8192 x 32000 tokens with and
+// without: d = 200 3.69 and 3.89 ms, 640 9.24 and 7.60, 1160 13.5 and 13.4, 1528 18.1 and 16.4; 4 x
+// 4096 x 1800 19.7 and 19.1, 2 x 4096 x 3072 15.9 and 14.9.
+constexpr int kChunkSums = 128;  // chunks of 16 readout rows
+inline bool exact_chunk_sums(const FusedArgs& a, int nmod) {
+    return (a.V + 15) / 16 > kChunkSums && (a.dg_mode == 2 || (a.dg_mode == 1 && a.m0 + nmod == a.K));
+}
 // the same for wider rows (k_exact_wide.hip): any bf16 width up to 4096
 int exact_wide_rows();
 hipError_t launch_local_loss_exact_wide(const FusedArgs& a, bool ext, int nmod, hipStream_t s);

@@ -109,3 +109,34 @@ def test_row_losses_of_wide_rows(d, T, V, bias):
     tol = 3e-7 + (n / 2) ** 0.5 * 2.0**-25 * 0.02 * d**0.5
     err = (got - ref).square().mean().sqrt()
     assert float(err) <= tol, (float(err), tol)
+
+
+@pytest.mark.parametrize("d", [200, 504, 640, 904, 1160, 1528, 1800, 3080, 4096])
+def test_gain_gradient_over_a_long_vocabulary(d):
+    """The exact forms, unsplit, over 2000 chunks of readout rows.  A term e n of dgain takes about
+    six roundings of 2.5e-8 (rms) of itself; their signs and the terms' are random, so the sum is
+    as close, 6e-8 of its norm.  (Accumulated chunk by chunk in the matrix instruction,
+    which cuts instead of rounding, e was off by enough for 9e-8.)"""
+    import torch
+
+    from paper_2609_35440_amd import binding
+    from tests.routes import route
+
+    T, V = 16384, 32000
+    assert route(False, 1, T, d, V)[0] == 1
+    g = torch.Generator(device="cuda").manual_seed(8)
+    h = torch.randn(1, T, d, generator=g, device="cuda").bfloat16()
+    W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).bfloat16()
+    y = torch.randint(0, V, (1, T), generator=g, device="cuda", dtype=torch.int32)
+    gain = (1 + 0.1 * torch.randn(d, generator=g, device="cuda")).bfloat16()
+    got = binding.readout_fwd_bwd(h, gain, W, y).dgain
+    W8 = W.double()
+    want = torch.zeros(d, dtype=torch.float64, device="cuda")
+    for t in range(0, T, 2048):
+        n = h[0, t:t + 2048].double()
+        n = n * torch.rsqrt(n.square().mean(1, keepdim=True) + 1e-6)
+        p = torch.softmax((n * gain.double()) @ W8.t(), 1)
+        p.scatter_add_(1, y[0, t:t + 2048].long()[:, None], torch.full((2048, 1), -1.0, dtype=torch.float64, device="cuda"))
+        want += ((p @ W8) * n).sum(0) / T
+    err = float((got.double() - want).norm() / want.norm())
+    assert err <= 6e-8, err
