@@ -99,10 +99,11 @@ size_t solo_readout_workspace_size(int K, int T, int d, int V, int dtype, int fi
  * 64 rows up to d = 1024 and 32 above, twice that in the forward-only
  * passes), "mfma_wide" (bf16 matrix-core kernels, d = 2560; 16-row tiles, 48
  * in the forward-only passes) or
- * "valu" (the fp32 family, for SOLO_F32 and for every other bf16 width: fp32
- * products and sums, on the fp32 matrix instructions; the name is that of the
- * vector-ALU kernels that served these calls first).  Returns "invalid" for
- * arguments solo_readout_fwd_bwd would reject.
+ * "valu" (the calls defined in fp32: SOLO_F32 on the fp32 matrix instructions, and
+ * every other bf16 width with logits, probabilities and sums of fp32 accuracy, from
+ * d = 72 on mostly as bf16 planes on the bf16 matrix instructions; nothing runs
+ * on the vector ALU any more, the name is that of the kernels that served these calls
+ * first).  Returns "invalid" for arguments solo_readout_fwd_bwd would reject.
  */
 const char* solo_readout_kernel_family(int K, int T, int d, int V, int dtype);
 
@@ -145,7 +146,10 @@ const char* solo_readout_kernel_family(int K, int T, int d, int V, int dtype);
  * stay unchanged until then.  The library allocates no memory, keeps no
  * pointer after returning and holds no global mutable state; concurrent
  * calls on different streams with different workspaces are safe.  Results are
- * bitwise reproducible for identical inputs (no floating-point atomics).
+ * bitwise reproducible for identical calls (no floating-point atomics).  The
+ * order of sums depends on the sizes and on which outputs are asked for: a
+ * module's loss and dh may differ in their last bits between calls with and
+ * without final_module_dW, or with other K.
  *
  * Errors: every argument check runs on the host before any launch; on error
  * nothing is enqueued and no output is touched.  SOLO_ERR_HIP means a launch

@@ -31,7 +31,7 @@
 // R = 32 while the accumulator fits the registers next to the streamed
 // operand (d <= 2048: 128 registers at 256 columns per wave), 16 above.
 //
-// Measured (K=2, T=1001, d=768, V=8003, fp32): 0.97 ms per training call, 14.7
+// Measured (K=2, T=1001, d=768, V=8003, fp32): 0.95 ms per training call, 14.7
 // with one thread per column on the vector ALU.
 //
 // Sums: a logit's k-sum is cut into pieces of 256, each summed by itself, so

@@ -26,8 +26,8 @@
 // workgroups are a few row tiles with all their splits and share both
 // operands' streams in its L2.
 //
-// Measured (4 x 16384 rows, d = 2048, V = 32000): exit evaluation 7.35 ms, 1.2
-// PFLOP/s in the product, against 8.4 ms of the fused pass; at d = 256 (4 x 8192) 0.67
+// Measured (4 x 16384 rows, d = 2048, V = 32000): exit evaluation 7.1 ms, 1.2
+// PFLOP/s in the product, against 8.7 ms of the fused pass; at d = 256 (4 x 8192) 0.65
 // against 1.79.  On two planes (4 x 8192 x 32000, d = 640): 2.3 ms, 115 on the vector ALU.
 #include "mfma_common.h"
 

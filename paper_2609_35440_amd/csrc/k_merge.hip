@@ -16,8 +16,8 @@
 // of 64 splits to 16 waves (565 us at d = 2048).
 //
 // Measured (fp32, K=2, T=1001, d=768, V=8003: 64 tiles): 2.22 ms per training
-// call with one workgroup per tile, 0.99 split.  bf16 exit evaluation of 4 x 16
-// rows, d=2048, V=32000: 2.10 ms on 4 workgroups, 0.09 split.
+// call with one workgroup per tile, 0.95 split.  bf16 exit evaluation of 4 x 16
+// rows, d=2048, V=32000: 2.10 ms on 4 workgroups, 0.064 split.
 #include "mfma_common.h"
 
 namespace solo {

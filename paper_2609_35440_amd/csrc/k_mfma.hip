@@ -984,11 +984,11 @@ int mfma_eval_rows(int d) { return d <= NW * 128 ? rows_of<128, false>() : rows_
 
 int mfma_rows(int d) { return d <= NW * 128 ? rows_of<128, true>() : rows_of<256, true>(); }
 
-// From d = 72 to 1536: up to 64 the fp32 kernels' narrow column slices are as fast or
-// faster (2 x 256 x 512 at d = 64: 45 us against 66; 4 x 8192 x 32000: 4.3 ms
-// against 3.9), and past 1536 two planes of 32 rows do not fit the registers
+// From d = 72 to 1536: up to 64 the fp32 kernels' narrow column slices are faster on most
+// sizes (training at d = 64: 2 x 256 x 512 46 us against 66, 2 x 1001 x 8003 135 against 247,
+// 20000 x 2000 0.76 ms against 1.34, but 4 x 8192 x 32000 4.5 ms against 3.6), and past 1536 two planes of 32 rows do not fit the registers
 // next to the accumulator.  At 4 x 8192 x 32000 tokens, against the fp32 kernels: d =
-// 640 7.6 ms against 35.8, d = 104 3.9 against 7.7 (fp32 storage).
+// 640 9.2 ms against 35.8, d = 104 3.7 against 7.7 (fp32 storage).
 bool exact_supported(int dtype, int d) { return dtype == 0 && d > 64 && d <= NW * 192; }
 int exact_rows(int d) { return d <= NW * 96 ? rows_of<96, true, true>() : rows_of<128, true, true>(); }
 hipError_t launch_local_loss_exact(const FusedArgs& a, bool ext, int nmod, hipStream_t s) {

@@ -184,7 +184,7 @@ bool make_plan(const solo_readout_args& a, bool eval, Plan* P, bool spare = true
 // Up to 1024 parts beside the whole tiles are looked at: 192 tiles (3 x 2048 x
 // 2048) want 4 ways, three full rounds of a quarter: training against V = 32000
 // 2.97 ms whole, 2.47 cut; 320 tiles (5 x 2048) 4.20 and 3.93; 3 x 1024 x 2560 3.40
-// and 2.58; ROT of 4 x 2048 x 2048 4.05 and 3.56.  More cuts gain little more.
+// and 2.58; ROT of 4 x 2048 x 2048 4.05 and 3.54.  More cuts gain little more.
 struct SplitCost {
     double chunk_us;    // one chunk of streamed rows of one workgroup
     double merge_us;    // the merge's launch
@@ -240,7 +240,8 @@ int local_splits(const Plan& P, int n, int K, int T, int d, int V, size_t room) 
 //          copies of bf16(g * h) it multiplies, `pass_rows` rows at a time,
 //          and its parts take the place of the readout copies.
 // The form with the least estimated time is taken.  Measured: 60 us per tile of
-// 256 x 256 of the product at d = 2048, 10 at d = 256; 1.05 and 1.28 us per chunk of 16
+// 256 x 256 of the product at d = 2048, 10 at d = 256 (planes of wide rows, 128 x 256: 100 us at
+// d = 3072, 155 at 4096); 1.05 and 1.28 us per chunk of 16
 // readout rows of the fused pass at d = 2048 (64 rows per tile) and 1024 (128),
 // 0.9 at d = 256 (128).  4 x 8192 x 32000 rows: product against fused pass 2.01
 // against 2.55 ms at d = 1024, 0.67 against 1.79 at d = 256.

@@ -134,7 +134,7 @@ inline bool exact_chunk_sums(const FusedArgs& a, int nmod) {
 int exact_wide_rows();
 hipError_t launch_local_loss_exact_wide(const FusedArgs& a, bool ext, int nmod, hipStream_t s);
 hipError_t launch_readout_grad_exact_wide(const FusedArgs& a, int nmod, hipStream_t s);
-// forward-only passes as a tiled product (k_logits.hip): d % 256 == 0
+// forward-only passes as a tiled product (k_logits.hip): d % 256 == 0, or on planes d % 8 == 0
 struct LogitsArgs {
     const bf16* X;          // [nX][d] stationary rows; module m of a launch x_stride elements further,
     long long x_stride;     // and module x_last another x_last_off (the terminal's own readout)

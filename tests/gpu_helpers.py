@@ -60,14 +60,14 @@ def row_loss_error_bound(h, gain, R, targets, tau, dtype, bias=None, eps=1e-6):
 
     The matrix-core kernels multiply the stored readout R by bf16(g * h_t), the
     exact product of two bf16 values rounded once to nearest even, and
-    accumulate in fp32; the vector-ALU kernels multiply in fp32.  Write
+    accumulate in fp32; the calls defined in fp32 multiply in fp32.  Write
     e_tj = rounded_tj - g_j h_tj for the operand's rounding.  The kernel's
     logit then differs from the exact one by
         tau r_t sum_j R_vj e_tj                      (the operand's rounding, exact)
       + tau r_t (an fp32 accumulation error of at most gamma sum_j |R_vj rounded_tj|)
     where gamma = n 2^-24 for n roundings along the accumulation: one per
     32-deep matrix instruction, the split-K tree and the scalings (d / 32 + 8)
-    on the matrix cores, d for the vector-ALU kernels' sequential sums.  With
+    on the bf16 kernels, d at most (sequential sums) where fp32 is defined.  With
     B_tv the absolute value of the first term plus the second, a row loss
     lse_t - z_{t,y} moves by at most max_v B_tv (the log-sum-exp is
     1-Lipschitz in the largest change) plus B_{t,y}; the exp2/log2

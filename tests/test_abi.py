@@ -80,7 +80,7 @@ def test_workspace_has_no_TV_term():
     assert b - a == 4 * 16384 * 28 + 512 * 2048 * 4 + 16384 * 2048 * 2
     # well below one module's T x V fp32 logits (2.1 GB at the 1B shape)
     assert a < 16384 * 32000 * 4 / 20
-    # vector-ALU family: 8-row token tiles, per-token records (p_y - 1 for the readout-gradient pass)
+    # the calls defined in fp32: gain partials of 8 rows, per-token records
     K, T, d, V = 2, 256, 64, 512
     assert B.workspace_size(K, T, d, V, B.SOLO_F32, True) == 3 * al(K * T * 4) + al(K * T * 16) + al(-(-T // 8) * d * 4)
     # invalid arguments -> 0
@@ -231,7 +231,7 @@ def test_general_workspace_sizes():
     # readout per head, one tiled copy each
     assert B.exit_eval_workspace_size(gargs()) == 3 * al(kt * 4) + wt
     assert B.exit_eval_workspace_size(gargs(readout_per_head=1, Wbar=P)) == 3 * al(kt * 4) + wt + al((K - 1) * tiled(V, d))
-    # the vector-ALU family (fp32) reads the row-major readout: no tiled copies
+    # the fp32 kernels read the row-major readout: no tiled copies
     assert B.exit_eval_workspace_size(gargs(dtype=B.SOLO_F32)) == 3 * al(kt * 4)
     # ROT: ones (d elements), the heads' rotated rows ((K-1) T d elements); fwd_bwd also
     # e and D ((K-1) T d floats each) and the transposed rotations ((K-1) d^2 elements)

@@ -27,7 +27,7 @@ pytestmark = pytest.mark.gpu
 
 K, T, V = 2, 70, 600
 
-# (id, dtype, d): 64-row matrix-core tiles, 32-row tiles, the wide tiling, vector-ALU bf16 and fp32
+# (id, dtype, d): 64-row matrix-core tiles, 32-row tiles, the wide tiling, bf16 widths defined in fp32, and fp32
 FAMILIES = [("mfma_d1024", "bf16", 1024), ("mfma_d2048", "bf16", 2048), ("wide_d2560", "bf16", 2560),
             ("valu_bf16_d72", "bf16", 72), ("valu_f32_d64", "f32", 64)]
 

@@ -1,5 +1,5 @@
 """GPU parity on a seeded sweep of random shapes: every kernel family and
-tiling (32- and 64-row matrix-core tiles, the wide tiling, the vector-ALU
+tiling (32- and 64-row matrix-core tiles, the wide tiling, the fp32
 family in bf16 and fp32), random module counts, ragged token and vocabulary
 counts, with and without the final module's readout gradient, the general
 entry point with random option sets, and exit evaluation across the
@@ -18,7 +18,7 @@ from tests.test_gpu_general import check_exit_eval, compare, oracle_general, run
 pytestmark = pytest.mark.gpu
 
 # widths per family: 64-row tiles (d <= 1024), 32-row tiles, the wide tiling,
-# bf16 widths of the vector-ALU family, fp32 (always vector-ALU)
+# bf16 widths defined in fp32, fp32
 WIDTHS_BF16 = [256, 512, 768, 1024, 1280, 1536, 1792, 2048, 2560, 40, 136]
 WIDTHS_F32 = [16, 64, 200]
 
@@ -88,7 +88,7 @@ def _rot_cases(n, seed):
     rng = np.random.default_rng(seed)
     out = []
     for i in range(n):
-        d = [256, 1024, 2048, 2560, 72, 1536][i % 6]  # both matrix-core tilings, vector-ALU bf16
+        d = [256, 1024, 2048, 2560, 72, 1536][i % 6]  # both bf16 tilings, a bf16 width defined in fp32
         K = int(rng.integers(2, 5))
         T = int(rng.integers(1, 90))
         V = int(rng.integers(1, 400))
@@ -120,7 +120,7 @@ def _eval_cases(n, seed):
     rng = np.random.default_rng(seed)
     out = []
     for i in range(n):
-        d = [256, 1024, 2048, 2560, 72, 24][i % 6]  # 128-, 64-, 48-row tiles, vector-ALU bf16 and fp32
+        d = [256, 1024, 2048, 2560, 72, 24][i % 6]  # 128-, 64-, 48-row tiles, a bf16 width defined in fp32, and fp32
         K = int(rng.integers(1, 4))
         T = int(rng.integers(1, 400))  # up to four 128-row tiles, ragged
         V = int(rng.integers(1, 600))

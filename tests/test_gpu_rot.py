@@ -31,7 +31,7 @@ CASES = [
     ("wide_d2560_all", "2b", dict(K=3, T=37, d=2560, V=300), ALL_ROT, ALL_FLAGS),
     ("valu_f32_all", "tiny", dict(K=3, T=37, d=24, V=45), ALL_ROT, ALL_FLAGS),
     ("valu_bf16_d72_all", "340m", dict(K=2, T=10, d=72, V=50), ALL_ROT, ALL_FLAGS),
-    # vector-ALU passes at a width whose rotation products run on the matrix cores
+    # passes defined in fp32 at a width whose rotation products run on the matrix cores
     ("valu_bf16_d3072_all", "1b", dict(K=2, T=20, d=3072, V=40), ALL_ROT, ALL_FLAGS),
     ("valu_f32_d256", "tiny", dict(K=3, T=21, d=256, V=30), dict(tau=True, rot=True),
      dict(final_module_dW=True, want_dtau=True)),
@@ -53,7 +53,7 @@ def test_identity_rotation_is_solo(cfg, ov):
     """R_k = I turns ROT into SOLO.  On the matrix-core families the rotated rows
     are bf16(g * h) itself, the operand the plain call rounds, so every logit,
     loss, row loss, readout and bias gradient is bit for bit the plain call's
-    (the vector-ALU family multiplies r, g and h in another order: to fp32
+    (the calls defined in fp32 multiply r, g and h in another order: to fp32
     rounding).  The input and gain gradients go through the rotate-back product
     (e split into two bf16 parts) and agree to its rounding (dh to one unit of
     its storage dtype's last place); the temperature

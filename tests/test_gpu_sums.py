@@ -111,8 +111,9 @@ def test_row_losses_of_wide_rows(d, T, V, bias):
     assert float(err) <= tol, (float(err), tol)
 
 
+@pytest.mark.parametrize("bias", [False, True], ids=["", "bias"])
 @pytest.mark.parametrize("d", [200, 504, 640, 904, 1160, 1528, 1800, 3080, 4096])
-def test_gain_gradient_over_a_long_vocabulary(d):
+def test_gain_gradient_over_a_long_vocabulary(d, bias):
     """The exact forms, unsplit, over 2000 chunks of readout rows.  A term e n of dgain takes about
     six roundings of 2.5e-8 (rms) of itself; their signs and the terms' are random, so the sum is
     as close, 6e-8 of its norm.  (Accumulated chunk by chunk in the matrix instruction,
@@ -129,13 +130,14 @@ def test_gain_gradient_over_a_long_vocabulary(d):
     W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).bfloat16()
     y = torch.randint(0, V, (1, T), generator=g, device="cuda", dtype=torch.int32)
     gain = (1 + 0.1 * torch.randn(d, generator=g, device="cuda")).bfloat16()
-    got = binding.readout_fwd_bwd(h, gain, W, y).dgain
-    W8 = W.double()
+    b = 0.5 * torch.randn(1, V, generator=g, device="cuda") if bias else None
+    got = binding.readout_general(h, gain, W, y, bias=b).dgain
+    W8, b8 = W.double(), b.double() if bias else 0.0
     want = torch.zeros(d, dtype=torch.float64, device="cuda")
     for t in range(0, T, 2048):
         n = h[0, t:t + 2048].double()
         n = n * torch.rsqrt(n.square().mean(1, keepdim=True) + 1e-6)
-        p = torch.softmax((n * gain.double()) @ W8.t(), 1)
+        p = torch.softmax((n * gain.double()) @ W8.t() + b8, 1)
         p.scatter_add_(1, y[0, t:t + 2048].long()[:, None], torch.full((2048, 1), -1.0, dtype=torch.float64, device="cuda"))
         want += ((p @ W8) * n).sum(0) / T
     err = float((got.double() - want).norm() / want.norm())
